@@ -287,7 +287,7 @@ static size_t carve(dcf_ctx *c, void *base, int mode, int nsteps, int seg_len) {
   c->U2 = cv.take<double>(nv * ncell);
   c->part = cv.take<double>(8 * RED_BLOCKS);
   c->force = cv.take<double>(4);
-  c->dtpart = cv.take<double>(std::max(update_blocks(g), flux_update_blocks(g)));
+  c->dtpart = cv.take<double>(std::max({update_blocks(g), flux_update_blocks(g), stage_tiles(g)}));
   g.flags = cv.take<unsigned>(64);
   for (int q = 0; q < NQ; ++q) c->qalt.Q[q] = g.ndim >= 2 ? cv.take<double>(nbox) : nullptr;
   if (mode >= 1) carve_adjoint(cv, g, c->adj);
@@ -485,6 +485,12 @@ static bool fused_stages(const dcf_ctx *c) {
   return g.source == SRC_MASSFLUX && g.bck[f] == BC_PERIODIC && g.bck[f + 1] == BC_PERIODIC;
 }
 
+// Partial maxima the last stage of a step leaves in dtpart.
+static unsigned dt_parts(const dcf_ctx *c) {
+  if (stage_fused(c->g)) return stage_tiles(c->g);
+  return fused_stages(c) ? flux_update_blocks(c->g) : update_blocks(c->g);
+}
+
 // A CFL step reduction left pending by the previous step (nparts partial
 // maxima in dtpart): the next fused step runs it with its first ghost fill.
 struct PendingDt {
@@ -507,10 +513,46 @@ static dcf_status rk3_stages(dcf_ctx *c, double *U, const double *dt, hipStream_
                              double *U1 = nullptr, double *U2 = nullptr,
                              double *dtpart = nullptr, int base = 0, bool box_ready = false,
                              bool write_next = false, const PendingDt *pend = nullptr,
-                             int nstages = 3) {
+                             int nstages = 3, const BoxOut *boxes = nullptr) {
   Dev &g = c->g;
   if (!U1) U1 = c->U1;
   if (!U2) U2 = c->U2;
+  if (stage_fused(g)) {
+    const double *in[3] = {U, U1, U2};
+    double *out[3] = {U1, U2, U};
+    const double a[3] = {0.0, 0.75, 1.0 / 3.0}, b[3] = {1.0, 0.25, 2.0 / 3.0};
+    Probe &pr = c->probe;
+    for (int k = 0; k < nstages; ++k) {
+      StageArgs A = {};
+      A.Un = U;
+      A.Uin = in[k];
+      A.Uout = out[k];
+      A.dt = dt;
+      A.a = a[k];
+      A.b = b[k];
+      if (k == 2) A.dtpart = dtpart;
+      if (boxes) A.box = boxes[k];
+      if (g.source == SRC_MASSFLUX) {
+        DCF_HIP(launch_prim_halo(g, in[k], st));
+        DCF_HIP(launch_force_direct(g, c->part, c->force, st));
+        A.force = c->force;
+      }
+      if (k == 0 && pend) {
+        A.part = c->dtpart;
+        A.nparts = pend->nparts;
+        A.cfl = pend->cfl;
+        A.dt_max = pend->dt_max;
+        A.dt_out = pend->dt;
+      }
+      // this launch does the work of every probed family; the first stage of a
+      // call is not a family-8 launch
+      const bool on = pr.which != 8 || k > 0 || box_ready;
+      if (on) pr.before(pr.which, st);
+      DCF_HIP(launch_stage(g, A, st));
+      if (on) pr.after(pr.which, st);
+    }
+    return DCF_OK;
+  }
   if (fused_stages(c)) {
     const double *in[3] = {U, U1, U2};
     double *out[3] = {U1, U2, U};
@@ -573,6 +615,18 @@ dcf_status dcf_rhs(dcf_ctx *c, const double *U, double *R, void *stream) {
   if (s) return s;
   if (!U || !R) return fail(DCF_EINVAL, "null array");
   hipStream_t st = (hipStream_t)stream;
+  if (stage_fused(c->g)) {
+    StageArgs A = {};
+    A.Un = A.Uin = U;
+    A.Rout = R;
+    if (c->g.source == SRC_MASSFLUX) {
+      DCF_HIP(launch_prim_halo(c->g, U, st));
+      DCF_HIP(launch_force_direct(c->g, c->part, c->force, st));
+      A.force = c->force;
+    }
+    DCF_HIP(launch_stage(c->g, A, st));
+    return DCF_OK;
+  }
   if ((s = eval_fluxes(c, U, st))) return s;
   DCF_HIP(launch_update(c->g, U, U, nullptr, R, nullptr, 0.0, 0.0, c->force, st));
   return DCF_OK;
@@ -726,7 +780,7 @@ dcf_status dcf_rk3_step_cfl(dcf_ctx *c, double *U, const double *dt, double cfl,
   if (!(dt_max > 0.0)) dt_max = 1.0e300;
   hipStream_t st = (hipStream_t)stream;
   if ((s = rk3_stages(c, U, dt, st, nullptr, nullptr, c->dtpart))) return s;
-  const unsigned nparts = fused_stages(c) ? flux_update_blocks(c->g) : update_blocks(c->g);
+  const unsigned nparts = dt_parts(c);
   DCF_HIP(launch_dt_final(c->dtpart, (int)nparts, cfl, dt_max, dt_next, st));
   return DCF_OK;
 }
@@ -740,18 +794,22 @@ dcf_status dcf_rk3_steps_cfl(dcf_ctx *c, double *U, double *dt, int nsteps, doub
   if (!(cfl > 0.0)) return fail(DCF_EINVAL, "cfl must be > 0");
   if (!(dt_max > 0.0)) dt_max = 1.0e300;
   hipStream_t st = (hipStream_t)stream;
-  const bool fused = fused_stages(c);
-  const unsigned nparts = fused ? flux_update_blocks(c->g) : update_blocks(c->g);
+  const bool fused = stage_fused(c->g) || fused_stages(c);
+  const unsigned nparts = dt_parts(c);
   const PendingDt pend{(int)nparts, cfl, dt_max, dt};
+  bool pending = false;
   for (int n = 0; n < nsteps; ++n) {
     // U is not touched between the steps of this call: each step after the
     // first starts from the primitive box the previous one left, and its
     // first ghost fill finishes the previous step's CFL reduction
     const bool chained = fused && n + 1 < nsteps;
     if ((s = rk3_stages(c, U, dt, st, nullptr, nullptr, c->dtpart, n & 1, fused && n > 0, chained,
-                        fused && n > 0 ? &pend : nullptr)))
+                        pending ? &pend : nullptr)))
       return s;
-    if (!chained) DCF_HIP(launch_dt_final(c->dtpart, (int)nparts, cfl, dt_max, dt, st));
+    // a stage launch's workgroups reduce the partial maxima themselves, each
+    // of them: only while they are few
+    pending = chained && (!stage_fused(c->g) || nparts <= 2048);
+    if (!pending) DCF_HIP(launch_dt_final(c->dtpart, (int)nparts, cfl, dt_max, dt, st));
   }
   return DCF_OK;
 }
@@ -866,6 +924,14 @@ static dcf_status segment_step(dcf_ctx *c, int k, hipStream_t st) {
   double *Ua = c->seg + (long)k * M, *Ub = Ua + M;
   DCF_HIP(launch_copy(Ub, Ua, M, st));
   double *S1 = c->sst + (long)(2 * k) * M, *S2 = S1 + M;
+  if (stage_fused(g) && c->boxc && g.source == SRC_NONE) {
+    BoxOut boxes[3];
+    for (int s = 0; s < 3; ++s) {
+      const Dev gs = stage_box(c, k, s);
+      for (int q = 0; q < NQ; ++q) boxes[s].Q[q] = gs.Q[q];
+    }
+    return rk3_stages(c, Ub, gr.dt, st, S1, S2, nullptr, 0, false, false, nullptr, 3, boxes);
+  }
   if (c->boxc && g.source == SRC_NONE) {  // the same three stages, keeping each stage's boxes
     const double *in[3] = {Ub, S1, S2};
     double *out[3] = {S1, S2, Ub};

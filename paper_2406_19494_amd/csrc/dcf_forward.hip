@@ -4,6 +4,7 @@
 // (CFL time step, body force, diagnostics, wall-pressure cost).
 #include <algorithm>
 
+#include "dcf_cells.hpp"
 #include "dcf_kernels.hpp"
 
 namespace dcf {
@@ -68,45 +69,6 @@ __global__ void k_line_length(const double *dx, int n, double *out) {
   *out = L;
 }
 
-// ---------------------------------------------------------------------------
-// Primitives from conserved variables (Eq. (2), ideal gas).
-// ---------------------------------------------------------------------------
-// From (rho, rho u, rho v, rho w, E) with zeros for unused momenta.
-__device__ __forceinline__ void prim_of_state(const Dev &g, const double *s, double *q) {
-  const int nd = g.ndim;
-  double rho = s[0];
-  double ir = rcp_nr(rho);
-  double u = s[1] * ir;
-  double v = nd >= 2 ? s[2] * ir : 0.0;
-  double w = nd >= 3 ? s[3] * ir : 0.0;
-  double E = s[4];
-  double p = (g.gamma - 1.0) * (E - 0.5 * rho * (u * u + v * v + w * w));
-  q[QR] = rho;
-  q[QU] = u;
-  q[QV] = v;
-  q[QW] = w;
-  q[QP] = p;
-  q[QT] = p * ir * g.iR;
-}
-
-__device__ __forceinline__ void cons_to_prim(const Dev &g, const double *U, long c, double *q) {
-  const int nd = g.ndim;
-  const long nc = g.ncell;
-  double rho = U[c];
-  double ir = rcp_nr(rho);
-  double u = U[nc + c] * ir;
-  double v = nd >= 2 ? U[2 * nc + c] * ir : 0.0;
-  double w = nd >= 3 ? U[3 * nc + c] * ir : 0.0;
-  double E = U[(long)(nd + 1) * nc + c];
-  double p = (g.gamma - 1.0) * (E - 0.5 * rho * (u * u + v * v + w * w));
-  q[QR] = rho;
-  q[QU] = u;
-  q[QV] = v;
-  q[QW] = w;
-  q[QP] = p;
-  q[QT] = p * ir * g.iR;
-}
-
 __global__ void k_init_state(Dev g, const double *P, double *U) {
   long c = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= g.ncell) return;
@@ -121,156 +83,8 @@ __global__ void k_init_state(Dev g, const double *P, double *U) {
 }
 
 // ---------------------------------------------------------------------------
-// Primitive box with halos.  The halo fill of the paper (values assigned to
-// halo cells, Section 3.2) is applied axis by axis, x then y then z, each
-// over the full extent of the axes filled before; a ghost thread resolves
-// that chain for its own cell: it follows the source cells back to the
-// interior (or to a Dirichlet profile) and applies the per-axis ghost
-// transforms in x, y, z order.
+// Primitive box with halos (the ghost cells by ghost_chain).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int ghost_source(int kind, int side, int m, int n) {
-  if (kind == BC_PERIODIC) return side == 0 ? n - 1 - m : m;
-  if (kind == BC_ZEROGRAD) return side == 0 ? 0 : n - 1;
-  return side == 0 ? m : n - 1 - m;  // walls mirror
-}
-
-// Sources of the ghost chain: the conserved state (the source cell is
-// converted here) or the primitive box once its interior is filled (the
-// source's primitives and mu are copied).
-struct FromState {
-  const double *U;
-  __device__ __forceinline__ void load(const Dev &g, const int *s, double *q, double &mu) const {
-    cons_to_prim(g, U, ((long)s[2] * g.n[1] + s[1]) * g.n[0] + s[0], q);
-    mu = -1.0;
-  }
-  __device__ __forceinline__ double pressure(const Dev &g, const int *w) const {
-    double q[6];
-    cons_to_prim(g, U, ((long)w[2] * g.n[1] + w[1]) * g.n[0] + w[0], q);
-    return q[QP];
-  }
-};
-struct FromBox {
-  __device__ __forceinline__ void load(const Dev &g, const int *s, double *q, double &mu) const {
-    const int nd = g.ndim;
-    const long sb = bidx(g, s[0], s[1], s[2]);
-    q[QR] = g.Q[QR][sb];
-    q[QU] = g.Q[QU][sb];
-    q[QV] = nd >= 2 ? g.Q[QV][sb] : 0.0;
-    q[QW] = nd >= 3 ? g.Q[QW][sb] : 0.0;
-    q[QP] = g.Q[QP][sb];
-    if (g.visc != VISC_NONE) {
-      q[QT] = g.Q[QT][sb];
-      mu = g.Q[QMU][sb];
-    } else {
-      q[QT] = q[QP] / (q[QR] * g.R);
-      mu = -1.0;
-    }
-  }
-  __device__ __forceinline__ double pressure(const Dev &g, const int *w) const {
-    return g.Q[QP][bidx(g, w[0], w[1], w[2])];
-  }
-};
-
-// Ghost cell p (box index b) through the halo-fill chain: follow the source
-// cells back to the interior (or to a Dirichlet profile), then apply the
-// per-axis ghost transforms in x, y, z order; mu is recomputed unless the
-// source's is still valid (copied and no transform changed T).
-template <class Src>
-__device__ __forceinline__ void ghost_chain(const Dev &g, const int *p, long b, const Src &src) {
-  const int nd = g.ndim;
-  int s[3] = {p[0], p[1], p[2]};
-  int side[3] = {0, 0, 0};
-  bool gh[3] = {false, false, false};
-  int top = -1;
-  for (int d = 0; d < nd; ++d) {
-    if (p[d] < 0 || p[d] >= g.n[d]) {
-      gh[d] = true;
-      side[d] = p[d] < 0 ? 0 : 1;
-      int m = side[d] == 0 ? -1 - p[d] : p[d] - g.n[d];
-      int kind = g.bck[2 * d + side[d]];
-      if (kind == BC_DIRICHLET)
-        top = d;
-      else
-        s[d] = ghost_source(kind, side[d], m, g.n[d]);
-    }
-  }
-  double q[6];
-  double mu = -1.0;  // mu of the source while no transform changed T
-  int start = 0;
-  if (top >= 0) {
-    const int d = top;
-    const int t1 = tan1(d), t2 = tan2(d);
-    int a = t1 < nd ? (t1 < d ? p[t1] : s[t1]) : 0;
-    int bb = t2 < nd ? (t2 < d ? p[t2] : s[t2]) : 0;
-    a = min(max(a, 0), g.n[t1] - 1);
-    bb = min(max(bb, 0), g.n[t2] - 1);
-    const long nt = (long)g.n[t1] * g.n[t2];
-    const long o = (long)bb * g.n[t1] + a;
-    const double *P = g.dir[2 * d + side[d]];
-    q[QR] = P[o];
-    q[QU] = P[nt + o];
-    q[QV] = P[2 * nt + o];
-    q[QW] = P[3 * nt + o];
-    q[QP] = P[4 * nt + o];
-    q[QT] = q[QP] / (q[QR] * g.R);
-    mu = -1.0;  // recomputed below
-    start = top + 1;
-  } else {
-    src.load(g, s, q, mu);  // the interior source cell
-  }
-  for (int d = start; d < nd; ++d) {
-    if (!gh[d]) continue;
-    const int face = 2 * d + side[d];
-    const int kind = g.bck[face];
-    if (!is_wall(kind)) continue;  // copies keep the value
-    double src_n = q[QU + d];
-    q[QU] = -q[QU];
-    q[QV] = -q[QV];
-    q[QW] = -q[QW];
-    const int t1 = tan1(d), t2 = tan2(d);
-    const int a = t1 < nd ? (t1 < d ? p[t1] : s[t1]) : 0;
-    const int bb = t2 < nd ? (t2 < d ? p[t2] : s[t2]) : 0;
-    const double sigma = side[d] == 0 ? 1.0 : -1.0;
-    if (kind == BC_POROUS && face == g.pface) {
-      if (a >= g.pb && a < g.pe && bb >= 0 && bb < g.n[t2]) {
-        // Darcy transpiration through the porous strip: inward-normal
-        // velocity -K (p_w - p_inf)/p_inf, p_w of the first interior cell.
-        int w[3];
-        w[d] = side[d] == 0 ? 0 : g.n[d] - 1;
-        w[t1] = a;
-        w[t2] = bb;
-        const double pw = src.pressure(g, w);
-        int kk = bb * (g.pe - g.pb) + (a - g.pb);
-        double vn = -g.K[kk] * (pw - g.pinf) / g.pinf;
-        q[QU + d] = 2.0 * sigma * vn - src_n;
-      }
-    } else if (kind == BC_DISTURB && a >= 0 && a < g.n[t1]) {
-      // Disturbance wall (Section 3.2, Eq. (8)): prescribed inward-normal
-      // velocity A sin(2 pi kappa x) at the wall-face centre, (A, kappa)
-      // taken from the boundary parameters.
-      const double *th = g.K + g.doff[face];
-      double vn = th[0] * sin(2.0 * M_PI * g.xm[t1][a] * th[1]);
-      q[QU + d] = 2.0 * sigma * vn - src_n;
-    }
-    if (g.Tw[face] > 0.0) {  // isothermal; adiabatic keeps rho and T
-      double Tg = 2.0 * g.Tw[face] - q[QT];
-      if (!(Tg > 0.0)) atomicOr(g.flags, 1u);
-      q[QT] = Tg;
-      q[QR] = q[QP] / (g.R * Tg);
-      mu = -1.0;
-    }
-  }
-  g.Q[QR][b] = q[QR];
-  g.Q[QU][b] = q[QU];
-  if (nd >= 2) g.Q[QV][b] = q[QV];
-  if (nd >= 3) g.Q[QW][b] = q[QW];
-  g.Q[QP][b] = q[QP];
-  if (g.visc != VISC_NONE) {
-    g.Q[QT][b] = q[QT];
-    g.Q[QMU][b] = mu >= 0.0 ? mu : viscosity(g, q[QT]);
-  }
-}
-
 // Interior cells: primitives of their own conserved state (x-fastest,
 // coalesced).
 __device__ __forceinline__ void prim_interior_body(const Dev &g, const double *U, unsigned t) {
@@ -707,18 +521,6 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double *sh /*[NV*BS]*
   for (int q = 0; q < NV; ++q) v[q] = sh[q * BS];
 }
 
-// Maximum over a 256-thread workgroup: within each 64-lane wavefront by lane
-// exchanges, then over the 4 wavefronts through LDS (sh: 4 doubles).  The
-// maximum is exact, so its value does not depend on the order.
-__device__ __forceinline__ double block_max(double v, double *sh) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  __syncthreads();  // a previous call's readers of sh are done
-  if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = v;
-  __syncthreads();
-  return fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-}
-
 // Body force, pass 1.  The volume-weighted sum of the unforced x-momentum
 // right-hand side, sum_c V_c R_c = -sum_D sum_c A_D (F_D(c+1/2) - F_D(c-1/2))
 // with A_D = V_c / dx_D constant along a grid line, telescopes along every
@@ -860,27 +662,6 @@ __global__ void __launch_bounds__(256) k_force_final(const double *part, int npa
   }
   block_sum<2>(v, sh);
   if (threadIdx.x == 0) f[0] = -v[0] / v[1];
-}
-
-// Signal rate of one cell, sum_d (|u_d| + c)/dx_d + 2 nu_eff sum_d 1/dx_d^2
-// (nu_eff = max(4/3, gamma/Pr) mu/rho); dt = cfl / max over cells.
-__device__ __forceinline__ double cell_sigma(const Dev &g, const double *q, const int *pos) {
-  double y;  // 1 / (rho cs)
-  double cs = sound_speed(g.gamma, q[QR], q[QP], y);
-  double conv = 0.0, inv2 = 0.0;
-  for (int d = 0; d < g.ndim; ++d) {
-    double id = g.idx[d][pos[d]];
-    conv += (fabs(q[QU + d]) + cs) * id;
-    inv2 += id * id;
-  }
-  double sig = conv;
-  if (g.visc != VISC_NONE) {
-    double mu = viscosity(g, q[QT]);
-    double nu = fmax(4.0 / 3.0, g.gamma / g.Pr) * mu * (cs * y);  // mu / rho
-    sig += 2.0 * nu * inv2;
-  }
-  if (!(sig < 1.0e300)) sig = 1.0e300;  // non-finite: flagged elsewhere
-  return sig;
 }
 
 // ---------------------------------------------------------------------------
@@ -1707,6 +1488,7 @@ void batch_entry_sizes(BatchEntry &e) {
   e.nb_upd = grid_for(g.ncell);
   e.nb_dt = grid_capped(g.ncell, RED_BLOCKS);
   e.nwmax = x_window(g);
+  stage_entry_sizes(e);
   for (int D = 0; D < 3; ++D) {
     e.yz_nbx[D] = e.yz_nby[D] = e.yz_ntot[D] = 0;
     if (D == 0 || D >= g.ndim) continue;
@@ -1740,7 +1522,11 @@ static hipError_t batch_step_t(const BatchEntry *tab, const BatchEntry *h, int n
   const unsigned ny = (unsigned)n;
   if (cfl > 0.0) {
     kb_dt_partial<<<dim3(md, ny), 256, 0, st>>>(tab);
-    kb_dt_final<<<ny, 256, 0, st>>>(tab, cfl);
+    if (!stage_fused(h[0].g)) kb_dt_final<<<ny, 256, 0, st>>>(tab, cfl);
+  }
+  if (stage_fused(h[0].g)) {
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_batch_stages(tab, h, n, cfl, st);
   }
   const size_t shm = sizeof(double) * Slots<NDIM, VISC>::NC * nw;
   if (NDIM >= 2) {

@@ -6,6 +6,36 @@
 
 namespace dcf {
 
+// Arguments of one stage Uout = a Un + b (Uin + dt R(Uin)).
+struct StageArgs {
+  const double *Un, *Uin;
+  double *Uout;
+  double *Rout;         // non-null: write R(Uin) here instead of the update
+  const double *dt;     // step size (device)
+  double a, b;
+  const double *force;  // constant-mass-flux body force (null: no source)
+  double *dtpart;       // non-null: the largest signal rate of each tile's new state
+  BoxOut box;           // non-null arrays: the primitive box of Uin, ghosts included
+  // non-null: the step size is not in dt yet but the CFL step of these partial
+  // maxima; every workgroup reduces them, the first one writes dt_out
+  const double *part;
+  int nparts;
+  double cfl, dt_max;
+  double *dt_out;
+};
+
+// Whether a grid's stages run as one launch each, the workgroups of that launch
+// (the length of dtpart), and the launch.
+bool stage_fused(const Dev &g);
+unsigned stage_tiles(const Dev &g);
+hipError_t launch_stage(const Dev &g, const StageArgs &A, hipStream_t st);
+struct BatchEntry;
+void stage_entry_sizes(BatchEntry &e);
+// The three stages of every solve of a batch, one launch each (cfl > 0: the
+// first one also reduces each solve's CFL partials).
+hipError_t launch_batch_stages(const BatchEntry *tab_dev, const BatchEntry *tab_host, int n,
+                               double cfl, hipStream_t st);
+
 constexpr int RED_BLOCKS = 1024;  // partial-sum slots of the two-pass reductions
 
 // One solve of a batched step: its context, its buffers and the number of
@@ -22,6 +52,7 @@ struct BatchEntry {
   unsigned yz_nbx[3], yz_nby[3], yz_ntot[3];  // tile grids of the y and z fluxes
   unsigned fu_nbx, fu_nby, fu_ntot;           // tile grid of the fused last-direction kernel
   int nwmax;            // x-flux LDS window length
+  unsigned st_tiles, st_nbx;  // tiles of the one-launch stage, tiles along x
 };
 
 // Fills the per-kernel workgroup counts of an entry (host side).

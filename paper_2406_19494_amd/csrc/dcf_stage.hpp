@@ -1,0 +1,174 @@
+// dcf_stage.hpp -- device code of the fused Runge-Kutta stage: the flux of one
+// face in its own frame, the primitives of a cell or ghost cell converted while
+// a tile is loaded, and the update of one cell.
+#pragma once
+
+#include "dcf_cells.hpp"
+#include "dcf_kernels.hpp"
+
+namespace dcf {
+
+// The step size of a stage (all NT threads; sh: NT / 64 doubles).
+template <int NT>
+__device__ __forceinline__ double stage_dt(const StageArgs &A, bool first, double *sh) {
+  if (A.Rout) return 0.0;
+  if (!A.part) return A.dt[0];
+  double m = 0.0;
+  for (int b = threadIdx.x; b < A.nparts; b += NT) m = fmax(m, A.part[b]);
+  m = block_max<NT>(m, sh);
+  const double dt = fmin(A.dt_max, A.cfl / m);
+  if (first && threadIdx.x == 0) A.dt_out[0] = dt;
+  return dt;
+}
+
+// Primitives (rho, u, v, w, p, T, mu) of cell p of the state U, interior or
+// ghost (at most three cells outside): interior cells and the images of
+// periodic axes are converted from the state, other ghosts follow the halo
+// chain.
+template <int NDIM, bool VISC>
+__device__ __forceinline__ void load_prims(const Dev &g, const double *U, const int *p,
+                                           double *q) {
+  int w[3] = {0, 0, 0};
+  bool inside = true, own = true;
+#pragma unroll
+  for (int d = 0; d < NDIM; ++d) {
+    const int n = g.n[d];
+    int x = p[d];
+    own = own && x >= 0 && x < n;
+    if (g.bck[2 * d] == BC_PERIODIC) x = x < 0 ? x + n : (x >= n ? x - n : x);
+    inside = inside && x >= 0 && x < n;
+    w[d] = x;
+  }
+  double mu = -1.0;
+  if (inside) {
+    const long nc = g.ncell;
+    const long c = ((long)w[2] * g.n[1] + w[1]) * g.n[0] + w[0];
+    double s[5];
+    s[0] = U[c];
+    s[1] = U[nc + c];
+    s[2] = NDIM >= 2 ? U[2 * nc + c] : 0.0;
+    s[3] = NDIM >= 3 ? U[3 * nc + c] : 0.0;
+    s[4] = U[(NDIM + 1) * nc + c];
+    prim_of_state_t<NDIM>(g, s, q);
+    if (own && !(finite_pos(q[QR]) && finite_pos(q[QP]))) atomicOr(g.flags, 1u);
+  } else {
+    ghost_value<NDIM>(g, p, FromState{U}, q, mu);
+  }
+  if (VISC) q[QMU] = viscosity(g, q[QT]);
+}
+
+// Total flux F = F^c - F^d (Eq. (6)) at one face in the face's own frame:
+// G = (mass, normal, first and second tangential momentum, energy).  P(m, o)
+// is primitive m (rho, u_n, u_t1, u_t2, p, T, mu) of the cell at offset o from
+// the face (o = -3 .. 2; the face lies between offsets -1 and 0); Dv(r, o) the
+// tangential velocity derivatives of that cell: r = 0 the tangential
+// divergence d u_t1/d t1 + d u_t2/d t2, r = 1, 2 d u_n/d t1, d u_n/d t2.  mf is
+// d xi/d n at the face.
+template <int NDIM, bool VISC, int SCH, class PA, class DA>
+__device__ __forceinline__ void frame_flux(const Dev &g, const PA &P, const DA &Dv, double mf,
+                                           double *G) {
+  double qL[5], qR[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    if ((m == 2 && NDIM < 2) || (m == 3 && NDIM < 3)) {
+      qL[m] = qR[m] = 0.0;
+      continue;
+    }
+    const double v0 = P(m, -3), v1 = P(m, -2), v2 = P(m, -1);
+    const double v3 = P(m, 0), v4 = P(m, 1), v5 = P(m, 2);
+    if (SCH == SCHEME_TENO6A)
+      teno6a_pair(v0, v1, v2, v3, v4, v5, qL[m], qR[m]);
+    else
+      weno5_pair(v0, v1, v2, v3, v4, v5, qL[m], qR[m]);
+  }
+  if (SCH == SCHEME_TENO6A) {
+    // interpolation limiter: a side whose reconstructed density or pressure
+    // is not positive takes its own cell's primitives (first order)
+    if (!(qL[0] > 0.0 && qL[4] > 0.0))
+#pragma unroll
+      for (int m = 0; m < 5; ++m)
+        qL[m] = ((m == 2 && NDIM < 2) || (m == 3 && NDIM < 3)) ? 0.0 : P(m, -1);
+    if (!(qR[0] > 0.0 && qR[4] > 0.0))
+#pragma unroll
+      for (int m = 0; m < 5; ++m)
+        qR[m] = ((m == 2 && NDIM < 2) || (m == 3 && NDIM < 3)) ? 0.0 : P(m, 0);
+  }
+  hllc(qL, qR, g.gamma, g.gm1i, G);
+  if constexpr (VISC) {
+    // Dissipative flux (Eqs. (4)-(5), Fourier's law): 4th-order (TENO6-A:
+    // 6th-order) central interpolation and differences
+    constexpr bool SIX = SCH == SCHEME_TENO6A;
+    auto face = [&](auto f) {
+      return SIX ? interp6(f(-3), f(-2), f(-1), f(0), f(1), f(2))
+                 : interp4(f(-2), f(-1), f(0), f(1));
+    };
+    auto diff = [&](auto f) {
+      return (SIX ? dface6(f(-3), f(-2), f(-1), f(0), f(1), f(2))
+                  : dface4(f(-2), f(-1), f(0), f(1))) * mf;
+    };
+    const double muf = face([&](int o) { return P(6, o); });
+    const double uf = face([&](int o) { return P(1, o); });
+    const double dun = diff([&](int o) { return P(1, o); });
+    const double dT = diff([&](int o) { return P(5, o); });
+    double tn = (4.0 / 3.0) * dun;
+    if constexpr (NDIM >= 2) tn -= (2.0 / 3.0) * face([&](int o) { return Dv(0, o); });
+    tn *= muf;
+    double en = uf * tn + muf * g.cpPr * dT;
+    G[1] -= tn;
+    if constexpr (NDIM >= 2) {
+      const double t1 = muf * (face([&](int o) { return Dv(1, o); }) +
+                               diff([&](int o) { return P(2, o); }));
+      en += face([&](int o) { return P(2, o); }) * t1;
+      G[2] -= t1;
+    }
+    if constexpr (NDIM >= 3) {
+      const double t2 = muf * (face([&](int o) { return Dv(2, o); }) +
+                               diff([&](int o) { return P(3, o); }));
+      en += face([&](int o) { return P(3, o); }) * t2;
+      G[3] -= t2;
+    }
+    G[4] -= en;
+  }
+  if (!(fabs(G[0]) + fabs(G[4]) < 1.0e300)) atomicOr(g.flags, 1u);  // non-finite flux
+}
+
+// The stage update of cell c (at p) from its right-hand side R (rho, the
+// three momenta, E): source, then Uout = a Un + b (Uin + dt R), or R itself.
+// Returns the signal rate of the new state when want_sigma.
+template <int NDIM>
+__device__ __forceinline__ double update_state(const Dev &g, const StageArgs &A, const int *p,
+                                               double dt, double *R, bool want_sigma) {
+  constexpr int NV = NDIM + 2;
+  const long nc = g.ncell;
+  const long c = ((long)(NDIM >= 3 ? p[2] : 0) * g.n[1] + (NDIM >= 2 ? p[1] : 0)) * g.n[0] + p[0];
+  // every load before the first store: Un may be Uout itself
+  double un[NV], ui[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    un[v] = A.Un[v * nc + c];
+    ui[v] = A.Uin[v * nc + c];
+  }
+  if (A.force) {
+    const double f = A.force[0];
+    R[1] += f;
+    R[4] += f * (ui[1] * rcp_nr(ui[0]));
+  }
+  if (A.Rout) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) A.Rout[v * nc + c] = R[v == NV - 1 ? 4 : v];
+    return 0.0;
+  }
+  double st[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const double uo = A.a * un[v] + A.b * (ui[v] + dt * R[v == NV - 1 ? 4 : v]);
+    A.Uout[v * nc + c] = uo;
+    st[v == NV - 1 ? 4 : v] = uo;
+  }
+  if (!want_sigma) return 0.0;
+  double q[6];
+  prim_of_state_t<NDIM>(g, st, q);
+  return cell_sigma(g, q, p);
+}
+
+}  // namespace dcf
