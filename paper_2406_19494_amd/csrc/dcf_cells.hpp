@@ -66,22 +66,26 @@ __device__ __forceinline__ int ghost_source(int kind, int side, int m, int n) {
 }
 
 // Sources of the ghost chain: the conserved state (the source cell is
-// converted here) or the primitive box once its interior is filled (the
-// source's primitives and mu are copied).
+// converted here), the primitive box once its interior is filled, or the LDS
+// window of a tile once its interior and periodic cells are (the source's
+// primitives and mu are copied).  A window holds the images of periodic axes,
+// so it is addressed by the source without their wrap.
 struct FromState {
   const double *U;
-  __device__ __forceinline__ void load(const Dev &g, const int *s, double *q, double &mu) const {
+  __device__ __forceinline__ void load(const Dev &g, const int *s, const int *, double *q,
+                                       double &mu) const {
     cons_to_prim(g, U, ((long)s[2] * g.n[1] + s[1]) * g.n[0] + s[0], q);
     mu = -1.0;
   }
-  __device__ __forceinline__ double pressure(const Dev &g, const int *w) const {
+  __device__ __forceinline__ double pressure(const Dev &g, const int *w, const int *) const {
     double q[6];
     cons_to_prim(g, U, ((long)w[2] * g.n[1] + w[1]) * g.n[0] + w[0], q);
     return q[QP];
   }
 };
 struct FromBox {
-  __device__ __forceinline__ void load(const Dev &g, const int *s, double *q, double &mu) const {
+  __device__ __forceinline__ void load(const Dev &g, const int *s, const int *, double *q,
+                                       double &mu) const {
     const int nd = g.ndim;
     const long sb = bidx(g, s[0], s[1], s[2]);
     q[QR] = g.Q[QR][sb];
@@ -97,8 +101,34 @@ struct FromBox {
       mu = -1.0;
     }
   }
-  __device__ __forceinline__ double pressure(const Dev &g, const int *w) const {
+  __device__ __forceinline__ double pressure(const Dev &g, const int *w, const int *) const {
     return g.Q[QP][bidx(g, w[0], w[1], w[2])];
+  }
+};
+
+// Window of a tile: NP arrays of PS values (rho, the NDIM velocities, p and,
+// viscous, T, mu), x and y from (x0, y0) with pitch W.
+template <int NDIM, bool VISC> struct FromWindow {
+  const double *lds;
+  int x0, y0, W, PS;
+  __device__ __forceinline__ void load(const Dev &g, const int *, const int *sw, double *q,
+                                       double &mu) const {
+    const double *v = lds + (NDIM >= 2 ? (sw[1] - y0) * W : 0) + sw[0] - x0;
+    q[QR] = v[0];
+    q[QU] = v[PS];
+    q[QV] = NDIM >= 2 ? v[2 * PS] : 0.0;
+    q[QW] = NDIM >= 3 ? v[3 * PS] : 0.0;
+    q[QP] = v[(NDIM + 1) * PS];
+    if (VISC) {
+      q[QT] = v[(NDIM + 2) * PS];
+      mu = v[(NDIM + 3) * PS];
+    } else {
+      q[QT] = q[QP] * rcp_nr(q[QR]) * g.iR;
+      mu = -1.0;
+    }
+  }
+  __device__ __forceinline__ double pressure(const Dev &g, const int *, const int *ww) const {
+    return lds[(NDIM + 1) * PS + (NDIM >= 2 ? (ww[1] - y0) * W : 0) + ww[0] - x0];
   }
 };
 
@@ -111,6 +141,7 @@ __device__ __forceinline__ void ghost_value(const Dev &g, const int *p, const Sr
                                             double &mu) {
   constexpr int nd = NDIM;
   int s[3] = {p[0], p[1], p[2]};
+  int sw[3] = {p[0], p[1], p[2]};  // the source without the wrap of periodic axes
   int side[3] = {0, 0, 0};
   bool gh[3] = {false, false, false};
   int top = -1;
@@ -125,6 +156,7 @@ __device__ __forceinline__ void ghost_value(const Dev &g, const int *p, const Sr
         top = d;
       else
         s[d] = ghost_source(kind, side[d], m, g.n[d]);
+      if (kind != BC_PERIODIC) sw[d] = s[d];
     }
   }
   mu = -1.0;  // mu of the source while no transform changed T
@@ -151,7 +183,7 @@ __device__ __forceinline__ void ghost_value(const Dev &g, const int *p, const Sr
     mu = -1.0;  // recomputed by the caller
     start = top + 1;
   } else {
-    src.load(g, s, q, mu);  // the interior source cell
+    src.load(g, s, sw, q, mu);  // the interior source cell
   }
 #pragma unroll
   for (int d = 0; d < nd; ++d) {
@@ -175,7 +207,11 @@ __device__ __forceinline__ void ghost_value(const Dev &g, const int *p, const Sr
         w[d] = side[d] == 0 ? 0 : g.n[d] - 1;
         w[t1] = a;
         w[t2] = bb;
-        const double pw = src.pressure(g, w);
+        int ww[3];
+        ww[d] = w[d];
+        ww[t1] = t1 < nd ? (t1 < d ? p[t1] : sw[t1]) : 0;
+        ww[t2] = t2 < nd ? (t2 < d ? p[t2] : sw[t2]) : 0;
+        const double pw = src.pressure(g, w, ww);
         int kk = bb * (g.pe - g.pb) + (a - g.pb);
         double vn = -g.K[kk] * (pw - g.pinf) / g.pinf;
         q[QU + d] = 2.0 * sigma * vn - src_n;

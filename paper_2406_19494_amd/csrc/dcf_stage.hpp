@@ -21,12 +21,11 @@ __device__ __forceinline__ double stage_dt(const StageArgs &A, bool first, doubl
   return dt;
 }
 
-// Primitives (rho, u, v, w, p, T, mu) of cell p of the state U, interior or
-// ghost (at most three cells outside): interior cells and the images of
-// periodic axes are converted from the state, other ghosts follow the halo
-// chain.
+// Primitives (rho, u, v, w, p, T, mu) of cell p of the state U when it is an
+// interior cell or its image along periodic axes (at most three cells
+// outside); false for the other ghost cells, which follow the halo chain.
 template <int NDIM, bool VISC>
-__device__ __forceinline__ void load_prims(const Dev &g, const double *U, const int *p,
+__device__ __forceinline__ bool load_prims(const Dev &g, const double *U, const int *p,
                                            double *q) {
   int w[3] = {0, 0, 0};
   bool inside = true, own = true;
@@ -39,22 +38,19 @@ __device__ __forceinline__ void load_prims(const Dev &g, const double *U, const 
     inside = inside && x >= 0 && x < n;
     w[d] = x;
   }
-  double mu = -1.0;
-  if (inside) {
-    const long nc = g.ncell;
-    const long c = ((long)w[2] * g.n[1] + w[1]) * g.n[0] + w[0];
-    double s[5];
-    s[0] = U[c];
-    s[1] = U[nc + c];
-    s[2] = NDIM >= 2 ? U[2 * nc + c] : 0.0;
-    s[3] = NDIM >= 3 ? U[3 * nc + c] : 0.0;
-    s[4] = U[(NDIM + 1) * nc + c];
-    prim_of_state_t<NDIM>(g, s, q);
-    if (own && !(finite_pos(q[QR]) && finite_pos(q[QP]))) atomicOr(g.flags, 1u);
-  } else {
-    ghost_value<NDIM>(g, p, FromState{U}, q, mu);
-  }
+  if (!inside) return false;
+  const long nc = g.ncell;
+  const long c = ((long)w[2] * g.n[1] + w[1]) * g.n[0] + w[0];
+  double s[5];
+  s[0] = U[c];
+  s[1] = U[nc + c];
+  s[2] = NDIM >= 2 ? U[2 * nc + c] : 0.0;
+  s[3] = NDIM >= 3 ? U[3 * nc + c] : 0.0;
+  s[4] = U[(NDIM + 1) * nc + c];
+  prim_of_state_t<NDIM>(g, s, q);
+  if (own && !(finite_pos(q[QR]) && finite_pos(q[QP]))) atomicOr(g.flags, 1u);
   if (VISC) q[QMU] = viscosity(g, q[QT]);
+  return true;
 }
 
 // Total flux F = F^c - F^d (Eq. (6)) at one face in the face's own frame:
@@ -132,26 +128,40 @@ __device__ __forceinline__ void frame_flux(const Dev &g, const PA &P, const DA &
   if (!(fabs(G[0]) + fabs(G[4]) < 1.0e300)) atomicOr(g.flags, 1u);  // non-finite flux
 }
 
-// The stage update of cell c (at p) from its right-hand side R (rho, the
+// What the update of one cell reads, loaded before the face fluxes so that the
+// memory round trip passes while they are computed.
+template <int NDIM> struct CellIn {
+  double un[NDIM + 2], ui[NDIM + 2], id[NDIM];
+};
+
+template <int NDIM>
+__device__ __forceinline__ void load_cell(const Dev &g, const StageArgs &A, const int *p,
+                                          CellIn<NDIM> &in) {
+  const long nc = g.ncell;
+  const long c = ((long)(NDIM >= 3 ? p[2] : 0) * g.n[1] + (NDIM >= 2 ? p[1] : 0)) * g.n[0] + p[0];
+#pragma unroll
+  for (int v = 0; v < NDIM + 2; ++v) {
+    in.un[v] = A.Un[v * nc + c];
+    in.ui[v] = A.Uin[v * nc + c];
+  }
+#pragma unroll
+  for (int d = 0; d < NDIM; ++d) in.id[d] = g.idx[d][p[d]];
+}
+
+// The stage update of the cell at p from its right-hand side R (rho, the
 // three momenta, E): source, then Uout = a Un + b (Uin + dt R), or R itself.
 // Returns the signal rate of the new state when want_sigma.
 template <int NDIM>
 __device__ __forceinline__ double update_state(const Dev &g, const StageArgs &A, const int *p,
-                                               double dt, double *R, bool want_sigma) {
+                                               const CellIn<NDIM> &in, double dt, double *R,
+                                               bool want_sigma) {
   constexpr int NV = NDIM + 2;
   const long nc = g.ncell;
   const long c = ((long)(NDIM >= 3 ? p[2] : 0) * g.n[1] + (NDIM >= 2 ? p[1] : 0)) * g.n[0] + p[0];
-  // every load before the first store: Un may be Uout itself
-  double un[NV], ui[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    un[v] = A.Un[v * nc + c];
-    ui[v] = A.Uin[v * nc + c];
-  }
   if (A.force) {
     const double f = A.force[0];
     R[1] += f;
-    R[4] += f * (ui[1] * rcp_nr(ui[0]));
+    R[4] += f * (in.ui[1] * rcp_nr(in.ui[0]));
   }
   if (A.Rout) {
 #pragma unroll
@@ -161,7 +171,7 @@ __device__ __forceinline__ double update_state(const Dev &g, const StageArgs &A,
   double st[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    const double uo = A.a * un[v] + A.b * (ui[v] + dt * R[v == NV - 1 ? 4 : v]);
+    const double uo = A.a * in.un[v] + A.b * (in.ui[v] + dt * R[v == NV - 1 ? 4 : v]);
     A.Uout[v * nc + c] = uo;
     st[v == NV - 1 ? 4 : v] = uo;
   }
