@@ -258,7 +258,8 @@ __device__ __forceinline__ void ghost_chain(const Dev &g, const int *p, long b, 
 
 // Signal rate of one cell, sum_d (|u_d| + c)/dx_d + 2 nu_eff sum_d 1/dx_d^2
 // (nu_eff = max(4/3, gamma/Pr) mu/rho); dt = cfl / max over cells.
-__device__ __forceinline__ double cell_sigma(const Dev &g, const double *q, const int *pos) {
+__device__ __forceinline__ double cell_sigma(const Dev &g, const double *q, const int *pos,
+                                             int law) {
   double y;  // 1 / (rho cs)
   double cs = sound_speed(g.gamma, q[QR], q[QP], y);
   double conv = 0.0, inv2 = 0.0;
@@ -268,13 +269,17 @@ __device__ __forceinline__ double cell_sigma(const Dev &g, const double *q, cons
     inv2 += id * id;
   }
   double sig = conv;
-  if (g.visc != VISC_NONE) {
-    double mu = viscosity(g, q[QT]);
+  if (law != VISC_NONE) {
+    double mu = viscosity(g, q[QT], law);
     double nu = fmax(4.0 / 3.0, g.gamma / g.Pr) * mu * (cs * y);  // mu / rho
     sig += 2.0 * nu * inv2;
   }
   if (!(sig < 1.0e300)) sig = 1.0e300;  // non-finite: flagged elsewhere
   return sig;
+}
+
+__device__ __forceinline__ double cell_sigma(const Dev &g, const double *q, const int *pos) {
+  return cell_sigma(g, q, pos, g.visc);
 }
 
 // Maximum over a workgroup of NT threads (whole wavefronts): within each
@@ -291,6 +296,21 @@ __device__ __forceinline__ double block_max(double v, double *sh) {
   double m = sh[0];
 #pragma unroll
   for (int w = 1; w < NT / 64; ++w) m = fmax(m, sh[w]);
+  return m;
+}
+
+// Sum over a workgroup of NT threads, likewise; a fixed order (pairs of lanes,
+// then the wavefronts in turn).
+template <int NT>
+__device__ __forceinline__ double block_total(double v, double *sh) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  __syncthreads();  // a previous call's readers of sh are done
+  if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = v;
+  __syncthreads();
+  double m = sh[0];
+#pragma unroll
+  for (int w = 1; w < NT / 64; ++w) m += sh[w];
   return m;
 }
 

@@ -46,6 +46,7 @@ struct Dev {
   const double *dx[3], *idx[3], *mc[3], *mf[3];
   const double *xm[3];   // cell-centre coordinates (midpoint of the two faces)
   double Lx;             // the x cell widths summed in index order (an x line's length)
+  double vol;            // product of the axes' lengths, each summed so
   // gas
   double gamma, R, Pr, cp, mu_ref, T_ref, vparam;
   double gm1i, cpPr;     // 1/(gamma - 1) and cp/Pr
@@ -159,16 +160,20 @@ __device__ __forceinline__ double sound_speed(double gamma, double rho, double p
 }
 
 // Dynamic viscosity: power law, or Sutherland's law (Section 3.2).
-__device__ __forceinline__ double viscosity(const Dev &g, double T) {
+__device__ __forceinline__ double viscosity(const Dev &g, double T, int law) {
   // (T/T_ref)^omega as exp(omega log(T/T_ref)): a few ulp, half the cost of pow
-  if (g.visc == VISC_POWER) return g.mu_ref * exp(g.vparam * log(T * g.iTref));
-  if (g.visc == VISC_SUTHERLAND) {
+  if (law == VISC_POWER) return g.mu_ref * exp(g.vparam * log(T * g.iTref));
+  if (law == VISC_SUTHERLAND) {
     // t^{3/2} (1 + s) / (t + s) with t^{3/2} = t^2 / sqrt(t)
     double t = T * g.iTref;
     double s = g.vparam * g.iTref;
     return g.mu_ref * (1.0 + s) * (t * t * rsq_nr(t)) * rcp_nr(t + s);
   }
   return 0.0;
+}
+
+__device__ __forceinline__ double viscosity(const Dev &g, double T) {
+  return viscosity(g, T, g.visc);
 }
 
 // WENO5-JS (Section 2.1): both reconstructions at the face between v2 and
@@ -217,6 +222,12 @@ __device__ __forceinline__ void weno5_pair(double v0, double v1, double v2, doub
   yr = nr * dl * r;
 }
 
+// Fixes a value where it is computed: the compiler otherwise moves the
+// arithmetic behind a later selection into a branch per side, which a
+// wavefront with both kinds of lanes runs one after the other and which ends
+// the block that its instructions could be scheduled in.
+__device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
+
 // HLLC flux in the face frame.  q = (rho, u_n, u_t1, u_t2, p) on each side;
 // F = (mass, normal momentum, t1 momentum, t2 momentum, energy).  Ties at
 // 0 <= S select the left-side state.  Star state written with one
@@ -235,34 +246,23 @@ __device__ __forceinline__ void hllc(const double *qL, const double *qR, double 
   double SR = fmax(uL + cL, uR + cR);
   double mL = rL * (SL - uL), mR = rR * (SR - uR);
   double Ss = (pR - pL + uL * mL - uR * mR) * rcp_nr(mL - mR);
-  if (0.0 <= SL) {
-    F[0] = rL * uL;
-    F[1] = rL * uL * uL + pL;
-    F[2] = rL * uL * vL;
-    F[3] = rL * uL * wL;
-    F[4] = uL * (EL + pL);
-    return;
-  }
-  if (SR < 0.0) {
-    F[0] = rR * uR;
-    F[1] = rR * uR * uR + pR;
-    F[2] = rR * uR * vR;
-    F[3] = rR * uR * wR;
-    F[4] = uR * (ER + pR);
-    return;
-  }
+  // 0 <= SL implies 0 <= S*, and SR < 0 implies S* < 0: on a supersonic face
+  // the selected side's wave term vanishes, F = F(U_K) (no branch: the
+  // reconstructions of the next variables and this arithmetic interleave)
   const bool left = (0.0 <= Ss);
   double r = left ? rL : rR, u = left ? uL : uR, v = left ? vL : vR, w = left ? wL : wR;
   double p = left ? pL : pR, E = left ? EL : ER, S = left ? SL : SR, m = left ? mL : mR;
+  const double SLm = fmin(SL, 0.0), SRp = fmax(SR, 0.0);
+  const double Sw = left ? SLm : SRp;
   double inv = rcp_nr(S - Ss);
   double Us0 = m * inv;
   double Us4 = (E * (S - u) + (Ss - u) * (m * Ss + p)) * inv;
   double fm = r * u;
-  F[0] = fm + S * (Us0 - r);
-  F[1] = fm * u + p + S * (Us0 * Ss - fm);
-  F[2] = fm * v + S * (Us0 * v - r * v);
-  F[3] = fm * w + S * (Us0 * w - r * w);
-  F[4] = u * (E + p) + S * (Us4 - E);
+  F[0] = fm + Sw * (Us0 - r);
+  F[1] = fm * u + p + Sw * (Us0 * Ss - fm);
+  F[2] = fm * v + Sw * (Us0 * v - r * v);
+  F[3] = fm * w + Sw * (Us0 * w - r * w);
+  F[4] = u * (E + p) + Sw * (Us4 - E);
 }
 
 // TENO6-A (Fu, Hu & Adams: targeted ENO, six points, adaptive dissipation):

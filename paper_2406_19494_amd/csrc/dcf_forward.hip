@@ -52,23 +52,6 @@ __global__ void k_metrics(int kind, double lo, double hi, double beta, int n, do
   }
 }
 
-// The cell widths of an axis summed in index order (one thread: the order of
-// the sum is part of the value).  Widths are loaded 16 at a time, all loads
-// of a group issued before its adds, so the sum waits for one memory round
-// trip per group instead of one per cell.
-__global__ void k_line_length(const double *dx, int n, double *out) {
-  double L = 0.0;
-  for (int i0 = 0; i0 < n; i0 += 16) {
-    double t[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) t[u] = i0 + u < n ? dx[i0 + u] : 0.0;
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (i0 + u < n) L += t[u];
-  }
-  *out = L;
-}
-
 __global__ void k_init_state(Dev g, const double *P, double *U) {
   long c = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= g.ncell) return;
@@ -1141,10 +1124,6 @@ hipError_t launch_axpy(double *y, double a, const double *x, long n, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_line_length(const double *dx, int n, double *out, hipStream_t st) {
-  k_line_length<<<1, 1, 0, st>>>(dx, n, out);
-  return hipGetLastError();
-}
 hipError_t launch_metrics(int kind, double lo, double hi, double beta, int n, double *dx,
                           double *idx, double *mc, double *mf, double *xm, hipStream_t st) {
   k_metrics<<<grid_for(n + 1), 256, 0, st>>>(kind, lo, hi, beta, n, dx, idx, mc, mf, xm);
@@ -1522,9 +1501,9 @@ static hipError_t batch_step_t(const BatchEntry *tab, const BatchEntry *h, int n
   const unsigned ny = (unsigned)n;
   if (cfl > 0.0) {
     kb_dt_partial<<<dim3(md, ny), 256, 0, st>>>(tab);
-    if (!stage_fused(h[0].g)) kb_dt_final<<<ny, 256, 0, st>>>(tab, cfl);
+    if (h[0].g.ndim != 2) kb_dt_final<<<ny, 256, 0, st>>>(tab, cfl);
   }
-  if (stage_fused(h[0].g)) {
+  if (h[0].g.ndim == 2) {
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_batch_stages(tab, h, n, cfl, st);
   }

@@ -14,6 +14,8 @@ struct StageArgs {
   const double *dt;     // step size (device)
   double a, b;
   const double *force;  // constant-mass-flux body force (null: no source)
+  const double *fpart;  // non-null: partial sums of the body force instead (3D)
+  int nfpart;
   double *dtpart;       // non-null: the largest signal rate of each tile's new state
   BoxOut box;           // non-null arrays: the primitive box of Uin, ghosts included
   // non-null: the step size is not in dt yet but the CFL step of these partial
@@ -29,6 +31,11 @@ struct StageArgs {
 bool stage_fused(const Dev &g);
 unsigned stage_tiles(const Dev &g);
 hipError_t launch_stage(const Dev &g, const StageArgs &A, hipStream_t st);
+// The body force of a stage from its state A.Uin alone, where that is built (3D
+// stages of launch_stage): partial sums into part (RED_BLOCKS doubles), which
+// the stage adds up.
+bool stage_force_from_state(const Dev &g);
+hipError_t launch_stage_force(const Dev &g, StageArgs &A, double *part, hipStream_t st);
 struct BatchEntry;
 void stage_entry_sizes(BatchEntry &e);
 // The three stages of every solve of a batch, one launch each (cfl > 0: the
@@ -65,8 +72,6 @@ hipError_t launch_batch_step(const BatchEntry *tab_dev, const BatchEntry *tab_ho
 
 hipError_t launch_metrics(int kind, double lo, double hi, double beta, int n, double *dx,
                           double *idx, double *mc, double *mf, double *xm, hipStream_t st);
-// out[0] = dx[0] + dx[1] + ... + dx[n-1], summed in index order.
-hipError_t launch_line_length(const double *dx, int n, double *out, hipStream_t st);
 hipError_t launch_init_state(const Dev &g, const double *P, double *U, hipStream_t st);
 hipError_t launch_prim_halo(const Dev &g, const double *U, hipStream_t st);
 hipError_t launch_fluxes(const Dev &g, hipStream_t st);

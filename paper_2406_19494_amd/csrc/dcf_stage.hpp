@@ -21,6 +21,16 @@ __device__ __forceinline__ double stage_dt(const StageArgs &A, bool first, doubl
   return dt;
 }
 
+// The body force from the partial sums of k_force3 (all NT threads; sh: NT / 64
+// doubles): f = -(volume sum of the x-momentum right-hand side) / volume.
+template <int NT>
+__device__ __forceinline__ double stage_force(const Dev &g, const StageArgs &A, double *sh) {
+  if (!A.fpart) return 0.0;
+  double v = 0.0;
+  for (int b = threadIdx.x; b < A.nfpart; b += NT) v += A.fpart[b];
+  return -block_total<NT>(v, sh) / g.vol;
+}
+
 // Primitives (rho, u, v, w, p, T, mu) of cell p of the state U when it is an
 // interior cell or its image along periodic axes (at most three cells
 // outside); false for the other ghost cells, which follow the halo chain.
@@ -59,73 +69,105 @@ __device__ __forceinline__ bool load_prims(const Dev &g, const double *U, const 
 // the face (o = -3 .. 2; the face lies between offsets -1 and 0); Dv(r, o) the
 // tangential velocity derivatives of that cell: r = 0 the tangential
 // divergence d u_t1/d t1 + d u_t2/d t2, r = 1, 2 d u_n/d t1, d u_n/d t2.  mf is
-// d xi/d n at the face.
-template <int NDIM, bool VISC, int SCH, class PA, class DA>
-__device__ __forceinline__ void frame_flux(const Dev &g, const PA &P, const DA &Dv, double mf,
+// d xi/d n at the face.  False when the flux is not finite.
+template <int NDIM, bool VISC, int SCH, bool PRELOAD, class PA, class DA>
+__device__ __forceinline__ bool frame_flux(const Dev &g, const PA &P, const DA &Dv, double mf,
                                            double *G) {
+  constexpr bool SIX = SCH == SCHEME_TENO6A;
+  constexpr bool on[7] = {true, true, NDIM >= 2, NDIM >= 3, true, VISC, VISC};
+  // PRELOAD: the reconstructions' stencils first, and the other loads before
+  // the Riemann solver, so that a face waits for LDS twice instead of 20 times
+  // (at 80 VGPRs; without, each variable's are read where they are used)
+  double v[7][6];
+  auto load = [&](int m) {
+#pragma unroll
+    for (int o = -3; o < 3; ++o)
+      v[m][o + 3] = on[m] && (m < 5 || SIX || (o >= -2 && o < 2)) ? P(m, o) : 0.0;
+  };
+  double dv[3][6];
+  auto load_d = [&](int r) {
+#pragma unroll
+    for (int o = -3; o < 3; ++o) dv[r][o + 3] = SIX || (o >= -2 && o < 2) ? Dv(r, o) : 0.0;
+  };
+  if (PRELOAD) {
+#pragma unroll
+    for (int m = 0; m < 5; ++m) load(m);
+    __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink them to their uses)
+  }
   double qL[5], qR[5];
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    if ((m == 2 && NDIM < 2) || (m == 3 && NDIM < 3)) {
+    if (!on[m]) {
       qL[m] = qR[m] = 0.0;
       continue;
     }
-    const double v0 = P(m, -3), v1 = P(m, -2), v2 = P(m, -1);
-    const double v3 = P(m, 0), v4 = P(m, 1), v5 = P(m, 2);
-    if (SCH == SCHEME_TENO6A)
-      teno6a_pair(v0, v1, v2, v3, v4, v5, qL[m], qR[m]);
+    if (!PRELOAD) load(m);
+    const double *x = v[m];
+    if (SIX)
+      teno6a_pair(x[0], x[1], x[2], x[3], x[4], x[5], qL[m], qR[m]);
     else
-      weno5_pair(v0, v1, v2, v3, v4, v5, qL[m], qR[m]);
+      weno5_pair(x[0], x[1], x[2], x[3], x[4], x[5], qL[m], qR[m]);
   }
-  if (SCH == SCHEME_TENO6A) {
+  if (SIX) {
     // interpolation limiter: a side whose reconstructed density or pressure
     // is not positive takes its own cell's primitives (first order)
     if (!(qL[0] > 0.0 && qL[4] > 0.0))
 #pragma unroll
-      for (int m = 0; m < 5; ++m)
-        qL[m] = ((m == 2 && NDIM < 2) || (m == 3 && NDIM < 3)) ? 0.0 : P(m, -1);
+      for (int m = 0; m < 5; ++m) qL[m] = v[m][2];
     if (!(qR[0] > 0.0 && qR[4] > 0.0))
 #pragma unroll
-      for (int m = 0; m < 5; ++m)
-        qR[m] = ((m == 2 && NDIM < 2) || (m == 3 && NDIM < 3)) ? 0.0 : P(m, 0);
+      for (int m = 0; m < 5; ++m) qR[m] = v[m][3];
+  }
+  if (PRELOAD && VISC) {
+    __builtin_amdgcn_sched_barrier(0);
+    load(5);
+    load(6);
+#pragma unroll
+    for (int r = 0; r < NDIM && NDIM > 1; ++r) load_d(r);
+    __builtin_amdgcn_sched_barrier(0);
   }
   hllc(qL, qR, g.gamma, g.gm1i, G);
+  // Dissipative flux (Eqs. (4)-(5), Fourier's law): 4th-order (TENO6-A:
+  // 6th-order) central interpolation and differences
+  double tn = 0.0, t1 = 0.0, t2 = 0.0, en = 0.0;
   if constexpr (VISC) {
-    // Dissipative flux (Eqs. (4)-(5), Fourier's law): 4th-order (TENO6-A:
-    // 6th-order) central interpolation and differences
-    constexpr bool SIX = SCH == SCHEME_TENO6A;
-    auto face = [&](auto f) {
-      return SIX ? interp6(f(-3), f(-2), f(-1), f(0), f(1), f(2))
-                 : interp4(f(-2), f(-1), f(0), f(1));
+    auto face = [&](const double *x) {
+      return SIX ? interp6(x[0], x[1], x[2], x[3], x[4], x[5])
+                 : interp4(x[1], x[2], x[3], x[4]);
     };
-    auto diff = [&](auto f) {
-      return (SIX ? dface6(f(-3), f(-2), f(-1), f(0), f(1), f(2))
-                  : dface4(f(-2), f(-1), f(0), f(1))) * mf;
+    auto diff = [&](const double *x) {
+      return (SIX ? dface6(x[0], x[1], x[2], x[3], x[4], x[5])
+                  : dface4(x[1], x[2], x[3], x[4])) * mf;
     };
-    const double muf = face([&](int o) { return P(6, o); });
-    const double uf = face([&](int o) { return P(1, o); });
-    const double dun = diff([&](int o) { return P(1, o); });
-    const double dT = diff([&](int o) { return P(5, o); });
-    double tn = (4.0 / 3.0) * dun;
-    if constexpr (NDIM >= 2) tn -= (2.0 / 3.0) * face([&](int o) { return Dv(0, o); });
+    auto tangential = [&](int r) {
+      if (!PRELOAD) load_d(r);
+      return face(dv[r]);
+    };
+    if (!PRELOAD) {
+      asm volatile("" ::: "memory");  // read again, not held since
+#pragma unroll
+      for (int m = 1; m < 7; ++m)
+        if (m != 4) load(m);
+    }
+    const double muf = face(v[6]);
+    tn = (4.0 / 3.0) * diff(v[1]);
+    if constexpr (NDIM >= 2) tn -= (2.0 / 3.0) * tangential(0);
     tn *= muf;
-    double en = uf * tn + muf * g.cpPr * dT;
-    G[1] -= tn;
+    en = face(v[1]) * tn + muf * g.cpPr * diff(v[5]);
     if constexpr (NDIM >= 2) {
-      const double t1 = muf * (face([&](int o) { return Dv(1, o); }) +
-                               diff([&](int o) { return P(2, o); }));
-      en += face([&](int o) { return P(2, o); }) * t1;
-      G[2] -= t1;
+      t1 = muf * (tangential(1) + diff(v[2]));
+      en += face(v[2]) * t1;
     }
     if constexpr (NDIM >= 3) {
-      const double t2 = muf * (face([&](int o) { return Dv(2, o); }) +
-                               diff([&](int o) { return P(3, o); }));
-      en += face([&](int o) { return P(3, o); }) * t2;
-      G[3] -= t2;
+      t2 = muf * (tangential(2) + diff(v[3]));
+      en += face(v[3]) * t2;
     }
-    G[4] -= en;
   }
-  if (!(fabs(G[0]) + fabs(G[4]) < 1.0e300)) atomicOr(g.flags, 1u);  // non-finite flux
+  G[1] -= tn;
+  G[2] -= t1;
+  G[3] -= t2;
+  G[4] -= en;
+  return fabs(G[0]) + fabs(G[4]) < 1.0e300;
 }
 
 // What the update of one cell reads, loaded before the face fluxes so that the
