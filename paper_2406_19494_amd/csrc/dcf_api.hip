@@ -530,6 +530,17 @@ static dcf_status rk3_stages(dcf_ctx *c, double *U, const double *dt, hipStream_
                              bool write_next = false, const PendingDt *pend = nullptr,
                              int nstages = 3, const BoxOut *boxes = nullptr) {
   Dev &g = c->g;
+  if (line_resident(g) && !dtpart) {
+    LineArgs A = {};
+    A.U = U;
+    A.dt = dt;
+    A.U1 = U1;
+    A.U2 = U2;
+    A.nsteps = 1;
+    A.nstages = nstages;
+    DCF_HIP(launch_line(g, A, st));
+    return DCF_OK;
+  }
   if (!U1) U1 = c->U1;
   if (!U2) U2 = c->U2;
   if (stage_fused(g)) {
@@ -608,6 +619,25 @@ static dcf_status rk3_stages(dcf_ctx *c, double *U, const double *dt, hipStream_
   if (nstages < 3) return DCF_OK;
   if ((s = eval_fluxes(c, U2, st))) return s;
   DCF_HIP(launch_update(g, U, U2, U, nullptr, dt, 1.0 / 3.0, 2.0 / 3.0, c->force, st, dtpart));
+  return DCF_OK;
+}
+
+// nsteps CFL steps of a short 1D line, at most 2048 to a launch.
+static dcf_status line_steps_cfl(dcf_ctx *c, double *U, const double *dt, int nsteps, double cfl,
+                                 double dt_max, double *dt_next, hipStream_t st) {
+  LineArgs A = {};
+  A.U = U;
+  A.dt = dt;
+  A.nstages = 3;
+  A.cfl = cfl;
+  A.dt_max = dt_max;
+  A.dt_next = dt_next;
+  while (nsteps > 0) {
+    A.nsteps = std::min(nsteps, 2048);
+    DCF_HIP(launch_line(c->g, A, st));
+    nsteps -= A.nsteps;
+    A.dt = dt_next;
+  }
   return DCF_OK;
 }
 
@@ -729,7 +759,7 @@ static dcf_status batch_fill(dcf_ctx *const *ctxs, double *const *U, double *con
     e.U2 = c->U2;
     e.dt = dt[i];
     e.part = c->part;
-    batch_entry_sizes(e);
+    batch_entry_sizes(e, n);
     memcpy(&h[i], &e, sizeof e);
   }
   return DCF_OK;
@@ -786,6 +816,7 @@ dcf_status dcf_rk3_step_cfl(dcf_ctx *c, double *U, const double *dt, double cfl,
   if (!(cfl > 0.0)) return fail(DCF_EINVAL, "cfl must be > 0");
   if (!(dt_max > 0.0)) dt_max = 1.0e300;
   hipStream_t st = (hipStream_t)stream;
+  if (line_resident(c->g)) return line_steps_cfl(c, U, dt, 1, cfl, dt_max, dt_next, st);
   if ((s = rk3_stages(c, U, dt, st, nullptr, nullptr, c->dtpart))) return s;
   const unsigned nparts = dt_parts(c);
   DCF_HIP(launch_dt_final(c->dtpart, (int)nparts, cfl, dt_max, dt_next, st));
@@ -801,6 +832,7 @@ dcf_status dcf_rk3_steps_cfl(dcf_ctx *c, double *U, double *dt, int nsteps, doub
   if (!(cfl > 0.0)) return fail(DCF_EINVAL, "cfl must be > 0");
   if (!(dt_max > 0.0)) dt_max = 1.0e300;
   hipStream_t st = (hipStream_t)stream;
+  if (line_resident(c->g)) return line_steps_cfl(c, U, dt, nsteps, cfl, dt_max, dt, st);
   const bool fused = stage_fused(c->g) || fused_stages(c);
   const unsigned nparts = dt_parts(c);
   const PendingDt pend{(int)nparts, cfl, dt_max, dt};

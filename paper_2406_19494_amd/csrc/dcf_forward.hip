@@ -1360,42 +1360,8 @@ __global__ void __launch_bounds__(256) kb_prim_interior(const BatchEntry *tab, i
   if (blockIdx.x >= e.nb_prim) return;
   prim_interior_body(e.g, stage_in(e, stage), blockIdx.x * blockDim.x + threadIdx.x);
 }
-__global__ void __launch_bounds__(256) kb_prim_ghost(const BatchEntry *tab) {
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.nb_ghost) return;
-  prim_ghost_body(e.g, blockIdx.x * blockDim.x + threadIdx.x);
-}
-
-template <int NDIM, bool VISC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(flux_waves(SCHEME_WENO5))))
-kb_flux_x(const BatchEntry *tab) {
-  extern __shared__ double lds[];
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.nb_x) return;
-  flux_x_body<NDIM, VISC>(e.g, e.nwmax, blockIdx.x, lds);
-}
-
-template <int NDIM, int D, bool VISC>
-__global__ void __launch_bounds__(256) kb_flux_yz(const BatchEntry *tab) {
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.yz_ntot[D]) return;
-  flux_yz_body<NDIM, D, VISC>(e.g, blockIdx.x, e.yz_ntot[D], e.yz_nbx[D], e.yz_nby[D]);
-}
-
-__global__ void __launch_bounds__(256) kb_update(const BatchEntry *tab, int stage) {
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.nb_upd) return;
-  // Shu-Osher stages: U1 = U + dt R(U); U2 = 3/4 U + 1/4 (U1 + dt R(U1));
-  // U = 1/3 U + 2/3 (U2 + dt R(U2))
-  const double a = stage == 0 ? 0.0 : (stage == 1 ? 0.75 : 1.0 / 3.0);
-  const double b = stage == 0 ? 1.0 : (stage == 1 ? 0.25 : 2.0 / 3.0);
-  double *out = stage == 0 ? e.U1 : (stage == 1 ? e.U2 : e.U);
-  update_body(e.g, e.U, stage_in(e, stage), out, nullptr, e.dt, a, b, nullptr,
-              blockIdx.x * blockDim.x + threadIdx.x);
-}
-
-// The fused-step forms (2D/3D): stage s works on the box of g (s even) or gb
-// (s odd); the update of stages 0 and 1 writes the next stage's interior.
+// Stage s works on the box of g (s even) or gb (s odd); the update of stages 0
+// and 1 writes the next stage's interior.
 __device__ __forceinline__ const Dev &stage_dev(const BatchEntry &e, int stage) {
   return (stage & 1) ? e.gb : e.g;
 }
@@ -1419,15 +1385,6 @@ kb_flux_xy(const BatchEntry *tab, int stage) {
                              e.yz_nbx[1], e.yz_nby[1]);
   else
     flux_x_body<3, VISC>(g, e.nwmax, blockIdx.x - ny_tiles, lds);
-}
-
-template <bool VISC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(flux_waves(SCHEME_WENO5))))
-kb_flux_x_s(const BatchEntry *tab, int stage) {
-  extern __shared__ double lds[];
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.nb_x) return;
-  flux_x_body<2, VISC>(stage_dev(e, stage), e.nwmax, blockIdx.x, lds);
 }
 
 template <int NDIM, bool VISC>
@@ -1459,96 +1416,73 @@ __global__ void __launch_bounds__(256) kb_dt_final(const BatchEntry *tab, double
   dt_final_body(e.part, (int)e.nb_dt, cfl, 1.0e300, e.dt);
 }
 
-void batch_entry_sizes(BatchEntry &e) {
+void batch_entry_sizes(BatchEntry &e, int n) {
   const Dev &g = e.g;
-  e.nb_prim = grid_for(g.ncell);
-  e.nb_ghost = g.nbox > g.ncell ? grid_for(g.nbox - g.ncell) : 0;
-  e.nb_x = grid_for(g.fcount[0]);
-  e.nb_upd = grid_for(g.ncell);
   e.nb_dt = grid_capped(g.ncell, RED_BLOCKS);
-  e.nwmax = x_window(g);
-  stage_entry_sizes(e);
-  for (int D = 0; D < 3; ++D) {
-    e.yz_nbx[D] = e.yz_nby[D] = e.yz_ntot[D] = 0;
-    if (D == 0 || D >= g.ndim) continue;
-    e.yz_nbx[D] = (g.n[0] + 15) / 16;
-    e.yz_nby[D] = (g.n[D] + 1 + 15) / 16;
-    e.yz_ntot[D] = e.yz_nbx[D] * e.yz_nby[D] * (D == 1 ? g.n[2] : g.n[1]);
-  }
+  stage_entry_sizes(e, n);
+  e.nb_prim = e.nb_ghost = e.nb_x = 0;
+  for (int D = 0; D < 3; ++D) e.yz_nbx[D] = e.yz_nby[D] = e.yz_ntot[D] = 0;
   e.fu_nbx = e.fu_nby = e.fu_ntot = 0;
-  if (g.ndim >= 2) {
-    const int D = g.ndim - 1;
-    e.fu_nbx = (g.n[0] + 15) / 16;
-    e.fu_nby = (g.n[D] + 14) / 15;
-    e.fu_ntot = e.fu_nbx * e.fu_nby * (D == 1 ? g.n[2] : g.n[1]);
-  }
+  e.nwmax = 0;
+  if (stage_fused(g)) return;  // the rest is of the split kernels
+  e.nb_prim = grid_for(g.ncell);
+  e.nb_ghost = grid_for(g.nbox - g.ncell);
+  e.nb_x = grid_for(g.fcount[0]);
+  e.nwmax = x_window(g);
+  e.yz_nbx[1] = (g.n[0] + 15) / 16;
+  e.yz_nby[1] = (g.n[1] + 1 + 15) / 16;
+  e.yz_ntot[1] = e.yz_nbx[1] * e.yz_nby[1] * g.n[2];
+  e.fu_nbx = (g.n[0] + 15) / 16;
+  e.fu_nby = (g.n[2] + 14) / 15;
+  e.fu_ntot = e.fu_nbx * e.fu_nby * g.n[1];
 }
 
-template <int NDIM, bool VISC>
-static hipError_t batch_step_t(const BatchEntry *tab, const BatchEntry *h, int n, double cfl,
-                               hipStream_t st) {
-  unsigned mp = 0, mh = 0, mx = 0, mu = 0, md = 0, my[3] = {0, 0, 0};
+// The 3D members whose stages do not run as one launch (their faces need more
+// of the halo chain): the split kernels' sequence.
+template <bool VISC>
+static hipError_t batch_split_stages(const BatchEntry *tab, const BatchEntry *h, int n,
+                                     hipStream_t st) {
+  unsigned mp = 0, mh = 0, mx = 0, my = 0, mf = 0;
   int nw = 0;
   for (int i = 0; i < n; ++i) {
     mp = std::max(mp, h[i].nb_prim);
     mh = std::max(mh, h[i].nb_ghost);
     mx = std::max(mx, h[i].nb_x);
-    mu = std::max(mu, h[i].nb_upd);
-    md = std::max(md, h[i].nb_dt);
+    my = std::max(my, h[i].yz_ntot[1]);
+    mf = std::max(mf, h[i].fu_ntot);
     nw = std::max(nw, h[i].nwmax);
-    for (int D = 1; D < 3; ++D) my[D] = std::max(my[D], h[i].yz_ntot[D]);
   }
+  if (!mf) return hipSuccess;
   const unsigned ny = (unsigned)n;
-  if (cfl > 0.0) {
-    kb_dt_partial<<<dim3(md, ny), 256, 0, st>>>(tab);
-    if (h[0].g.ndim != 2) kb_dt_final<<<ny, 256, 0, st>>>(tab, cfl);
-  }
-  if (h[0].g.ndim == 2) {
-    const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_batch_stages(tab, h, n, cfl, st);
-  }
-  const size_t shm = sizeof(double) * Slots<NDIM, VISC>::NC * nw;
-  if (NDIM >= 2) {
-    // the single-solve step's launch sequence, one launch per kernel for all
-    unsigned mf = 0;
-    for (int i = 0; i < n; ++i) mf = std::max(mf, h[i].fu_ntot);
-    constexpr int ND = NDIM < 2 ? 2 : NDIM;
-    const size_t shm_xy = std::max(shm, sizeof(YzTile<ND, VISC>));
-    for (int stage = 0; stage < 3; ++stage) {
-      if (stage == 0) kb_prim_interior<<<dim3(mp, ny), 256, 0, st>>>(tab, 0);
-      if (mh) kb_prim_ghost_s<<<dim3(mh, ny), 256, 0, st>>>(tab, stage);
-      if (NDIM == 3)
-        kb_flux_xy<VISC><<<dim3(my[1] + mx, ny), 256, shm_xy, st>>>(tab, stage);
-      else
-        kb_flux_x_s<VISC><<<dim3(mx, ny), 256, shm, st>>>(tab, stage);
-      kb_flux_update<ND, VISC><<<dim3(mf, ny), 256, 0, st>>>(tab, stage);
-    }
-    return hipGetLastError();
-  }
+  const size_t shm = std::max(sizeof(double) * Slots<3, VISC>::NC * nw, sizeof(YzTile<3, VISC>));
   for (int stage = 0; stage < 3; ++stage) {
-    kb_prim_interior<<<dim3(mp, ny), 256, 0, st>>>(tab, stage);
-    if (mh) kb_prim_ghost<<<dim3(mh, ny), 256, 0, st>>>(tab);
-    kb_flux_x<NDIM, VISC><<<dim3(mx, ny), 256, shm, st>>>(tab);
-    if (NDIM >= 2) kb_flux_yz<NDIM < 2 ? 2 : NDIM, 1, VISC><<<dim3(my[1], ny), 256, 0, st>>>(tab);
-    if (NDIM >= 3) kb_flux_yz<3, 2, VISC><<<dim3(my[2], ny), 256, 0, st>>>(tab);
-    kb_update<<<dim3(mu, ny), 256, 0, st>>>(tab, stage);
+    if (stage == 0) kb_prim_interior<<<dim3(mp, ny), 256, 0, st>>>(tab, 0);
+    kb_prim_ghost_s<<<dim3(mh, ny), 256, 0, st>>>(tab, stage);
+    kb_flux_xy<VISC><<<dim3(my + mx, ny), 256, shm, st>>>(tab, stage);
+    kb_flux_update<3, VISC><<<dim3(mf, ny), 256, 0, st>>>(tab, stage);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_batch_step(const BatchEntry *tab_dev, const BatchEntry *tab_host, int n,
-                             double cfl, hipStream_t st) {
-  const int nd = tab_host[0].g.ndim;
-  const bool v = tab_host[0].g.visc != VISC_NONE;
-  switch (nd) {
-    case 1: return v ? batch_step_t<1, true>(tab_dev, tab_host, n, cfl, st)
-                     : batch_step_t<1, false>(tab_dev, tab_host, n, cfl, st);
-    case 2: return v ? batch_step_t<2, true>(tab_dev, tab_host, n, cfl, st)
-                     : batch_step_t<2, false>(tab_dev, tab_host, n, cfl, st);
-    case 3: return v ? batch_step_t<3, true>(tab_dev, tab_host, n, cfl, st)
-                     : batch_step_t<3, false>(tab_dev, tab_host, n, cfl, st);
+hipError_t launch_batch_step(const BatchEntry *tab, const BatchEntry *h, int n, double cfl,
+                             hipStream_t st) {
+  const int nd = h[0].g.ndim;
+  if (nd < 1 || nd > 3) return hipErrorInvalidValue;
+  if (cfl > 0.0) {
+    unsigned md = 0, split = 0;
+    for (int i = 0; i < n; ++i) {
+      md = std::max(md, h[i].nb_dt);
+      split = std::max(split, h[i].fu_ntot);
+    }
+    kb_dt_partial<<<dim3(md, (unsigned)n), 256, 0, st>>>(tab);
+    // (the one-launch stages reduce the partials themselves)
+    if (split) kb_dt_final<<<(unsigned)n, 256, 0, st>>>(tab, cfl);
   }
-  return hipErrorInvalidValue;
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = launch_batch_stages(tab, h, n, cfl, st);
+  if (e != hipSuccess || nd < 3) return e;
+  return h[0].g.visc != VISC_NONE ? batch_split_stages<true>(tab, h, n, st)
+                                  : batch_split_stages<false>(tab, h, n, st);
 }
 
 hipError_t launch_cost(const Dev &g, int face, double pref, const double *U, double w,

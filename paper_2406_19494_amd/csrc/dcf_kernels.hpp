@@ -36,8 +36,27 @@ hipError_t launch_stage(const Dev &g, const StageArgs &A, hipStream_t st);
 // the stage adds up.
 bool stage_force_from_state(const Dev &g);
 hipError_t launch_stage_force(const Dev &g, StageArgs &A, double *part, hipStream_t st);
+
+// Arguments of the steps of a short 1D line in one workgroup (line_steps).
+struct LineArgs {
+  double *U;            // advanced in place (not written when nstages = 2)
+  const double *dt;     // step size of the first step
+  double *U1, *U2;      // nullable: the stage states of the last step
+  int nsteps, nstages;
+  double cfl, dt_max;   // cfl > 0: dt_next[0] receives the CFL step of the last state
+  double *dt_next;
+  // non-null: the first step is the CFL step of these partial maxima instead,
+  // and goes to dt_first
+  const double *part;
+  int nparts;
+  double cfl_first;
+  double *dt_first;
+};
+bool line_resident(const Dev &g);
+hipError_t launch_line(const Dev &g, const LineArgs &A, hipStream_t st);
+
 struct BatchEntry;
-void stage_entry_sizes(BatchEntry &e);
+void stage_entry_sizes(BatchEntry &e, int n);
 // The three stages of every solve of a batch, one launch each (cfl > 0: the
 // first one also reduces each solve's CFL partials).
 hipError_t launch_batch_stages(const BatchEntry *tab_dev, const BatchEntry *tab_host, int n,
@@ -55,15 +74,17 @@ struct BatchEntry {
   double *U, *U1, *U2;  // state (advanced in place) and the two stage states
   double *dt;           // step size (device, one double)
   double *part;         // reduction partials of the CFL step
-  unsigned nb_prim, nb_ghost, nb_x, nb_upd, nb_dt;
-  unsigned yz_nbx[3], yz_nby[3], yz_ntot[3];  // tile grids of the y and z fluxes
+  unsigned nb_prim, nb_ghost, nb_x, nb_dt;
+  unsigned yz_nbx[3], yz_nby[3], yz_ntot[3];  // tile grid of the y fluxes
   unsigned fu_nbx, fu_nby, fu_ntot;           // tile grid of the fused last-direction kernel
   int nwmax;            // x-flux LDS window length
-  unsigned st_tiles, st_nbx;  // tiles of the one-launch stage, tiles along x
+  // one-launch stage: its workgroups (0: the split kernels instead), tiles along
+  // x, and in 3D the division of the planes
+  unsigned st_tiles, st_nbx, st_len, st_nch;
 };
 
-// Fills the per-kernel workgroup counts of an entry (host side).
-void batch_entry_sizes(BatchEntry &e);
+// Fills the per-kernel workgroup counts of an entry of a batch of n (host side).
+void batch_entry_sizes(BatchEntry &e, int n);
 // One TVD-RK3 step of every solve in the table (tab_dev: device copy of
 // tab_host), optionally preceded by the CFL step (cfl > 0).  All entries
 // share ndim and the viscous flag and carry no source term.

@@ -8,6 +8,194 @@
 namespace dcf {
 
 // ---------------------------------------------------------------------------
+// 1D.  A line of fewer than 1024 cells is stepped by one workgroup, one cell and
+// one face per thread, with the state in registers: all stages of all steps of
+// a call in one launch (a stage of 200 cells takes 1.5 us, a launch by itself
+// 3.5).  Longer lines take a launch per stage, in tiles of 255 cells.
+// ---------------------------------------------------------------------------
+template <bool VISC> struct Line1 {
+  static constexpr int NP = VISC ? 5 : 3;  // rho, u, p (, T, mu)
+};
+
+// Flux of the face before window cell w (prims [NP][pitch]) into fl [3][fpitch].
+template <bool VISC, int SCH>
+__device__ __forceinline__ void line_face(const Dev &g, const double *w, int pitch, double mf,
+                                          double *fl, int fpitch) {
+  auto P = [&](int m, int o) {
+    const int a = m < 2 ? m : (m == 4 ? 2 : m - 2);  // rho, u, p, T, mu
+    return w[a * pitch + o];
+  };
+  auto Dv = [&](int, int) { return 0.0; };
+  double G[5];
+  if (!frame_flux<1, VISC, SCH, false>(g, P, Dv, mf, G)) atomicOr(g.flags, 1u);
+  fl[0] = G[0];
+  fl[fpitch] = G[1];
+  fl[2 * fpitch] = G[4];
+}
+
+template <bool VISC>
+__device__ __forceinline__ void line_store(const double *q, double *w, int pitch) {
+  w[0] = q[QR];
+  w[pitch] = q[QU];
+  w[2 * pitch] = q[QP];
+  if (VISC) {
+    w[3 * pitch] = q[QT];
+    w[4 * pitch] = q[QMU];
+  }
+}
+
+// Ghost sources of a line whose interior is in the window.
+template <bool VISC> struct FromLine {
+  const double *w;  // of cell 0
+  int pitch;
+  __device__ __forceinline__ void load(const Dev &g, const int *s, const int *, double *q,
+                                       double &mu) const {
+    const double *v = w + s[0];
+    q[QR] = v[0];
+    q[QU] = v[pitch];
+    q[QV] = q[QW] = 0.0;
+    q[QP] = v[2 * pitch];
+    q[QT] = VISC ? v[3 * pitch] : q[QP] * rcp_nr(q[QR]) * g.iR;
+    mu = VISC ? v[4 * pitch] : -1.0;
+  }
+  __device__ __forceinline__ double pressure(const Dev &g, const int *s, const int *) const {
+    return w[2 * pitch + s[0]];
+  }
+};
+
+// nsteps steps of the line (n < NT) from U with step dt[0]; with cfl > 0 each
+// step's CFL step replaces it and the last one goes to dt_next.  U1, U2
+// (nullable): the stage states of the last step; nstages = 2 makes only those.
+template <bool VISC, int SCH, int NT>
+__device__ __forceinline__ void line_steps(const Dev &g, const LineArgs &A, double *lds) {
+  constexpr int NP = Line1<VISC>::NP, PITCH = NT + 6;
+  double *win = lds, *fl = lds + NP * PITCH;  // windows [NP][NT + 6], faces [3][NT]
+  __shared__ double sh[NT / 64];
+  const int t = threadIdx.x, n = g.n[0];
+  const bool cell = t < n;
+  const int pos[3] = {t, 0, 0};
+  const double id = cell ? g.idx[0][t] : 0.0, mf = VISC ? g.mf[0][min(t, n)] : 0.0;
+  double u[3] = {1.0, 0.0, 1.0}, un[3];
+  if (cell)
+#pragma unroll
+    for (int v = 0; v < 3; ++v) u[v] = A.U[v * n + t];
+  double dt = A.part ? 0.0 : A.dt[0];
+  if (A.part) {  // the CFL step of these partial maxima
+    double m = 0.0;
+    for (int b = t; b < A.nparts; b += NT) m = fmax(m, A.part[b]);
+    dt = A.cfl_first / block_max<NT>(m, sh);
+    if (t == 0) A.dt_first[0] = dt;
+  }
+#pragma unroll 1
+  for (int step = 0; step < A.nsteps; ++step) {
+#pragma unroll
+    for (int v = 0; v < 3; ++v) un[v] = u[v];
+    double sig = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < A.nstages; ++k) {
+      const double a = k == 0 ? 0.0 : (k == 1 ? 0.75 : 1.0 / 3.0);
+      const double b = k == 0 ? 1.0 : (k == 1 ? 0.25 : 2.0 / 3.0);
+      double st[5] = {u[0], u[1], 0.0, 0.0, u[2]}, q[NQ];
+      if (cell) {
+        prim_of_state_t<1>(g, st, q);
+        if (!(finite_pos(q[QR]) && finite_pos(q[QP]))) atomicOr(g.flags, 1u);
+        if (VISC) q[QMU] = viscosity(g, q[QT]);
+        line_store<VISC>(q, win + 3 + t, PITCH);
+      }
+      __syncthreads();
+      if (t < 6) {
+        const int p[3] = {t < 3 ? t - 3 : n + t - 3, 0, 0};
+        double mu;
+        ghost_value<1>(g, p, FromLine<VISC>{win + 3, PITCH}, q, mu);
+        if (VISC) q[QMU] = mu >= 0.0 ? mu : viscosity(g, q[QT]);
+        line_store<VISC>(q, win + 3 + p[0], PITCH);
+      }
+      __syncthreads();
+      if (t <= n) line_face<VISC, SCH>(g, win + 3 + t, PITCH, mf, fl + t, NT);
+      __syncthreads();
+      if (cell) {
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+          double R = 0.0;
+          R -= (fl[v * NT + t + 1] - fl[v * NT + t]) * id;
+          u[v] = a * un[v] + b * (u[v] + dt * R);
+        }
+        double *keep = k == 0 ? A.U1 : (k == 1 ? A.U2 : nullptr);
+        if (keep && step == A.nsteps - 1)
+#pragma unroll
+          for (int v = 0; v < 3; ++v) keep[v * n + t] = u[v];
+        if (A.cfl > 0.0 && k == 2) {
+          double sn[5] = {u[0], u[1], 0.0, 0.0, u[2]};
+          prim_of_state_t<1>(g, sn, q);
+          sig = cell_sigma(g, q, pos);
+        }
+      }
+    }
+    if (A.cfl > 0.0) dt = fmin(A.dt_max, A.cfl / block_max<NT>(sig, sh));
+  }
+  if (cell && A.nstages == 3)
+#pragma unroll
+    for (int v = 0; v < 3; ++v) A.U[v * n + t] = u[v];
+  if (A.cfl > 0.0 && t == 0) A.dt_next[0] = dt;
+}
+
+template <bool VISC, int SCH, int NT>
+__global__ void __launch_bounds__(NT) k_line(Dev g, LineArgs A) {
+  __shared__ double lds[Line1<VISC>::NP * (NT + 6) + 3 * NT];
+  line_steps<VISC, SCH, NT>(g, A, lds);
+}
+
+// One stage of a tile of 255 cells of a longer line.
+template <bool VISC, int SCH>
+__device__ __forceinline__ void stage1_tile(const Dev &g, const StageArgs &A, unsigned tile,
+                                            double *lds) {
+  constexpr int T = 255, NT = 256, NP = Line1<VISC>::NP, PITCH = T + 6;
+  double *win = lds, *fl = lds + NP * PITCH;
+  __shared__ double sh[NT / 64];
+  const int t = threadIdx.x, n = g.n[0], i0 = (int)tile * T;
+  const int pc[3] = {i0 + t, 0, 0};
+  const bool cell = t < T && pc[0] < n;
+  CellIn<1> in;
+  if (cell) load_cell<1>(g, A, pc, in);
+  const double dt = stage_dt<NT>(A, tile == 0, sh);
+  const double mf = VISC ? g.mf[0][min(i0 + t, n)] : 0.0;
+  for (int w = t; w < PITCH; w += NT) {
+    const int p[3] = {i0 + w - 3, 0, 0};
+    if (p[0] > n + 2) continue;
+    double q[NQ], mu;
+    if (!load_prims<1, VISC>(g, A.Uin, p, q)) {
+      ghost_value<1>(g, p, FromState{A.Uin}, q, mu);
+      if (VISC) q[QMU] = viscosity(g, q[QT]);
+    }
+    line_store<VISC>(q, win + w, PITCH);
+  }
+  __syncthreads();
+  if (i0 + t <= n) line_face<VISC, SCH>(g, win + t + 3, PITCH, mf, fl + t, NT);
+  __syncthreads();
+  double sig = 0.0;
+  if (cell) {
+    double R[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+      double r = 0.0;
+      r -= (fl[v * NT + t + 1] - fl[v * NT + t]) * in.id[0];
+      R[v == 2 ? 4 : v] = r;
+    }
+    sig = update_state<1>(g, A, pc, in, dt, R, A.dtpart != nullptr);
+  }
+  if (A.dtpart) {
+    const double m = block_max<NT>(sig, sh);
+    if (t == 0) A.dtpart[tile] = m;
+  }
+}
+
+template <bool VISC, int SCH>
+__global__ void __launch_bounds__(256) k_stage1(Dev g, StageArgs A) {
+  __shared__ double lds[Line1<VISC>::NP * 261 + 3 * 256];
+  stage1_tile<VISC, SCH>(g, A, blockIdx.x, lds);
+}
+
+// ---------------------------------------------------------------------------
 // 2D: tiles of TX x TY cells.
 // ---------------------------------------------------------------------------
 // SMALL: 12 x 8 cells and 4 wavefronts, else 16 x 16 cells and 8 wavefronts.
@@ -739,14 +927,33 @@ __device__ __forceinline__ void stage3_range(const Dev &g, const StageArgs &A, u
   }
 }
 
+// How a grid's plane-tiles are divided (stage3_split): ranges of len, or (len =
+// 0) every tile's planes in nch nearly equal chunks.
+struct Split3 {
+  unsigned nbx, len, nch, groups;
+};
+__device__ __forceinline__ void split_range(const Dev &g, const Split3 &s, unsigned wg,
+                                            unsigned long &r0, unsigned long &r1) {
+  const unsigned long nz = (unsigned long)g.n[2];
+  if (s.len) {
+    const unsigned long total = (unsigned long)s.nbx * ((g.n[1] + 15) / 16) * nz;
+    r0 = (unsigned long)wg * s.len;
+    r1 = min(r0 + s.len, total);
+  } else {
+    const unsigned long tile = wg / s.nch, c = wg % s.nch;
+    r0 = tile * nz + c * nz / s.nch;
+    r1 = tile * nz + (c + 1) * nz / s.nch;
+  }
+}
+
 template <int LAW, int SCH>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
-k_stage3(Dev g, StageArgs A, unsigned nbx, unsigned len) {
+k_stage3(Dev g, StageArgs A, Split3 s) {
   __shared__ double lds[Col3<LAW != VISC_NONE>::SIZE];
   const unsigned wg = xcd_remap(blockIdx.x, gridDim.x);
-  const unsigned long r0 = (unsigned long)wg * len;
-  const unsigned long total = (unsigned long)nbx * ((g.n[1] + 15) / 16) * g.n[2];
-  stage3_range<LAW, SCH>(g, A, wg, r0, min(r0 + len, total), nbx, lds);
+  unsigned long r0, r1;
+  split_range(g, s, wg, r0, r1);
+  stage3_range<LAW, SCH>(g, A, wg, r0, r1, s.nbx, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -896,40 +1103,41 @@ static bool stage3_takes(const Dev &g) {
   return true;
 }
 
-static unsigned stage3_nbx(const Dev &g) { return tiles_along(g.n[0], Col3<true>::TX); }
-static unsigned stage3_nby(const Dev &g) { return tiles_along(g.n[1], Col3<true>::TY); }
-
-// Planes per workgroup.  A run of planes costs its length and about 1.5 planes
-// for its start.  Either the planes of all tiles are divided over the 256 CUs
-// (a range then spans parts of up to one more tile than its length needs), or
-// each tile's nz planes into equal runs, in rounds of 256.
-static unsigned stage3_len(const Dev &g) {
+// A run of planes costs its length and about 1.8 planes for its start (12 us
+// against 6.5 per plane).  Either the planes of all tiles are divided over the
+// 256 CUs (a range then spans parts of one more tile than its length needs), or
+// each tile's nz planes into nch chunks, in rounds of 256 workgroups.  (64^3: 12
+// chunks per tile 50 us, ranges of 5 planes 54 us; 192 x 128 x 128: ranges of 52
+// planes 353 us, 7 chunks per tile 420 us.)
+// (slots: the workgroups in flight, a share of 256 for a member of a batch.)
+static Split3 stage3_split(const Dev &g, unsigned slots = 256) {
   const unsigned nz = g.n[2];
-  const unsigned long total = (unsigned long)stage3_nbx(g) * stage3_nby(g) * nz;
-  unsigned best = 1;
+  const unsigned tiles = tiles_along(g.n[0], Col3<true>::TX) * tiles_along(g.n[1], Col3<true>::TY);
+  const unsigned long total = (unsigned long)tiles * nz;
+  Split3 s = {tiles_along(g.n[0], Col3<true>::TX), 0u, 1u, 0u};
   double cost = 1e300;
-  auto consider = [&](unsigned len) {
-    const unsigned long n = (total + len - 1) / len;
-    const unsigned runs = nz % len == 0 ? 1 : (len % nz == 0 ? len / nz : (len - 1) / nz + 2);
-    const double t = (double)((n + 255) / 256) * (len + 1.5 * runs);
+  for (unsigned c = 1; c <= nz; ++c) {
+    const unsigned long n = (unsigned long)tiles * c;
+    const double t = (double)((n + slots - 1) / slots) * ((nz + c - 1) / c + 1.8);
     if (t < cost) {
       cost = t;
-      best = len;
+      s.nch = c;
     }
-  };
-  consider((unsigned)((total + 255) / 256));
-  for (unsigned len = 1; len <= nz; ++len)
-    if (nz % len == 0) consider(len);
-  return best;
-}
-static unsigned stage3_groups(const Dev &g) {
-  const unsigned len = stage3_len(g);
-  return (unsigned)(((unsigned long)stage3_nbx(g) * stage3_nby(g) * g.n[2] + len - 1) / len);
+  }
+  s.groups = tiles * s.nch;
+  const unsigned len = (unsigned)((total + slots - 1) / slots);
+  const unsigned runs = len % nz == 0 ? len / nz : (len - 1) / nz + 2;
+  if (len + 1.8 * runs < cost) {
+    s.len = len;
+    s.groups = (unsigned)((total + len - 1) / len);
+  }
+  return s;
 }
 
-bool stage_fused(const Dev &g) { return g.ndim == 2 || stage3_takes(g); }
+bool stage_fused(const Dev &g) { return g.ndim <= 2 || stage3_takes(g); }
 unsigned stage_tiles(const Dev &g) {
-  if (g.ndim == 3) return stage3_groups(g);
+  if (g.ndim == 1) return tiles_along(g.n[0], 255);
+  if (g.ndim == 3) return stage3_split(g).groups;
   return stage2_small(g) ? stage2_tiles_t<true>(g) : stage2_tiles_t<false>(g);
 }
 
@@ -972,18 +1180,57 @@ hipError_t launch_stage_force(const Dev &g, StageArgs &A, double *part, hipStrea
 
 hipError_t launch_stage(const Dev &g, const StageArgs &A, hipStream_t st) {
   if (!stage_fused(g)) return hipErrorInvalidValue;
+  if (g.ndim == 1) {
+    const unsigned n = tiles_along(g.n[0], 255);
+    const bool v = g.visc != VISC_NONE;
+    if (g.scheme == SCHEME_TENO6A) {
+      if (v) k_stage1<true, SCHEME_TENO6A><<<n, 256, 0, st>>>(g, A);
+      else k_stage1<false, SCHEME_TENO6A><<<n, 256, 0, st>>>(g, A);
+    } else {
+      if (v) k_stage1<true, SCHEME_WENO5><<<n, 256, 0, st>>>(g, A);
+      else k_stage1<false, SCHEME_WENO5><<<n, 256, 0, st>>>(g, A);
+    }
+    return hipGetLastError();
+  }
   if (g.ndim == 3) {
-    const unsigned nbx = stage3_nbx(g), len = stage3_len(g), n = stage3_groups(g);
+    const Split3 s = stage3_split(g);
     if (g.visc == VISC_POWER)
-      k_stage3<VISC_POWER, SCHEME_WENO5><<<n, 512, 0, st>>>(g, A, nbx, len);
+      k_stage3<VISC_POWER, SCHEME_WENO5><<<s.groups, 512, 0, st>>>(g, A, s);
     else if (g.visc == VISC_SUTHERLAND)
-      k_stage3<VISC_SUTHERLAND, SCHEME_WENO5><<<n, 512, 0, st>>>(g, A, nbx, len);
+      k_stage3<VISC_SUTHERLAND, SCHEME_WENO5><<<s.groups, 512, 0, st>>>(g, A, s);
     else
-      k_stage3<VISC_NONE, SCHEME_WENO5><<<n, 512, 0, st>>>(g, A, nbx, len);
+      k_stage3<VISC_NONE, SCHEME_WENO5><<<s.groups, 512, 0, st>>>(g, A, s);
     return hipGetLastError();
   }
   if (g.visc != VISC_NONE) launch_stage_v<true>(g, A, st);
   else launch_stage_v<false>(g, A, st);
+  return hipGetLastError();
+}
+
+// Lines that one workgroup steps: at 1023 cells a stage takes as long there as
+// a launch per stage would (the body force needs the whole line's fluxes first
+// and takes that path).
+bool line_resident(const Dev &g) {
+  return g.ndim == 1 && g.n[0] < 1024 && g.source == SRC_NONE;
+}
+
+template <bool VISC, int SCH>
+static void launch_line_t(const Dev &g, const LineArgs &A, hipStream_t st) {
+  if (g.n[0] < 256) k_line<VISC, SCH, 256><<<1, 256, 0, st>>>(g, A);
+  else if (g.n[0] < 512) k_line<VISC, SCH, 512><<<1, 512, 0, st>>>(g, A);
+  else k_line<VISC, SCH, 1024><<<1, 1024, 0, st>>>(g, A);
+}
+
+hipError_t launch_line(const Dev &g, const LineArgs &A, hipStream_t st) {
+  if (!line_resident(g)) return hipErrorInvalidValue;
+  const bool v = g.visc != VISC_NONE;
+  if (g.scheme == SCHEME_TENO6A) {
+    if (v) launch_line_t<true, SCHEME_TENO6A>(g, A, st);
+    else launch_line_t<false, SCHEME_TENO6A>(g, A, st);
+  } else {
+    if (v) launch_line_t<true, SCHEME_WENO5>(g, A, st);
+    else launch_line_t<false, SCHEME_WENO5>(g, A, st);
+  }
   return hipGetLastError();
 }
 
@@ -1022,22 +1269,100 @@ kb_stage2(const BatchEntry *tab, int stage, double cfl) {
   stage2_tile<VISC, SCHEME_WENO5, false>(e.g, A, blockIdx.x, e.st_nbx, lds);
 }
 
-void stage_entry_sizes(BatchEntry &e) {
-  e.st_tiles = e.st_nbx = 0;
-  if (e.g.ndim != 2) return;
-  e.st_tiles = stage2_tiles_t<false>(e.g);
-  e.st_nbx = stage2_nbx_t<false>(e.g);
+// 1D members: lines short enough are stepped whole by one workgroup each, the
+// others (st_tiles > 0) stage by stage.
+template <bool VISC>
+__global__ void __launch_bounds__(1024) kb_line(const BatchEntry *tab, double cfl) {
+  __shared__ double lds[Line1<VISC>::NP * 1030 + 3 * 1024];
+  const BatchEntry &e = tab[blockIdx.x];
+  if (e.st_tiles) return;
+  LineArgs A = {};
+  A.U = e.U;
+  A.dt = e.dt;
+  A.nsteps = 1;
+  A.nstages = 3;
+  if (cfl > 0.0) {
+    A.part = e.part;
+    A.nparts = (int)e.nb_dt;
+    A.cfl_first = cfl;
+    A.dt_first = e.dt;
+  }
+  line_steps<VISC, SCHEME_WENO5, 1024>(e.g, A, lds);
+}
+template <bool VISC>
+__global__ void __launch_bounds__(256) kb_stage1(const BatchEntry *tab, int stage, double cfl) {
+  __shared__ double lds[Line1<VISC>::NP * 261 + 3 * 256];
+  const BatchEntry &e = tab[blockIdx.y];
+  if (blockIdx.x >= e.st_tiles) return;
+  const StageArgs A = batch_args(e, stage, cfl);
+  stage1_tile<VISC, SCHEME_WENO5>(e.g, A, blockIdx.x, lds);
+}
+
+// 3D members whose stages run as one launch; each viscosity law has its kernel,
+// a workgroup of another member's law returns.
+template <int LAW>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+kb_stage3(const BatchEntry *tab, int stage, double cfl) {
+  __shared__ double lds[Col3<LAW != VISC_NONE>::SIZE];
+  const BatchEntry &e = tab[blockIdx.y];
+  if (blockIdx.x >= e.st_tiles || e.g.visc != LAW) return;
+  const StageArgs A = batch_args(e, stage, cfl);
+  const Split3 s = {e.st_nbx, e.st_len, e.st_nch, e.st_tiles};
+  unsigned long r0, r1;
+  split_range(e.g, s, blockIdx.x, r0, r1);
+  stage3_range<LAW, SCHEME_WENO5>(e.g, A, blockIdx.x, r0, r1, s.nbx, lds);
+}
+
+void stage_entry_sizes(BatchEntry &e, int n) {
+  e.st_tiles = e.st_nbx = e.st_len = e.st_nch = 0;
+  if (!stage_fused(e.g)) return;
+  if (e.g.ndim == 1) {
+    e.st_tiles = line_resident(e.g) ? 0u : stage_tiles(e.g);
+  } else if (e.g.ndim == 3) {
+    const Split3 s = stage3_split(e.g, std::max(1u, 256u / (unsigned)n));
+    e.st_tiles = s.groups;
+    e.st_nbx = s.nbx;
+    e.st_len = s.len;
+    e.st_nch = s.nch;
+  } else {
+    e.st_tiles = stage2_tiles_t<false>(e.g);
+    e.st_nbx = stage2_nbx_t<false>(e.g);
+  }
 }
 
 hipError_t launch_batch_stages(const BatchEntry *tab, const BatchEntry *h, int n, double cfl,
                                hipStream_t st) {
   unsigned nt = 0;
-  for (int i = 0; i < n; ++i) nt = std::max(nt, h[i].st_tiles);
+  bool law[3] = {false, false, false};
+  for (int i = 0; i < n; ++i) {
+    nt = std::max(nt, h[i].st_tiles);
+    if (h[i].st_tiles) law[h[i].g.visc] = true;
+  }
   const dim3 grid(nt, (unsigned)n);
   const bool v = h[0].g.visc != VISC_NONE;
+  if (h[0].g.ndim == 1) {
+    bool lines = false;
+    for (int i = 0; i < n; ++i) lines = lines || !h[i].st_tiles;
+    if (lines) {
+      if (v) kb_line<true><<<(unsigned)n, 1024, 0, st>>>(tab, cfl);
+      else kb_line<false><<<(unsigned)n, 1024, 0, st>>>(tab, cfl);
+    }
+    for (int stage = 0; stage < 3 && nt; ++stage) {
+      if (v) kb_stage1<true><<<grid, 256, 0, st>>>(tab, stage, cfl);
+      else kb_stage1<false><<<grid, 256, 0, st>>>(tab, stage, cfl);
+    }
+    return hipGetLastError();
+  }
+  if (!nt) return hipSuccess;
   for (int stage = 0; stage < 3; ++stage) {
-    if (v) kb_stage2<true><<<grid, 512, 0, st>>>(tab, stage, cfl);
-    else kb_stage2<false><<<grid, 512, 0, st>>>(tab, stage, cfl);
+    if (h[0].g.ndim == 2) {
+      if (v) kb_stage2<true><<<grid, 512, 0, st>>>(tab, stage, cfl);
+      else kb_stage2<false><<<grid, 512, 0, st>>>(tab, stage, cfl);
+      continue;
+    }
+    if (law[VISC_NONE]) kb_stage3<VISC_NONE><<<grid, 512, 0, st>>>(tab, stage, cfl);
+    if (law[VISC_POWER]) kb_stage3<VISC_POWER><<<grid, 512, 0, st>>>(tab, stage, cfl);
+    if (law[VISC_SUTHERLAND]) kb_stage3<VISC_SUTHERLAND><<<grid, 512, 0, st>>>(tab, stage, cfl);
   }
   return hipGetLastError();
 }
