@@ -963,6 +963,15 @@ static dcf_status segment_step(dcf_ctx *c, int k, hipStream_t st) {
   double *Ua = c->seg + (long)k * M, *Ub = Ua + M;
   DCF_HIP(launch_copy(Ub, Ua, M, st));
   double *S1 = c->sst + (long)(2 * k) * M, *S2 = S1 + M;
+  if (stage_fused(g) && c->boxc && g.source == SRC_NONE && g.ndim != 2) {
+    // the 1D and 3D stage kernels keep no box: each stage's is filled from its
+    // input, as the reverse step would fill it
+    const dcf_status e = rk3_stages(c, Ub, gr.dt, st, S1, S2);
+    if (e) return e;
+    const double *in[3] = {Ua, S1, S2};
+    for (int s = 0; s < 3; ++s) DCF_HIP(launch_prim_halo(stage_box(c, k, s), in[s], st));
+    return DCF_OK;
+  }
   if (stage_fused(g) && c->boxc && g.source == SRC_NONE) {
     BoxOut boxes[3];
     for (int s = 0; s < 3; ++s) {

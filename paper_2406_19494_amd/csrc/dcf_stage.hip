@@ -1116,7 +1116,9 @@ static Split3 stage3_split(const Dev &g, unsigned slots = 256) {
   const unsigned long total = (unsigned long)tiles * nz;
   Split3 s = {tiles_along(g.n[0], Col3<true>::TX), 0u, 1u, 0u};
   double cost = 1e300;
-  for (unsigned c = 1; c <= nz; ++c) {
+  // (more rounds than a few only add starts)
+  const unsigned cmax = 8u * slots / tiles + 8u;
+  for (unsigned c = 1; c <= nz && c <= cmax; ++c) {
     const unsigned long n = (unsigned long)tiles * c;
     const double t = (double)((n + slots - 1) / slots) * ((nz + c - 1) / c + 1.8);
     if (t < cost) {
