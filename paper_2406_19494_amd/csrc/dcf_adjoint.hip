@@ -19,6 +19,7 @@
 // cell per phase), and the tile only writes the cells all of whose faces it
 // computed; no atomics anywhere, so results are bitwise reproducible.
 #include "dcf_adjoint.hpp"
+#include "dcf_cells.hpp"
 #include "dcf_kernels.hpp"
 
 namespace dcf {
@@ -34,61 +35,97 @@ template <int D> struct TileShape {
 __host__ inline int tile_faces(int D) { return D == 0 ? 64 : 32; }
 
 // ---------------------------------------------------------------------------
-// Reverse of WENO5-JS: g[0..4] += d y / d (a..e) * yb.
+// Reverse of WENO5-JS at one face (the arithmetic of weno5_pair): the adjoints
+// c[0..5] that the six cells v0..v5 receive from the adjoints ylb, yrb of the
+// two reconstructed values.  Both sides share the differences; a side without
+// adjoint (the downwind side of a supersonic face) is skipped.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void weno5_vjp(double a, double b, double c, double d, double e,
-                                          double yb, double *g) {
-  // the forward in the form the face flux evaluates it: t_k = (eps +
-  // beta_k) / sqrt(d_k), u_k = t_k^2, weights w_k = u_i u_j (i, j != k),
-  // candidates q_k at six times the third-order values, y = N / (6 W)
-  const double eps = 1.0e-6;
-  const double c1312 = 13.0 / 12.0;
-  constexpr double is1 = 3.162277660168379, is6 = 1.2909944487358056,
-                   is3 = 1.8257418583505538;  // 1 / sqrt(d_k), d = 0.1, 0.6, 0.3
-  double q0 = 2.0 * a - 7.0 * b + 11.0 * c;
-  double q1 = -b + 5.0 * c + 2.0 * d;
-  double q2 = 2.0 * c + 5.0 * d - e;
-  double r0 = a - 2.0 * b + c, s0 = a - 4.0 * b + 3.0 * c;
-  double r1 = b - 2.0 * c + d, s1 = b - d;
-  double r2 = c - 2.0 * d + e, s2 = 3.0 * c - 4.0 * d + e;
-  double t0 = fma(c1312 * is1 * r0, r0, fma(0.25 * is1 * s0, s0, eps * is1));
-  double t1 = fma(c1312 * is6 * r1, r1, fma(0.25 * is6 * s1, s1, eps * is6));
-  double t2 = fma(c1312 * is3 * r2, r2, fma(0.25 * is3 * s2, s2, eps * is3));
-  double u0 = t0 * t0, u1 = t1 * t1, u2 = t2 * t2;
-  double w0 = u1 * u2, w1 = u0 * u2, w2 = u0 * u1;
-  double iW = rcp_nr(6.0 * (w0 + w1 + w2));
-  double y6 = 6.0 * ((w0 * q0 + w1 * q1 + w2 * q2) * iW);
-  double Nb = yb * iW;
-  double q0b = Nb * w0, q1b = Nb * w1, q2b = Nb * w2;
-  double w0b = Nb * (q0 - y6), w1b = Nb * (q1 - y6), w2b = Nb * (q2 - y6);
-  double u0b = w1b * u2 + w2b * u1;
-  double u1b = w0b * u2 + w2b * u0;
-  double u2b = w0b * u1 + w1b * u0;
-  double t0b = 2.0 * t0 * u0b, t1b = 2.0 * t1 * u1b, t2b = 2.0 * t2 * u2b;
-  // d t_k / d r_k = 2 (13/12) r_k / sqrt(d_k), d t_k / d s_k = s_k / (2 sqrt(d_k))
-  double r0b = (2.0 * c1312 * is1) * r0 * t0b, s0b = (0.5 * is1) * s0 * t0b;
-  double r1b = (2.0 * c1312 * is6) * r1 * t1b, s1b = (0.5 * is6) * s1 * t1b;
-  double r2b = (2.0 * c1312 * is3) * r2 * t2b, s2b = (0.5 * is3) * s2 * t2b;
-  g[0] += 2.0 * q0b + r0b + s0b;
-  g[1] += -7.0 * q0b - q1b - 2.0 * r0b - 4.0 * s0b + r1b + s1b;
-  g[2] += 11.0 * q0b + 5.0 * q1b + 2.0 * q2b + r0b + 3.0 * s0b - 2.0 * r1b + r2b + 3.0 * s2b;
-  g[3] += 2.0 * q1b + 5.0 * q2b + r1b - s1b - 2.0 * r2b - 4.0 * s2b;
-  g[4] += -q2b + r2b + s2b;
+// One side: a, s the candidates' offsets (times six) and first-derivative terms
+// of its three stencils, d and r = d^2 their second differences; ab and sb
+// receive the adjoints of a and (a quarter) of s, db / (13/3 / sqrt(d_k)) those
+// of d.
+__device__ __forceinline__ void weno5_side_vjp(const double *a, const double *s, const double *d,
+                                               const double *r, double yb, double *ab, double *sb,
+                                               double *db) {
+  // t_k = (eps + beta_k) / sqrt(d_k), u_k = t_k^2, weights w_k = u_i u_j
+  // (i, j != k), offset of the value N / (6 W)
+  constexpr double eps = 1.0e-6, c1312 = 13.0 / 12.0;
+  // 1 / sqrt(d_k), d = 0.1, 0.6, 0.3
+  constexpr double sc[3] = {3.162277660168379, 1.2909944487358056, 1.8257418583505538};
+  double h[3], t[3], u[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    h[k] = (0.25 * sc[k]) * s[k];
+    t[k] = fma(c1312 * sc[k], r[k], fma(h[k], s[k], eps * sc[k]));
+    u[k] = t[k] * t[k];
+  }
+  const double w0 = u[1] * u[2], w1 = u[0] * u[2], w2 = u[0] * u[1];
+  const double iW = rcp_nr(w0 + w1 + w2);
+  const double o = (w0 * a[0] + w1 * a[1] + w2 * a[2]) * iW;  // six times the offset
+  const double nb = (yb * (1.0 / 6.0)) * iW;
+  ab[0] = nb * w0;
+  ab[1] = nb * w1;
+  ab[2] = nb * w2;
+  const double w0b = nb * (a[0] - o), w1b = nb * (a[1] - o), w2b = nb * (a[2] - o);
+  const double ub[3] = {w1b * u[2] + w2b * u[1], w0b * u[2] + w2b * u[0],
+                        w0b * u[1] + w1b * u[0]};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double tu = t[k] * ub[k];  // half of the adjoint of t_k
+    sb[k] = h[k] * tu;
+    db[k] = d[k] * tu;
+  }
 }
 
-// Reverse of the physical flux of one state (Eq. (3), face frame).
-__device__ __forceinline__ void phys_flux_vjp(const double *q, double gm1i, const double *Fb,
-                                              double *qb) {
-  double r = q[0], u = q[1], v = q[2], w = q[3], p = q[4];
-  double k2 = u * u + v * v + w * w;
-  double E = p * gm1i + 0.5 * r * k2;
-  double Eb = Fb[4] * u;
-  qb[0] += Fb[0] * u + Fb[1] * u * u + Fb[2] * u * v + Fb[3] * u * w + Eb * 0.5 * k2;
-  qb[1] += Fb[0] * r + 2.0 * Fb[1] * r * u + Fb[2] * r * v + Fb[3] * r * w + Fb[4] * (E + p) +
-           Eb * r * u;
-  qb[2] += Fb[2] * r * u + Eb * r * v;
-  qb[3] += Fb[3] * r * u + Eb * r * w;
-  qb[4] += Fb[1] + Fb[4] * u + Eb * gm1i;
+__device__ __forceinline__ void weno5_vjp(double v0, double v1, double v2, double v3, double v4,
+                                          double v5, double ylb, double yrb, double *c) {
+  const double e0 = v1 - v0, e1 = v2 - v1, e2 = v3 - v2, e3 = v4 - v3, e4 = v5 - v4;
+  const double d0 = e1 - e0, d1 = e2 - e1, d2 = e3 - e2, d3 = e4 - e3;
+  const double r0 = d0 * d0, r1 = d1 * d1, r2 = d2 * d2, r3 = d3 * d3;
+  // adjoint of the second differences of stencil k: k4[k] db[k]
+  constexpr double c13 = 13.0 / 3.0;
+  constexpr double k4[3] = {c13 * 3.162277660168379, c13 * 1.2909944487358056,
+                            c13 * 1.8257418583505538};
+  double e0b = 0.0, e1b = 0.0, e2b = 0.0, e3b = 0.0, e4b = 0.0;
+  double d0b = 0.0, d1b = 0.0, d2b = 0.0, d3b = 0.0;
+  double ab[3], sb[3], db[3];
+  if (ylb != 0.0) {
+    const double a[3] = {fma(5.0, e1, -2.0 * e0), fma(2.0, e2, e1), fma(4.0, e2, -e3)};
+    const double s[3] = {fma(3.0, e1, -e0), e1 + e2, fma(-3.0, e2, e3)};
+    const double d[3] = {d0, d1, d2}, r[3] = {r0, r1, r2};
+    weno5_side_vjp(a, s, d, r, ylb, ab, sb, db);
+    e0b = -2.0 * ab[0] - 4.0 * sb[0];
+    e1b = fma(5.0, ab[0], ab[1]) + fma(12.0, sb[0], 4.0 * sb[1]);
+    e2b = fma(4.0, ab[2], 2.0 * ab[1]) + fma(-12.0, sb[2], 4.0 * sb[1]);
+    e3b = fma(4.0, sb[2], -ab[2]);
+    d0b = k4[0] * db[0];
+    d1b = k4[1] * db[1];
+    d2b = k4[2] * db[2];
+  }
+  if (yrb != 0.0) {
+    const double a[3] = {fma(-5.0, e3, 2.0 * e4), fma(-2.0, e2, -e3), fma(-4.0, e2, e1)};
+    const double s[3] = {fma(-3.0, e3, e4), e2 + e3, fma(3.0, e2, -e1)};
+    const double d[3] = {d3, d2, d1}, r[3] = {r3, r2, r1};
+    weno5_side_vjp(a, s, d, r, yrb, ab, sb, db);
+    e4b = 2.0 * ab[0] + 4.0 * sb[0];
+    e3b += fma(-5.0, ab[0], -ab[1]) + fma(-12.0, sb[0], 4.0 * sb[1]);
+    e2b += fma(-4.0, ab[2], -2.0 * ab[1]) + fma(12.0, sb[2], 4.0 * sb[1]);
+    e1b += fma(-4.0, sb[2], ab[2]);
+    d3b = k4[0] * db[0];
+    d2b = fma(k4[1], db[1], d2b);
+    d1b = fma(k4[2], db[2], d1b);
+  }
+  e0b -= d0b;
+  e1b += d0b - d1b;
+  e2b += d1b - d2b;
+  e3b += d2b - d3b;
+  e4b += d3b;
+  c[0] = -e0b;
+  c[1] = e0b - e1b;
+  c[2] = e1b - e2b + ylb;
+  c[3] = e2b - e3b + yrb;
+  c[4] = e3b - e4b;
+  c[5] = e4b;
 }
 
 // Reverse of the HLLC flux (same branch choices as the forward: Davis wave
@@ -110,26 +147,22 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   double aR = uL + cL, bR = uR + cR;
   const bool selR = bR > aR;
   double SR = selR ? bR : aR;
-  for (int m = 0; m < 5; ++m) qLb[m] = qRb[m] = 0.0;
-  if (0.0 <= SL) {
-    phys_flux_vjp(qL, gm1i, Fb, qLb);
-    return;
-  }
-  if (SR < 0.0) {
-    phys_flux_vjp(qR, gm1i, Fb, qRb);
-    return;
-  }
   double mL = rL * (SL - uL), mR = rR * (SR - uR);
   double Nn = pR - pL + uL * mL - uR * mR, Dd = mL - mR;
   const double iDd = rcp_nr(Dd);
   double Ss = Nn * iDd;
   const bool left = (0.0 <= Ss);
   double r = left ? rL : rR, u = left ? uL : uR, v = left ? vL : vR, w = left ? wL : wR;
-  double p = left ? pL : pR, E = left ? EL : ER, S = left ? SL : SR, m = left ? mL : mR;
-  double inv = rcp_nr(S - Ss);
+  double p = left ? pL : pR, E = left ? EL : ER, SK = left ? SL : SR, m = left ? mL : mR;
+  double inv = rcp_nr(SK - Ss);
+  // a supersonic face (0 <= SL: left, or SR < 0: right) has the flux of its
+  // side alone: the wave term has weight S = 0 there, and the adjoint of the
+  // clamped speed is dropped (selections only, as in the forward)
+  const bool sub = left ? SL < 0.0 : 0.0 <= SR;
+  const double S = sub ? SK : 0.0;
   double Us0 = m * inv;
   double A4 = m * Ss + p;
-  double N4 = E * (S - u) + (Ss - u) * A4;
+  double N4 = E * (SK - u) + (Ss - u) * A4;
   double Us4 = N4 * inv;
   double fm = r * u;
   const double F0 = Fb[0], F1 = Fb[1], F2 = Fb[2], F3 = Fb[3], F4 = Fb[4];
@@ -146,7 +179,7 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   double pb = F1 + F4 * u;
   double Eb = F4 * (u - S);
   double N4b = Us4b * inv, invb = Us4b * N4;
-  Eb += N4b * (S - u);
+  Eb += N4b * (SK - u);
   Sb += N4b * E;
   ub -= N4b * (E + A4);
   Ssb += N4b * (A4 + (Ss - u) * m);
@@ -155,7 +188,7 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   mb += Us0b * inv;
   invb += Us0b * m;
   double db = -invb * inv * inv;
-  Sb += db;
+  Sb = sub ? Sb + db : 0.0;
   Ssb -= db;
   rb += fmb * u;
   ub += fmb * r;
@@ -164,12 +197,12 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   ub += Eb * r * u;
   vb += Eb * r * v;
   wb += Eb * r * w;
-  double *qKb = left ? qLb : qRb;
-  qKb[0] += rb;
-  qKb[1] += ub;
-  qKb[2] += vb;
-  qKb[3] += wb;
-  qKb[4] += pb;
+  const double kb[5] = {rb, ub, vb, wb, pb};
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    qLb[m] = left ? kb[m] : 0.0;
+    qRb[m] = left ? 0.0 : kb[m];
+  }
   double mLb = left ? mb : 0.0, mRb = left ? 0.0 : mb;
   double SLb = left ? Sb : 0.0, SRb = left ? 0.0 : Sb;
   double Nnb = Ssb * iDd, Ddb = -Ssb * Ss * iDd;
@@ -185,21 +218,11 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   qRb[0] += mRb * (SR - uR);
   SRb += mRb * rR;
   qRb[1] -= mRb * rR;
-  double cLb = 0.0, cRb = 0.0;
-  if (selL) {
-    qRb[1] += SLb;
-    cRb -= SLb;
-  } else {
-    qLb[1] += SLb;
-    cLb -= SLb;
-  }
-  if (selR) {
-    qRb[1] += SRb;
-    cRb += SRb;
-  } else {
-    qLb[1] += SRb;
-    cLb += SRb;
-  }
+  const double tLR = selL ? SLb : 0.0, tLL = selL ? 0.0 : SLb;  // S_L = u - c of a side
+  const double tRR = selR ? SRb : 0.0, tRL = selR ? 0.0 : SRb;  // S_R = u + c of a side
+  qLb[1] += tLL + tRL;
+  qRb[1] += tLR + tRR;
+  const double cLb = tRL - tLL, cRb = tRR - tLR;
   // c = sqrt(gamma p / rho): dc/dp = gamma / (2 rho c) = gamma y / 2 and
   // dc/drho = -c / (2 rho) = -c^2 y / 2
   qLb[4] += cLb * (0.5 * gamma) * yL;
@@ -210,8 +233,12 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
 
 // Flux adjoint at face f of direction D from the stage-output adjoint Wb:
 // with Rb = b dt Wb (the right-hand-side adjoint, 5-component flux layout),
-// Fb[m] = Rb_m(cell f)/dx_f - Rb_m(cell f-1)/dx_{f-1}.  (With the body
-// force A.Wb is the copy k_force_adj_apply corrected.)
+// Fb[m] = Rb_m(cell f)/dx_f - Rb_m(cell f-1)/dx_{f-1}.
+// With the mass-flux body force f = -sum_c V_c R_rhou(c) / W every cell's
+// x-momentum right-hand side also carries the force's dependence on the face
+// fluxes: its adjoint gets -f-bar V_c / W.  Between the two cells of a face
+// these terms cancel (V_c / dx is the face's area); the boundary faces keep
+// theirs, as in the forward's boundary-flux form.
 template <int NDIM>
 __device__ __forceinline__ void face_adjoint(const Dev &g, const AdjBuffers &A, int D,
                                              const int *pos, int f, double *Fb) {
@@ -242,6 +269,13 @@ __device__ __forceinline__ void face_adjoint(const Dev &g, const AdjBuffers &A, 
     Fb[m] = hr ? r : Fb[m];
     const double l = Fb[m] - (s * wl[m]) * idl;
     Fb[m] = hl ? l : Fb[m];
+  }
+  if (g.source == SRC_MASSFLUX && !(hr && hl)) {
+    double area = A.src[1] / g.vol;
+#pragma unroll
+    for (int e = 0; e < NDIM; ++e)
+      if (e != D) area *= g.dx[e][pos[e]];
+    Fb[1] += hr ? -area : area;
   }
 }
 
@@ -335,15 +369,16 @@ template <int NDIM, int D, bool VISC> struct DirLds {
   static constexpr int SIZE = ACC + BUF;  // doubles
 };
 
-// One tile of direction D.  SIDE: the tile writes its completed cells' Qb
-// contributions to the side arrays Qby (set, never added) instead of adding
-// them to Qb, so that it can run concurrently with the x tiles that set Qb;
-// k_tangential_vjp (ghost cells) and k_interior_vjp (interior cells) add the
-// two.
-template <int NDIM, int D, bool VISC, bool SIDE>
+// One tile of direction D.  ALL: the tiles of every direction run in one launch,
+// so a y or z tile writes its completed cells' Qb contributions to the side
+// arrays Qby or Qbz (set, never added) instead of adding them to the Qb that
+// the x tiles set; k_ghost_vjp (ghost cells) and k_interior_vjp (interior
+// cells) add them.
+template <int NDIM, int D, bool VISC, bool ALL>
 __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, unsigned P,
                                              unsigned nb, double *lds) {
   using L = DirLds<NDIM, D, VISC>;
+  constexpr bool SIDE = ALL && D > 0;
   constexpr int OLO = -3, OHI = 2, NOFF = L::NOFF, SPAN = OHI - OLO;
   constexpr int TF = L::TF, TW = L::TW;
   constexpr int NCW = L::NCW;  // window cells per line
@@ -409,16 +444,7 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
       const double *Qm = g.Q[qi[m]];
       double v0 = Qm[base - 3 * s], v1 = Qm[base - 2 * s], v2 = Qm[base - s];
       double v3 = Qm[base], v4 = Qm[base + s], v5 = Qm[base + 2 * s];
-      double gL[5] = {0, 0, 0, 0, 0}, gR[5] = {0, 0, 0, 0, 0};
-      // an upwind (supersonic) face leaves one side without adjoint
-      if (qLb[m] != 0.0) weno5_vjp(v0, v1, v2, v3, v4, qLb[m], gL);
-      if (qRb[m] != 0.0) weno5_vjp(v5, v4, v3, v2, v1, qRb[m], gR);
-      c[0] = gL[0];
-      c[1] = gL[1] + gR[4];
-      c[2] = gL[2] + gR[3];
-      c[3] = gL[3] + gR[2];
-      c[4] = gL[4] + gR[1];
-      c[5] = gR[0];
+      weno5_vjp(v0, v1, v2, v3, v4, v5, qLb[m], qRb[m], c);
     }
     if (D == 0) {
       // window cell w = L (and w = 64 + L for the last SPAN cells) takes
@@ -570,15 +596,16 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
     const long b = bidx(g, p[0], p[1], p[2]);
     const bool ghost = cell < 0 || cell >= g.n[D];
     if constexpr (SIDE) {
-      A.Qby[QR][b] = acc[0][ll][w];
+      double *const *Qs = D == 1 ? A.Qby : A.Qbz;
+      Qs[QR][b] = acc[0][ll][w];
 #pragma unroll
-      for (int c = 0; c < NDIM; ++c) A.Qby[QU + c][b] = acc[1 + c][ll][w];
-      A.Qby[QP][b] = acc[CP][ll][w];
+      for (int c = 0; c < NDIM; ++c) Qs[QU + c][b] = acc[1 + c][ll][w];
+      Qs[QP][b] = acc[CP][ll][w];
       if constexpr (VISC) {
-        A.Qby[QT][b] = acc[CT][ll][w];
-        A.Qby[QMU][b] = acc[CMU][ll][w];
+        Qs[QT][b] = acc[CT][ll][w];
+        Qs[QMU][b] = acc[CMU][ll][w];
       } else {
-        A.Qby[QT][b] = 0.0;
+        Qs[QT][b] = 0.0;
       }
     } else if (D == 0 || ghost) {
       // first writer of this cell in the stage: set every component the
@@ -608,14 +635,16 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
       // diagonal d u_t / d x_t is shared with the kernel of every earlier
       // direction other than t, which covered the cells interior along D
       constexpr bool sh1 = D >= 2 || (D == 1 && T1 != 0), sh2 = D >= 2 || (D == 1 && T2 != 0);
+      // (tiles of all directions in one launch: the later direction's share of
+      // a diagonal is set in Gs)
       if constexpr (T1 < NDIM) {
-        double &d1 = A.Gb[3 * T1 + T1][b];
-        d1 = (sh1 && !ghost ? d1 : 0.0) + acc[CG][ll][w];
+        double &d1 = (ALL && sh1 ? A.Gs[T1] : A.Gb[3 * T1 + T1])[b];
+        d1 = (!ALL && sh1 && !ghost ? d1 : 0.0) + acc[CG][ll][w];
         A.Gb[3 * T1 + D][b] = acc[CG + 1][ll][w];
       }
       if constexpr (T2 < NDIM) {
-        double &d2 = A.Gb[3 * T2 + T2][b];
-        d2 = (sh2 && !ghost ? d2 : 0.0) + acc[CG + 2][ll][w];
+        double &d2 = (ALL && sh2 ? A.Gs[T2] : A.Gb[3 * T2 + T2])[b];
+        d2 = (!ALL && sh2 && !ghost ? d2 : 0.0) + acc[CG + 2][ll][w];
         A.Gb[3 * T2 + D][b] = acc[CG + 3][ll][w];
       }
     }
@@ -624,44 +653,72 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
 
 // One direction per launch (1D, 3D).
 template <int NDIM, int D, bool VISC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NDIM == 2 ? 5 : 4)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_dir_vjp(Dev g, AdjBuffers A) {
   __shared__ double lds[DirLds<NDIM, D, VISC>::SIZE];
   dir_vjp_tile<NDIM, D, VISC, false>(g, A, blockIdx.x, gridDim.x, lds);
 }
 
-// 2D: the x and y tiles of a stage in one launch, so that the two directions'
-// tiles share the CUs (each alone leaves the FP64 units idle while its
-// workgroups wait on memory).  Workgroups are dealt in groups of 8, x and y
-// alternating while both have tiles left: group c of a direction holds its
-// tiles 8c .. 8c+7, so that a tile's index modulo 8 is its hardware index
-// modulo 8 (its XCD) as in a launch of its own.  The y tiles write their cell
-// contributions to Qby; the x tiles set Qb.
-template <bool VISC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
-k_dir_vjp_xy(Dev g, AdjBuffers A, unsigned nx, unsigned ny) {
-  constexpr int SX = DirLds<2, 0, VISC>::SIZE, SY = DirLds<2, 1, VISC>::SIZE;
-  __shared__ double lds[SX > SY ? SX : SY];
-  const unsigned grp = blockIdx.x / 8u, r = blockIdx.x % 8u;
-  const unsigned cx = (nx + 7u) / 8u, cy = (ny + 7u) / 8u, cm = cx < cy ? cx : cy;
-  unsigned dir, ci;
-  if (grp < 2u * cm) {
-    dir = grp % 2u;
-    ci = grp / 2u;
-  } else {
-    dir = cx > cy ? 0u : 1u;
-    ci = grp - cm;
+// The tiles of every direction of a stage in one launch, so that the
+// directions' tiles share the CUs (each alone leaves the FP64 units idle while
+// its workgroups wait on memory).  Workgroups are dealt in groups of 8, the
+// directions in turn while they have tiles left: group c of a direction holds
+// its tiles 8c .. 8c+7, so that a tile's index modulo 8 is its hardware index
+// modulo 8 (its XCD) as in a launch of its own.  The y and z tiles write their
+// cell contributions to Qby and Qbz; the x tiles set Qb.
+struct DirGroups {
+  unsigned c[3];  // groups of 8 workgroups per direction (0: no such axis)
+};
+
+// Group number grp -> direction and group within it.
+__device__ __forceinline__ void dir_of_group(const DirGroups &G, int nd, unsigned grp, int &dir,
+                                             unsigned &ci) {
+  // rounds of nd groups while every direction has some, then of those left
+  unsigned lo = 0u;  // groups per direction dealt so far
+  for (;;) {
+    unsigned left = 0u, m = 0xffffffffu;
+    for (int d = 0; d < nd; ++d)
+      if (G.c[d] > lo) {
+        ++left;
+        m = G.c[d] < m ? G.c[d] : m;
+      }
+    const unsigned span = left * (m - lo);
+    if (grp < span || left <= 1u) {
+      const unsigned k = grp % left;
+      ci = lo + grp / left;
+      unsigned seen = 0u;
+      dir = 0;
+      for (int d = 0; d < nd; ++d)
+        if (G.c[d] > lo) {
+          if (seen == k) dir = d;
+          ++seen;
+        }
+      return;
+    }
+    grp -= span;
+    lo = m;
   }
-  const unsigned P = ci * 8u + r;
-  if (dir == 0u) dir_vjp_tile<2, 0, VISC, false>(g, A, P, 8u * cx, lds);
-  else dir_vjp_tile<2, 1, VISC, true>(g, A, P, 8u * cy, lds);
+}
+
+template <int NDIM, bool VISC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k_dir_vjp_all(Dev g, AdjBuffers A, DirGroups G) {
+  constexpr int SX = DirLds<NDIM, 0, VISC>::SIZE, SY = DirLds<NDIM, 1, VISC>::SIZE;
+  __shared__ double lds[SX > SY ? SX : SY];  // (z tiles as y tiles)
+  unsigned ci;
+  int dir;
+  dir_of_group(G, NDIM, blockIdx.x / 8u, dir, ci);
+  const unsigned P = ci * 8u + blockIdx.x % 8u;
+  if (dir == 0) dir_vjp_tile<NDIM, 0, VISC, true>(g, A, P, 8u * G.c[0], lds);
+  else if (NDIM == 2 || dir == 1) dir_vjp_tile<NDIM, 1, VISC, true>(g, A, P, 8u * G.c[1], lds);
+  else if constexpr (NDIM == 3)
+    dir_vjp_tile<NDIM, 2, VISC, true>(g, A, P, 8u * G.c[2], lds);
 }
 
 // ---------------------------------------------------------------------------
 // Gather of the tangential-derivative adjoints (transpose of the
 // cell-centred 4th-order difference along t), then mu'(T) folding: on the
-// ghost cells in a launch of their own (the halo transposes read them), on
-// the interior cells inside k_interior_vjp.
+// ghost cells in k_ghost_vjp, on the interior cells inside k_interior_vjp.
 // ---------------------------------------------------------------------------
 // d mu / dT from T and mu(T): omega mu / T (power law), mu (1.5/t - 1/(t+s))
 // / T_ref with t = T/T_ref, s = S/T_ref (Sutherland).
@@ -678,8 +735,9 @@ __device__ __forceinline__ double dviscosity(const Dev &g, double T, double mu) 
 // Gather of the tangential-derivative adjoints at box cell p: y = x + k along
 // t contributes coef(k) mc(y) Gb(y); the metric factors of the (at most
 // four) neighbours along each axis are shared by the NDIM velocity components.
-// INTERIOR: p is an interior cell (else a box cell of the ghost layers).
-template <int NDIM, bool INTERIOR>
+// INTERIOR: p is an interior cell (else a box cell of the ghost layers).  ALL3:
+// the diagonals' second shares are in Gs.
+template <int NDIM, bool INTERIOR, bool ALL3>
 __device__ __forceinline__ void tangential_gather(const Dev &g, const AdjBuffers &A, const int *p,
                                                   long b, double *add) {
   constexpr int ks[4] = {-1, 1, -2, 2};
@@ -704,6 +762,7 @@ __device__ __forceinline__ void tangential_gather(const Dev &g, const AdjBuffers
       const long bb = (INTERIOR || in[t][r]) ? b + ks[r] * st : b;
 #pragma unroll
       for (int phi = 0; phi < NDIM; ++phi) gv[t][r][phi] = A.Gb[3 * t + phi][bb];
+      if constexpr (ALL3) gv[t][r][t] += A.Gs[t][bb];
     }
   }
 #pragma unroll
@@ -728,90 +787,6 @@ template <int NDIM> struct HaloQ {
   static constexpr int qs[6] = {QR, QU, NDIM >= 2 ? QV : QP,
                                 NDIM == 3 ? QW : (NDIM == 2 ? QP : QT), NDIM == 3 ? QP : QT, QT};
 };
-
-// Ghost cell number t (0 <= t < nbox - ncell) -> its box position: the z
-// ghost planes, then the y ghost rows of the interior planes, then the x
-// ghost cells of the interior rows (x fastest within each part).
-__device__ __forceinline__ void ghost_cell(const Dev &g, long t, int *p) {
-  const long N0 = g.N[0], N1 = g.N[1];
-  const int h0 = g.h[0], h1 = g.h[1], h2 = g.h[2];
-  const int n0 = g.n[0], n1 = g.n[1], n2 = g.n[2];
-  const long cz = 2L * h2 * N0 * N1;
-  if (t < cz) {
-    const long pl = t / (N0 * N1), rem = t % (N0 * N1);
-    p[2] = pl < h2 ? (int)pl - h2 : n2 + (int)pl - h2;
-    p[1] = (int)(rem / N0) - h1;
-    p[0] = (int)(rem % N0) - h0;
-    return;
-  }
-  t -= cz;
-  const long cy = 2L * h1 * N0 * n2;
-  if (t < cy) {
-    const long row = t / N0;
-    const int rr = (int)(row % (2 * h1));
-    p[2] = (int)(row / (2 * h1));
-    p[1] = rr < h1 ? rr - h1 : n1 + rr - h1;
-    p[0] = (int)(t % N0) - h0;
-    return;
-  }
-  t -= cy;
-  const int c = (int)(t % (2 * h0));
-  const long line = t / (2 * h0);
-  p[2] = (int)(line / n1);
-  p[1] = (int)(line % n1);
-  p[0] = c < h0 ? c - h0 : n0 + c - h0;
-}
-
-// Ghost cells, before the halo transposes read them: the y tiles' side
-// arrays (2D; on the y ghosts interior along x, which no x tile writes, they
-// are the whole value), the tangential gather, and mu'(T) folded into T.
-// Interior cells take the same three steps in k_interior_vjp.
-template <int NDIM>
-__global__ void __launch_bounds__(64) k_tangential_vjp(Dev g, AdjBuffers A) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= g.nbox - g.ncell) return;
-  int p[3];
-  ghost_cell(g, t, p);
-  const long b = bidx(g, p[0], p[1], p[2]);
-  const bool visc = g.visc != VISC_NONE;
-  // every load first (Qb, Qby and Gb may overlap as far as the compiler
-  // knows, which would serialise loads behind stores), then the stores
-  // 2D: a y ghost's adjoint is the y tiles' side array (x ghosts: x tiles only)
-  const bool side = NDIM == 2 && p[0] >= 0 && p[0] < g.n[0];
-  const bool gather = NDIM >= 2 && A.Gb[0] != nullptr;
-  // every active component is read (from the side array or from Qb; both
-  // exist for each of them), whichever of them the stores below use
-  double qb[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    if (q == QW && NDIM < 3) {
-      qb[q] = 0.0;
-      continue;
-    }
-    const double x = (side ? A.Qby[q] : A.Qb[q])[b];
-    qb[q] = side ? 0.0 + x : x;
-  }
-  double add[NDIM];
-  if (gather) tangential_gather<NDIM, false>(g, A, p, b, add);
-  const double Tq = g.Q[QT][b], muq = g.Q[QMU][b];  // (every box array exists)
-  const double dmu = visc ? dviscosity(g, Tq, muq) : 0.0;
-  if (side) {
-#pragma unroll
-    for (int i = 0; i < HaloQ<NDIM>::nq; ++i) {
-      const int q = HaloQ<NDIM>::qs[i];
-      A.Qb[q][b] = qb[q];
-    }
-    if (visc) A.Qb[QMU][b] = qb[QMU];
-  }
-  if (gather) {
-#pragma unroll
-    for (int phi = 0; phi < NDIM; ++phi) {
-      qb[QU + phi] += add[phi];
-      A.Qb[QU + phi][b] = qb[QU + phi];
-    }
-  }
-  if (visc) A.Qb[QT][b] = qb[QT] + dmu * qb[QMU];
-}
 
 // Source cell of ghost layer m (0 nearest the face) on side `side` of an axis
 // of n cells: the cell the forward halo fill copies (and mirrors) into it.
@@ -844,204 +819,226 @@ __device__ __forceinline__ void ghost_transform(const Dev &g, bool wall, bool is
   }
 }
 
-// ---------------------------------------------------------------------------
-// Transpose of the halo fill along axis d, folding ghost adjoints (complete
-// after k_tangential_vjp) into their sources, axes in the order z, y, x.
-// When the two sides' sources cannot coincide (n >= 6) a thread takes one
-// ghost layer of one side of a column (its ghost and its source are its own
-// cells); the zero-gradient copy (three layers, one source) and the porous /
-// disturbance terms (which sum the three layers' normal-velocity adjoints)
-// are taken by the layer-0 thread.  Short axes (n < 6) keep one thread per
-// column doing both sides and every layer in turn.
-// ---------------------------------------------------------------------------
-__host__ inline long halo_vjp_threads(const Dev &g, int d) {
-  const int t1 = tan1(d), t2 = tan2(d);
-  const long n1 = t1 < d ? g.N[t1] : g.n[t1];
-  const long n2 = t2 < d ? g.N[t2] : g.n[t2];
-  return (g.n[d] >= 6 ? 6 : 1) * n1 * n2;
+// Wall columns of a disturbance face of axis d: those inside along its first
+// tangential axis, and along the second all that the fill along d covers.
+__host__ inline long disturb_cols(const Dev &g, int d) {
+  const int t2 = tan2(d);
+  return (long)g.n[tan1(d)] * (t2 < d ? g.N[t2] : g.n[t2]);
 }
 
-template <int NDIM>
-__global__ void __launch_bounds__(64) k_halo_vjp(Dev g, AdjBuffers A, int d, double *dJdK) {
-  using H = HaloQ<NDIM>;
-  constexpr int nq = H::nq, iP = nq - 2;
-  const int t1 = tan1(d), t2 = tan2(d);
-  int lo1 = 0, n1 = g.n[t1], lo2 = 0, n2 = g.n[t2];
-  if (t1 < d) { lo1 = -g.h[t1]; n1 = g.N[t1]; }
-  if (t2 < d) { lo2 = -g.h[t2]; n2 = g.N[t2]; }
-  const long ncol = (long)n1 * n2;
-  const bool split = g.n[d] >= 6;
-  const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= (split ? 6 : 1) * ncol) return;
-  // thread -> (column, side, layer): columns fastest, then side, then layer
-  const long col = split ? tid % ncol : tid;
-  const int r = split ? (int)(tid / ncol) : 0;
-  const int side_lo = split ? r % 2 : 0, side_hi = split ? side_lo + 1 : 2;
-  const int mlo = split ? r / 2 : 0, mhi = split ? mlo + 1 : 3;
-  const int a = lo1 + (int)(col % n1), bq = lo2 + (int)(col / n1);
-  const int n = g.n[d];
-  // ghost cells of this column that are ghosts along another axis too (edges
-  // and corners of the box) are written only by the tangential-derivative
-  // adjoint and by the transposes of later axes: this kernel, their last
-  // reader, clears them for the next stage.  Every other cell the adjoint
-  // reads is set afresh each stage by the flux adjoints.
-  const bool edge = a < 0 || a >= g.n[t1] || bq < 0 || bq >= g.n[t2];
-  for (int side = side_lo; side < side_hi; ++side) {
-    const int face = 2 * d + side;
-    const int kind = g.bck[face];
-    const bool merged = kind == BC_ZEROGRAD;  // every layer copies one cell
-    const bool distinct = !merged && n >= 3;  // three distinct sources
-    // layers of this side that this thread folds
-    int m0 = mlo, m1 = mhi;
-    if (!distinct && kind != BC_DIRICHLET) {
-      if (m0 > 0) continue;  // the layer-0 thread folds the whole column
-      m1 = 3;
+// The ghost layers of side `side` along an axis of n cells that copy (and
+// mirror) cell i: layers m0 .. m0 + cnt - 1 (cnt 0: none).  The zero-gradient
+// copy fills all three layers from one cell; Dirichlet ghosts copy none.
+__device__ __forceinline__ void halo_images(int kind, int side, int i, int n, int &m0, int &cnt) {
+  const int lo = i, hi = n - 1 - i;
+  m0 = (kind == BC_PERIODIC) == (side == 0) ? hi : lo;
+  cnt = m0 < 3 ? 1 : 0;
+  if (kind == BC_ZEROGRAD) {
+    cnt = (side == 0 ? lo : hi) == 0 ? 3 : 0;
+    m0 = 0;
+  }
+  if (kind == BC_DIRICHLET) cnt = 0;
+}
+
+// Ghost cells along exactly one axis: their complete adjoint, before the
+// interior cells collect it.  The flux tiles' contribution (Qb, or the side
+// array of the axis' direction), the tangential gather, mu'(T) folded into T,
+// and the ghosts along a second axis (the edges of the box) that copy this
+// cell: the halo fill runs along x, then y, then z, so its transpose folds z
+// ghosts first, and an edge's adjoint is a tangential gather alone (velocity
+// components: no face flux reads an edge, and no derivative that is a ghost
+// along two axes has an adjoint, so corners have none).
+// Launch and memory latency bound: a thread per ghost, no second pass over
+// the edges (this kernel and the collection in k_interior_vjp replace a
+// transpose launch per axis, 6 to 7 us each).
+template <int NDIM, int D, bool ALL3>
+__device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int want_dk,
+                                          const int *p);
+
+template <int NDIM, bool ALL3>
+__global__ void __launch_bounds__(64)
+k_ghost_vjp(Dev g, AdjBuffers A, int want_dk) {
+  long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long n0 = g.n[0], n1 = g.n[1], n2 = g.n[2];
+  // ghost number c (side, layer) of an axis of n cells -> its position
+  auto at = [](int c, int n) { return c < 3 ? c - 3 : n + c - 3; };
+  if (t < 6 * n1 * n2) {  // x ghosts: a line's six together
+    const long line = t / 6;
+    const int p[3] = {at((int)(t % 6), g.n[0]), (int)(line % n1), (int)(line / n1)};
+    ghost_vjp<NDIM, 0, ALL3>(g, A, want_dk, p);
+    return;
+  }
+  // y, then z ghosts: x fastest
+  t -= 6 * n1 * n2;
+  if constexpr (NDIM >= 2) {
+    if (t < 6 * n0 * n2) {
+      const long row = t / n0;
+      const int p[3] = {(int)(t % n0), at((int)(row % 6), g.n[1]), (int)(row / 6)};
+      ghost_vjp<NDIM, 1, ALL3>(g, A, want_dk, p);
+      return;
     }
-    auto mine = [&](int m) { return m >= m0 && m < m1; };
-    int pG[3][3];
-    long G[3], S[3];
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      const int gd = side == 0 ? -1 - m : n + m, sd = halo_source(kind, side, m, n);
-      int ps[3];
-#pragma unroll
-      for (int e = 0; e < 3; ++e) {  // no dynamic register index
-        pG[m][e] = e == d ? gd : (e == t1 ? a : bq);
-        ps[e] = e == d ? sd : pG[m][e];
-      }
-      G[m] = bidx(g, pG[m][0], pG[m][1], pG[m][2]);
-      S[m] = bidx(g, ps[0], ps[1], ps[2]);
-    }
-    if (kind == BC_DIRICHLET) {  // ghost adjoints discarded
-      if (edge)
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-          if (mine(m))
-#pragma unroll
-            for (int i = 0; i < nq; ++i) A.Qb[H::qs[i]][G[m]] = 0.0;
-      continue;
-    }
-    const double sigma = side == 0 ? 1.0 : -1.0;
-    const bool wall = is_wall(kind);
-    const bool iso = wall && g.Tw[face] > 0.0;
-    // porous and disturbance columns are never edge columns, so the layer-0
-    // thread reads the other layers' ghosts while no thread clears them
-    const bool porous = kind == BC_POROUS && face == g.pface && a >= g.pb && a < g.pe &&
-                        bq >= 0 && bq < g.n[t2] && m0 == 0;
-    const bool disturb = kind == BC_DISTURB && dJdK && a >= 0 && a < g.n[t1] && m0 == 0;
-    const bool allgn = porous || disturb;  // needs every layer's normal-velocity adjoint
-    double gb[3][6] = {}, sv[3][6] = {}, rg[3] = {}, pg[3] = {}, gn[3] = {};
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      if (mine(m)) {
-#pragma unroll
-        for (int i = 0; i < nq; ++i) gb[m][i] = A.Qb[H::qs[i]][G[m]];
-        gn[m] = gb[m][1];  // gb[m][1 + d], without a dynamic register index
-#pragma unroll
-        for (int c = 1; c < NDIM; ++c)
-          if (c == d) gn[m] = gb[m][1 + c];
-      } else if (allgn) {
-        gn[m] = A.Qb[QU + d][G[m]];
-      }
-    }
-    if (merged) {
-#pragma unroll
-      for (int i = 0; i < nq; ++i) sv[0][i] = A.Qb[H::qs[i]][S[0]];
-    } else if (distinct) {
-#pragma unroll
-      for (int m = 0; m < 3; ++m)
-        if (mine(m))
-#pragma unroll
-          for (int i = 0; i < nq; ++i) sv[m][i] = A.Qb[H::qs[i]][S[m]];
-    }
-    if (iso) {
-#pragma unroll
-      for (int m = 0; m < 3; ++m)
-        if (mine(m)) {
-          rg[m] = g.Q[QR][G[m]];
-          pg[m] = g.Q[QP][G[m]];
-        }
-    }
-    int kk = 0;
-    double pw = 0.0, Kk = 0.0, kb0 = 0.0;
-    if (porous) {
-      kk = bq * (g.pe - g.pb) + (a - g.pb);
-      pw = g.Q[QP][S[0]];
-      Kk = g.K[kk];
-      if (dJdK) kb0 = dJdK[kk];
-    }
-    double xd = 0.0, th0 = 0.0, th1 = 0.0;
-    if (disturb) {
-      xd = g.xm[t1][a];
-      th0 = g.K[g.doff[face]];
-      th1 = g.K[g.doff[face] + 1];
-    }
-    double cs[3][6] = {};
-    double vsum = 0.0;  // sum over the column's ghosts of the normal-velocity adjoint
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      if (wall) vsum += gn[m];
-      if (mine(m)) ghost_transform<NDIM>(g, wall, iso, gb[m], rg[m], pg[m], cs[m]);
-    }
-    if (porous) {
-      // v_g[d] = 2 sigma v_n - v_s[d], v_n = -K (p_w - p_inf)/p_inf; the
-      // wall cell W is the source of ghost layer 0
-      double kb = 0.0;
-#pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        const double vnb = 2.0 * sigma * gn[m];
-        cs[0][iP] += -Kk / g.pinf * vnb;
-        kb += -(pw - g.pinf) / g.pinf * vnb;
-      }
-      if (dJdK) dJdK[kk] = kb0 + kb;
-    }
-    if (edge)
-#pragma unroll
-      for (int m = 0; m < 3; ++m)
-        if (mine(m))
-#pragma unroll
-          for (int i = 0; i < nq; ++i) A.Qb[H::qs[i]][G[m]] = 0.0;
-    // fold into the sources
-    if (merged) {
-#pragma unroll
-      for (int i = 0; i < nq; ++i)
-        A.Qb[H::qs[i]][S[0]] = sv[0][i] + ((cs[0][i] + cs[1][i]) + cs[2][i]);
-    } else if (distinct) {
-#pragma unroll
-      for (int m = 0; m < 3; ++m)
-        if (mine(m))
-#pragma unroll
-          for (int i = 0; i < nq; ++i) A.Qb[H::qs[i]][S[m]] = sv[m][i] + cs[m][i];
-    } else {  // n < 3: sources may repeat, accumulate layer by layer
-#pragma unroll
-      for (int m = 0; m < 3; ++m)
-#pragma unroll
-        for (int i = 0; i < nq; ++i) A.Qb[H::qs[i]][S[m]] += cs[m][i];
-    }
-    if (kind == BC_DISTURB && dJdK && m0 == 0) {
-      // v_g[d] = 2 sigma A sin(phi) - v_s[d], phi = 2 pi kappa x: per-column
-      // partials of dJ/dA and dJ/dkappa, summed over columns by k_disturb_sum
-      double dA = 0.0, dk = 0.0;
-      if (disturb) {
-        const double ph = 2.0 * M_PI * xd * th1;
-        const double w = 2.0 * sigma * vsum;
-        dA = w * sin(ph);
-        dk = w * th0 * cos(ph) * 2.0 * M_PI * xd;
-      }
-      A.dpart[(2 * side) * A.dcols + col] = dA;
-      A.dpart[(2 * side + 1) * A.dcols + col] = dk;
+    t -= 6 * n0 * n2;
+  }
+  if constexpr (NDIM == 3) {
+    if (t < 6 * n0 * n1) {
+      const long row = t / n0;
+      const int p[3] = {(int)(t % n0), (int)(row % n1), at((int)(row / n1), g.n[2])};
+      ghost_vjp<NDIM, 2, ALL3>(g, A, want_dk, p);
     }
   }
 }
 
-// dJ/d(A, kappa) += column sums of k_halo_vjp's partials for one disturbance
-// face (one block, fixed summation order: deterministic).
-__global__ void __launch_bounds__(256) k_disturb_sum(const double *part, long cols, double *out) {
+// The ghost at p, a ghost along axis D.
+template <int NDIM, int D, bool ALL3>
+__device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int want_dk,
+                                          const int *p) {
+  const long b = bidx(g, p[0], p[1], p[2]);
+  const bool visc = g.visc != VISC_NONE;
+  // every load first (Qb, Qby and Gb may overlap as far as the compiler
+  // knows, which would serialise loads behind stores), then the stores
+  const bool gather = NDIM >= 2 && A.Gb[0] != nullptr;
+  double qb[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    qb[q] = 0.0;
+    if ((q == QW && NDIM < 3) || (q == QMU && !visc)) continue;
+    if ((NDIM == 2 || ALL3) && D == 1) qb[q] = A.Qby[q][b];
+    else if (ALL3 && D == 2) qb[q] = A.Qbz[q][b];
+    else qb[q] = A.Qb[q][b];
+  }
+  const double Tq = g.Q[QT][b], muq = g.Q[QMU][b];  // (every box array exists)
+  if (visc) qb[QT] += dviscosity(g, Tq, muq) * qb[QMU];
+  if (gather) {
+    double add[NDIM];
+    tangential_gather<NDIM, false, ALL3>(g, A, p, b, add);
+#pragma unroll
+    for (int phi = 0; phi < NDIM; ++phi) qb[QU + phi] += add[phi];
+  }
+  // the edges folded into this ghost: layers of the axes e after D, as bits
+  // (2 (e - 1) + side) 3 + layer; each lane takes its next one per pass
+  if (gather && D + 1 < NDIM) {
+    unsigned mask = 0u, walls = 0u;
+#pragma unroll
+    for (int e = 1; e < NDIM; ++e) {
+      if (e <= D) continue;
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        int m0, cnt;
+        halo_images(g.bck[2 * e + side], side, p[e], g.n[e], m0, cnt);
+        mask |= (cnt == 3 ? 7u : (cnt ? 1u << m0 : 0u)) << (3 * (2 * (e - 1) + side));
+        if (is_wall(g.bck[2 * e + side])) walls |= 1u << (2 * (e - 1) + side);
+      }
+    }
+    while (mask) {
+      const int bit = __ffs(mask) - 1;
+      mask &= mask - 1u;
+      const int fs = bit / 3, m = bit - 3 * fs, side = fs & 1;
+      const bool ez = fs >= 2;
+      const int x = side == 0 ? -1 - m : (ez ? g.n[2] : g.n[1]) + m;
+      const int pe[3] = {p[0], ez ? p[1] : x, ez ? x : p[2]};
+      double add[NDIM];
+      tangential_gather<NDIM, false, ALL3>(g, A, pe, bidx(g, pe[0], pe[1], pe[2]), add);
+      const double sign = (walls >> fs) & 1u ? -1.0 : 1.0;
+#pragma unroll
+      for (int phi = 0; phi < NDIM; ++phi) qb[QU + phi] += sign * add[phi];
+    }
+  }
+  // the (A, kappa) of a z disturbance wall act on its edge columns too, those
+  // whose x lies inside: the layer-0 source's thread sums the column
+  if (NDIM == 3 && D == 1 && want_dk) {
+#pragma unroll 1
+    for (int side = 0; side < 2; ++side) {
+      const int kind = g.bck[4 + side];
+      if (kind != BC_DISTURB || p[2] != halo_source(kind, side, 0, g.n[2])) continue;
+      double vsum = 0.0;
+      if (gather)
+#pragma unroll 1
+        for (int m = 0; m < 3; ++m) {
+          const int pe[3] = {p[0], p[1], side == 0 ? -1 - m : g.n[2] + m};
+          double add[NDIM];
+          tangential_gather<NDIM, false, ALL3>(g, A, pe, bidx(g, pe[0], pe[1], pe[2]), add);
+          vsum += add[NDIM - 1];
+        }
+      A.dpart[side * A.dcols + (long)(p[1] + 3) * g.n[0] + p[0]] = vsum;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < HaloQ<NDIM>::nq; ++i) {
+    const int q = HaloQ<NDIM>::qs[i];
+    A.Qb[q][b] = qb[q];
+  }
+}
+
+// Contributions of the ghosts that copy interior cell p (box index b), added to
+// its adjoint qb (HaloQ order), and through the walls' parameters to dJ/dK.
+// Face by face, as most faces have none of a wavefront's cells (a pass per lane
+// over the faces it is near cost 24 against 15 us at 1024 x 256).
+template <int NDIM, int d>
+__device__ __forceinline__ void collect_ghosts(const Dev &g, const AdjBuffers &A, const int *p,
+                                               long b, double *dJdK, double *qb) {
+  using H = HaloQ<NDIM>;
+  constexpr int nq = H::nq, iP = nq - 2;
+  const int n = g.n[d], i = p[d];
+  const long sd = g.sb[d];
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    const int face = 2 * d + side;
+    const int kind = g.bck[face];
+    int m0, cnt;
+    halo_images(kind, side, i, n, m0, cnt);
+    if (cnt == 0) continue;
+    // box index of ghost layer 0 and the step to the next layer
+    const long G0 = b + ((side == 0 ? -1 : n) - i) * sd, gs = side == 0 ? -sd : sd;
+    if (cnt == 3) {  // copies, all of this cell
+#pragma unroll
+      for (int q = 0; q < nq; ++q) {
+        const double *Q = A.Qb[H::qs[q]] + G0;
+        qb[q] += (Q[0] + Q[gs]) + Q[2 * gs];
+      }
+      continue;
+    }
+    const bool wall = is_wall(kind), iso = wall && g.Tw[face] > 0.0;
+    const long G = G0 + m0 * gs;
+    double gb[6], cs[6];
+#pragma unroll
+    for (int q = 0; q < nq; ++q) gb[q] = A.Qb[H::qs[q]][G];
+    const double rg = g.Q[QR][G], pg = g.Q[QP][G];
+    ghost_transform<NDIM>(g, wall, iso, gb, rg, pg, cs);
+#pragma unroll
+    for (int q = 0; q < nq; ++q) qb[q] += cs[q];
+    if ((kind != BC_POROUS && kind != BC_DISTURB) || m0 != 0) continue;
+    // the wall cell of a porous or disturbance column (the source of ghost
+    // layer 0): the sum of the layers' normal-velocity adjoints
+    constexpr int t1 = tan1(d), t2 = tan2(d);
+    const int a = p[t1], bq = p[t2];
+    const double *Qn = A.Qb[QU + d] + G0;
+    const double vsum = Qn[0] + Qn[gs] + Qn[2 * gs];
+    if (kind == BC_DISTURB) {
+      if (dJdK) A.dpart[side * A.dcols + (long)(bq + (t2 < d ? 3 : 0)) * g.n[t1] + a] = vsum;
+    } else if (face == g.pface && a >= g.pb && a < g.pe) {
+      // v_g[d] = 2 sigma v_n - v_s[d], v_n = -K (p_w - p_inf)/p_inf
+      const int kk = bq * (g.pe - g.pb) + (a - g.pb);
+      const double vnb = (side == 0 ? 2.0 : -2.0) * vsum;
+      qb[iP] += -g.K[kk] / g.pinf * vnb;
+      if (dJdK) dJdK[kk] += -(g.Q[QP][b] - g.pinf) / g.pinf * vnb;
+    }
+  }
+}
+
+// dJ/d(A, kappa) of one disturbance face from the sums of its columns'
+// normal-velocity ghost adjoints (one block, fixed summation order:
+// deterministic): v_g[d] = 2 sigma A sin(phi) - v_s[d], phi = 2 pi kappa x.
+__global__ void __launch_bounds__(256) k_disturb_sum(Dev g, const double *part, long cols,
+                                                     int face, double *out) {
   __shared__ double sh[2][256];
   double v[2] = {0.0, 0.0};
+  const int t1 = tan1(face / 2);
+  const double th0 = g.K[g.doff[face]], th1 = g.K[g.doff[face] + 1];
   for (long i = threadIdx.x; i < cols; i += 256) {
-    v[0] += part[i];
-    v[1] += part[cols + i];
+    const double xd = g.xm[t1][i % g.n[t1]];
+    const double ph = 2.0 * M_PI * xd * th1, w = (face % 2 == 0 ? 2.0 : -2.0) * part[i];
+    v[0] += w * sin(ph);
+    v[1] += w * th0 * cos(ph) * 2.0 * M_PI * xd;
   }
   sh[0][threadIdx.x] = v[0];
   sh[1][threadIdx.x] = v[1];
@@ -1062,88 +1059,39 @@ __global__ void __launch_bounds__(256) k_disturb_sum(const double *part, long co
 // ---------------------------------------------------------------------------
 // Mass-flux body force of a stage, adjoint side: the source adds f to the
 // x-momentum and f u to the energy right-hand side of every cell, so with
-// Rb = b dt Wb, f-bar = sum_c (Rb_rhou(c) + Rb_E(c) u(c)); also the volume
-// W = sum_c V_c.  Two passes, fixed-shape trees (deterministic): src[1] =
-// f-bar, src[2] = W.
+// Rb = b dt Wb, f-bar = sum_c (Rb_rhou(c) + Rb_E(c) u(c)), into src[1].  Two
+// passes, fixed-shape trees (deterministic); the second also adds the forward's
+// force partials (f into src[0]).  (One launch whose last workgroup adds the
+// partial sums took 12.9 us, its fences most of it.)
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_force_adj_partial(Dev g, AdjBuffers A) {
-  __shared__ double sh[2][256];
+  __shared__ double sh[4];
   const double s = A.bcoef * A.dtp[0];
   const long nc = g.ncell;
   const int nd = g.ndim;
   const unsigned n0 = g.n[0], n01 = n0 * (unsigned)g.n[1];
-  double v[2] = {0.0, 0.0};
-  for (long c = (long)blockIdx.x * blockDim.x + threadIdx.x; c < nc;
-       c += (long)gridDim.x * blockDim.x) {
+  double v = 0.0;
+  for (long c = (long)blockIdx.x * 256 + threadIdx.x; c < nc; c += (long)gridDim.x * 256) {
     const unsigned cu = (unsigned)c;
     const int k = (int)(cu / n01), j = (int)((cu % n01) / n0), i = (int)(cu % n0);
     const double rb1 = s * A.Wb[nc + c], rbE = s * A.Wb[(long)(nd + 1) * nc + c];
-    v[0] += rb1 + rbE * g.Q[QU][bidx(g, i, j, k)];
-    double V = g.dx[0][i];
-    if (nd >= 2) V *= g.dx[1][j];
-    if (nd >= 3) V *= g.dx[2][k];
-    v[1] += V;
+    v += rb1 + rbE * g.Q[QU][bidx(g, i, j, k)];
   }
-  sh[0][threadIdx.x] = v[0];
-  sh[1][threadIdx.x] = v[1];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      sh[0][threadIdx.x] += sh[0][threadIdx.x + w];
-      sh[1][threadIdx.x] += sh[1][threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    A.spart[2 * blockIdx.x] = sh[0][0];
-    A.spart[2 * blockIdx.x + 1] = sh[1][0];
-  }
+  v = block_total<256>(v, sh);
+  if (threadIdx.x == 0) A.spart[blockIdx.x] = v;
 }
 
-// With the mass-flux body force f = -sum_c V_c R_rhou(c) / W every cell's
-// x-momentum right-hand side also carries the force's dependence on the
-// face fluxes: its adjoint gets -f-bar V_c / W (between the cells of a line
-// these terms cancel in the face adjoints, leaving the boundary faces, as in
-// the forward's boundary-flux form).  Written as a copy of the stage-output
-// adjoint whose x-momentum component is Wb_rhou - f-bar V_c / (W b dt); the
-// flux adjoints read the copy (the other kernels the stage's own Wb).
-__global__ void __launch_bounds__(256) k_force_adj_apply(Dev g, AdjBuffers A, double *Wc) {
-  const unsigned cu = blockIdx.x * blockDim.x + threadIdx.x;
-  if (cu >= (unsigned)g.ncell) return;
-  const long nc = g.ncell;
-  const int nd = g.ndim;
-  const unsigned n0 = g.n[0], n01 = n0 * (unsigned)g.n[1];
-  const int k = (int)(cu / n01), j = (int)((cu % n01) / n0), i = (int)(cu % n0);
-  double V = g.dx[0][i];
-  if (nd >= 2) V *= g.dx[1][j];
-  if (nd >= 3) V *= g.dx[2][k];
-  const double s = A.bcoef * A.dtp[0];
-  for (int v = 0; v < nd + 2; ++v) {
-    const double w = A.Wb[(long)v * nc + cu];
-    Wc[(long)v * nc + cu] = v == 1 ? w - (A.src[1] / A.src[2]) * V / s : w;
-  }
-}
-
-__global__ void __launch_bounds__(256) k_force_adj_final(AdjBuffers A, int nparts) {
-  __shared__ double sh[2][256];
-  double v[2] = {0.0, 0.0};
-  for (int b = threadIdx.x; b < nparts; b += 256) {
-    v[0] += A.spart[2 * b];
-    v[1] += A.spart[2 * b + 1];
-  }
-  sh[0][threadIdx.x] = v[0];
-  sh[1][threadIdx.x] = v[1];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      sh[0][threadIdx.x] += sh[0][threadIdx.x + w];
-      sh[1][threadIdx.x] += sh[1][threadIdx.x + w];
-    }
-    __syncthreads();
-  }
+__global__ void __launch_bounds__(256) k_force_adj_final(Dev g, AdjBuffers A, int nparts,
+                                                         const double *fpart, int nfpart) {
+  __shared__ double sh[4];
+  double fb = 0.0, f = 0.0;
+  for (int x = threadIdx.x; x < nparts; x += 256) fb += A.spart[x];
+  for (int x = threadIdx.x; x < nfpart; x += 256) f += fpart[x];
+  fb = block_total<256>(fb, sh);
+  f = block_total<256>(f, sh);
   if (threadIdx.x == 0) {
-    A.src[1] = sh[0][0];
-    A.src[2] = sh[1][0];
+    A.src[1] = fb;
+    if (fpart) A.src[0] = -f / g.vol;
   }
 }
 
@@ -1153,11 +1101,13 @@ __global__ void __launch_bounds__(256) k_force_adj_final(AdjBuffers A, int npart
 // later stages' combinations, a3 W3 + a2 W2 (their output adjoints, still
 // held), so no accumulator crosses the stages.
 // ---------------------------------------------------------------------------
-template <int NDIM>
-__global__ void __launch_bounds__(256) k_interior_vjp(Dev g, AdjBuffers A, const double *V,
+template <int NDIM, bool ALL3>
+__global__ void __launch_bounds__(256)
+k_interior_vjp(Dev g, AdjBuffers A, const double *V,
                                                       const double *Wb, double a, double b,
                                                       double *Vb, const double *w3, double a3,
-                                                      const double *w2, double a2, int fold) {
+                                                      const double *w2, double a2, int fold,
+                                                      double *dJdK) {
   constexpr int nd = NDIM;
   const unsigned cu = blockIdx.x * blockDim.x + threadIdx.x;  // ncell < 2^31
   if (cu >= (unsigned)g.ncell) return;
@@ -1179,30 +1129,52 @@ __global__ void __launch_bounds__(256) k_interior_vjp(Dev g, AdjBuffers A, const
     f3[v] = fold ? w3[x] : 0.0;
     f2[v] = fold ? w2[x] : 0.0;
   }
-  // the primitive adjoint of the cell: the flux adjoints' (x tiles plus, in
-  // 2D, the y tiles' side arrays) with the halo transposes' contributions,
-  // the tangential gather, and mu'(T) folded into T
+  // the primitive adjoint of the cell: the flux adjoints' (x tiles plus, with
+  // all directions in one launch, the side arrays), the tangential gather,
+  // mu'(T) folded into T, and the ghosts that copy the cell
   double rb = A.Qb[QR][bx], pb = A.Qb[QP][bx], Tb = A.Qb[QT][bx];
   double ub[3] = {A.Qb[QU][bx], nd >= 2 ? A.Qb[QV][bx] : 0.0, nd >= 3 ? A.Qb[QW][bx] : 0.0};
   const bool visc = g.visc != VISC_NONE;
   double mub = visc ? A.Qb[QMU][bx] : 0.0;
-  if constexpr (NDIM == 2) {
+  const int pc[3] = {i, j, k};
+  if constexpr (NDIM == 2 || ALL3) {
     rb += A.Qby[QR][bx];
-    ub[0] += A.Qby[QU][bx];
-    ub[1] += A.Qby[QV][bx];
+#pragma unroll
+    for (int q = 0; q < NDIM; ++q) ub[q] += A.Qby[QU + q][bx];
     pb += A.Qby[QP][bx];
     Tb += A.Qby[QT][bx];
     if (visc) mub += A.Qby[QMU][bx];
   }
+  if constexpr (ALL3) {
+    rb += A.Qbz[QR][bx];
+#pragma unroll
+    for (int q = 0; q < NDIM; ++q) ub[q] += A.Qbz[QU + q][bx];
+    pb += A.Qbz[QP][bx];
+    Tb += A.Qbz[QT][bx];
+    if (visc) mub += A.Qbz[QMU][bx];
+  }
   if (NDIM >= 2 && A.Gb[0] != nullptr) {
-    const int pc[3] = {i, j, k};
     double add[NDIM];
-    tangential_gather<NDIM, true>(g, A, pc, bx, add);
+    tangential_gather<NDIM, true, ALL3>(g, A, pc, bx, add);
 #pragma unroll
     for (int phi = 0; phi < NDIM; ++phi) ub[phi] += add[phi];
   }
   const double Tq = g.Q[QT][bx], muq = g.Q[QMU][bx];  // (every box array exists)
   if (visc) Tb += dviscosity(g, Tq, muq) * mub;
+  bool rim = false;  // within three cells of a face
+#pragma unroll
+  for (int d = 0; d < NDIM; ++d) rim |= min(pc[d], g.n[d] - 1 - pc[d]) < 3;
+  if (rim) {
+    double qb[6] = {};
+    if constexpr (NDIM == 3) collect_ghosts<NDIM, 2>(g, A, pc, bx, dJdK, qb);
+    if constexpr (NDIM >= 2) collect_ghosts<NDIM, 1>(g, A, pc, bx, dJdK, qb);
+    collect_ghosts<NDIM, 0>(g, A, pc, bx, dJdK, qb);
+    rb += qb[0];
+#pragma unroll
+    for (int q = 0; q < NDIM; ++q) ub[q] += qb[1 + q];
+    pb += qb[HaloQ<NDIM>::nq - 2];
+    Tb += qb[HaloQ<NDIM>::nq - 1];
+  }
   if (g.source == SRC_MASSFLUX)  // energy source f u: u-bar += Rb_E f
     ub[0] += (A.bcoef * A.dtp[0] * wv[nd + 1]) * A.src[0];
   double rho = Vc[0];
@@ -1257,18 +1229,15 @@ static inline unsigned blocks(long n) { return (unsigned)((n + 255) / 256 > 0 ? 
     if (e_ != hipSuccess) return e_;  \
   } while (0)
 
-// dJ/d(A, kappa) of the disturbance faces of axis d from the per-column
-// partials its halo transpose wrote.
+// dJ/d(A, kappa) of the disturbance faces of axis d from the columns' sums.
 static hipError_t disturb_sums(const Dev &g, const AdjBuffers &A, int d, double *dJdK,
                                hipStream_t st) {
   if (!dJdK) return hipSuccess;
-  const int t1 = tan1(d), t2 = tan2(d);
-  const long n1 = t1 < d ? g.N[t1] : g.n[t1];
-  const long n2 = t2 < d ? g.N[t2] : g.n[t2];
   for (int side = 0; side < 2; ++side) {
     const int face = 2 * d + side;
     if (g.bck[face] != BC_DISTURB) continue;
-    k_disturb_sum<<<1, 256, 0, st>>>(A.dpart + 2 * side * A.dcols, n1 * n2, dJdK + g.doff[face]);
+    k_disturb_sum<<<1, 256, 0, st>>>(g, A.dpart + side * A.dcols, disturb_cols(g, d), face,
+                                     dJdK + g.doff[face]);
     DCF_TRY(hipGetLastError());
   }
   return hipSuccess;
@@ -1290,21 +1259,30 @@ static hipError_t stage_vjp(const Dev &g, const AdjBuffers &A0, const double *V,
   A.bcoef = b;
   if (!have_box) DCF_TRY(launch_prim_halo(g, V, st));  // the stage's primitive box
   if (g.source == SRC_MASSFLUX) {
-    // the stage's body force f (as the forward stage computed it), f-bar,
-    // and the x-momentum adjoint corrected for the force's dependence
-    DCF_TRY(launch_force_direct(g, A.spart, A.src, st));
+    // the stage's body force f (as the forward stage computed it) and f-bar
+    StageArgs F = {};
+    F.Uin = V;
+    if (stage_force_from_state(g)) {
+      DCF_TRY(launch_stage_force(g, F, A.spart + RED_BLOCKS, st));
+    } else {
+      DCF_TRY(launch_force_direct(g, A.spart, A.src, st));
+    }
     const unsigned nb = (unsigned)std::min<long>((g.ncell + 255) / 256, RED_BLOCKS);
     k_force_adj_partial<<<nb, 256, 0, st>>>(g, A);
-    k_force_adj_final<<<1, 256, 0, st>>>(A, (int)nb);
-    k_force_adj_apply<<<blocks(g.ncell), 256, 0, st>>>(g, A, A.fwb);
+    k_force_adj_final<<<1, 256, 0, st>>>(g, A, (int)nb, F.fpart, F.nfpart);
     DCF_TRY(hipGetLastError());
-    A.Wb = A.fwb;  // for the flux adjoints; k_interior_vjp takes Wb itself
   }
-  if (g.ndim == 2) {
-    const unsigned nx = tile_count<-3, 2>(g, 0), ny = tile_count<-3, 2>(g, 1);
-    const unsigned nblk = 8u * ((nx + 7u) / 8u + (ny + 7u) / 8u);
-    auto k = visc ? k_dir_vjp_xy<true> : k_dir_vjp_xy<false>;
-    k<<<nblk, 256, 0, st>>>(g, A, nx, ny);
+  const bool all3 = adjoint_all3(g);
+  if (g.ndim == 2 || all3) {
+    DirGroups G = {};
+    unsigned nblk = 0u;
+    for (int D = 0; D < g.ndim; ++D) {
+      G.c[D] = (tile_count<-3, 2>(g, D) + 7u) / 8u;
+      nblk += 8u * G.c[D];
+    }
+    auto k = all3 ? (visc ? k_dir_vjp_all<3, true> : k_dir_vjp_all<3, false>)
+                  : (visc ? k_dir_vjp_all<2, true> : k_dir_vjp_all<2, false>);
+    k<<<nblk, 256, 0, st>>>(g, A, G);
     DCF_TRY(hipGetLastError());
   } else {
     for (int D = 0; D < g.ndim; ++D) {
@@ -1313,23 +1291,24 @@ static hipError_t stage_vjp(const Dev &g, const AdjBuffers &A0, const double *V,
       DCF_TRY(hipGetLastError());
     }
   }
-  if ((visc || g.ndim == 2) && g.nbox > g.ncell) {  // 2D: also the y tiles' side arrays
-    auto tk = g.ndim == 1 ? k_tangential_vjp<1>
-                          : (g.ndim == 2 ? k_tangential_vjp<2> : k_tangential_vjp<3>);
-    tk<<<(unsigned)((g.nbox - g.ncell + 63) / 64), 64, 0, st>>>(g, A);
+  const bool dist_z = g.ndim == 3 && (g.bck[4] == BC_DISTURB || g.bck[5] == BC_DISTURB);
+  if (visc || g.ndim == 2 || all3 || dist_z) {  // (else the tiles left the ghosts complete)
+    auto gk = g.ndim == 1 ? k_ghost_vjp<1, false>
+                          : (g.ndim == 2 ? k_ghost_vjp<2, false>
+                                         : (all3 ? k_ghost_vjp<3, true> : k_ghost_vjp<3, false>));
+    long ng = 0;
+    for (int d = 0; d < g.ndim; ++d) ng += 6L * (g.ncell / g.n[d]);
+    gk<<<(unsigned)((ng + 63) / 64), 64, 0, st>>>(g, A, dJdK ? 1 : 0);
     DCF_TRY(hipGetLastError());
   }
-  // the halo transposes, axes z, y, x
-  for (int d = g.ndim - 1; d >= 0; --d) {
-    auto hk = g.ndim == 1 ? k_halo_vjp<1> : (g.ndim == 2 ? k_halo_vjp<2> : k_halo_vjp<3>);
-    const long nt = halo_vjp_threads(g, d);
-    hk<<<(unsigned)((nt + 63) / 64), 64, 0, st>>>(g, A, d, dJdK);
-    DCF_TRY(hipGetLastError());
-    DCF_TRY(disturb_sums(g, A, d, dJdK, st));
-  }
-  auto ik = g.ndim == 1 ? k_interior_vjp<1> : (g.ndim == 2 ? k_interior_vjp<2> : k_interior_vjp<3>);
-  ik<<<blocks(g.ncell), 256, 0, st>>>(g, A, V, Wb, a, b, Vb, w3, a3, w2, a2, fold);
-  return hipGetLastError();
+  auto ik = g.ndim == 1 ? k_interior_vjp<1, false>
+                        : (g.ndim == 2 ? k_interior_vjp<2, false>
+                                       : (all3 ? k_interior_vjp<3, true>
+                                               : k_interior_vjp<3, false>));
+  ik<<<blocks(g.ncell), 256, 0, st>>>(g, A, V, Wb, a, b, Vb, w3, a3, w2, a2, fold, dJdK);
+  DCF_TRY(hipGetLastError());
+  for (int d = g.ndim - 1; d >= 0; --d) DCF_TRY(disturb_sums(g, A, d, dJdK, st));
+  return hipSuccess;
 }
 
 hipError_t vjp_step(Dev g, const AdjBuffers &A, const double *Un, const double *U1,

@@ -10,21 +10,29 @@ namespace dcf {
 struct AdjBuffers {
   double *Qb[NQ];   // adjoint of the primitive box (rho, u, v, w, p, T, mu)
   double *Gb[9];    // adjoint of cell-centred velocity derivatives d u_phi / d x_t (3 t + phi)
-  double *Qby[NQ];  // 2D: the y-direction tiles' Qb contributions (no w), added to Qb's
-                    // on ghost and interior cells; every cell read is written each stage
+  double *Qby[NQ];  // all directions' tiles in one launch: the y tiles' Qb contributions,
+                    // added to Qb's on interior cells, Qb itself on y ghosts; every cell
+                    // read is written each stage
+  double *Qbz[NQ];  // the z tiles' (3D)
+  double *Gs[3];    // second direction's share of the adjoint of d u_t / d x_t (3D, as Qbz)
   double *Ub1, *Ub2;  // stage adjoints
   const double *Wb;  // stage-output adjoint of the stage being reversed
-  double *fwb;       // (body force) Wb with the corrected x-momentum component
   const double *dtp; // step size (device)
   double bcoef;      // weight b of the stage's V + dt R(V) term
-  double *src;      // body-force adjoint of a stage: f, f-bar = sum Rb_rhou + Rb_E u, volume
-  double *spart;    // reduction partials of the body force and of its adjoint
-  double *dpart;    // per-column partial sums of dJ/d(A, kappa), 4 per wall column
-  long dcols;       // columns per disturbance-face partial array
+  double *src;      // body force of a stage: f, f-bar = sum Rb_rhou + Rb_E u
+  double *spart;    // partial sums of f-bar, then of f
+  double *dpart;    // normal-velocity ghost adjoints of the disturbance walls' columns, an
+                    // array per side
+  long dcols;       // columns per array
   double *zero_begin;  // Qb and Gb are carved back to back: one clear (with the
                        // workspace) zeroes both
   long zero_count;
 };
+
+// 3D grids whose flux adjoints run in one launch (side arrays for two
+// directions), else one launch per direction adding to Qb.  XXXRULE
+constexpr long ADJ_ALL3_CELLS = 1L << 19;
+inline bool adjoint_all3(const Dev &g) { return g.ndim == 3 && g.ncell <= ADJ_ALL3_CELLS; }
 
 // Lays the adjoint buffers out in the workspace (or measures them).
 template <class Carver> void carve_adjoint(Carver &cv, const Dev &g, AdjBuffers &a) {
@@ -34,10 +42,15 @@ template <class Carver> void carve_adjoint(Carver &cv, const Dev &g, AdjBuffers 
   for (int q = 0; q < 9; ++q)
     a.Gb[q] = (visc && q / 3 < g.ndim && q % 3 < g.ndim) ? cv.template take<double>(g.nboxp)
                                                            : nullptr;
+  const bool all3 = adjoint_all3(g);
+  for (int t = 0; t < 3; ++t)
+    a.Gs[t] = (visc && all3) ? cv.template take<double>(g.nboxp) : nullptr;
   a.zero_begin = a.Qb[0];
   a.zero_count = (long)((cv.off - off0) / sizeof(double));
-  for (int q = 0; q < NQ; ++q)
-    a.Qby[q] = (g.ndim == 2 && q != QW) ? cv.template take<double>(g.nboxp) : nullptr;
+  for (int q = 0; q < NQ; ++q) {
+    a.Qby[q] = ((g.ndim == 2 && q != QW) || all3) ? cv.template take<double>(g.nboxp) : nullptr;
+    a.Qbz[q] = all3 ? cv.template take<double>(g.nboxp) : nullptr;
+  }
   a.Ub1 = cv.template take<double>((long)g.nv * g.ncell);
   a.Ub2 = cv.template take<double>((long)g.nv * g.ncell);
   long cols = 1;
@@ -47,9 +60,8 @@ template <class Carver> void carve_adjoint(Carver &cv, const Dev &g, AdjBuffers 
     cols = n1 * n2 > cols ? n1 * n2 : cols;
   }
   a.dcols = cols;
-  a.dpart = cv.template take<double>(4 * cols);
+  a.dpart = cv.template take<double>(2 * cols);
   a.src = cv.template take<double>(4);
-  a.fwb = cv.template take<double>((long)g.nv * g.ncell);
   a.spart = cv.template take<double>(2 * RED_BLOCKS);
 }
 
