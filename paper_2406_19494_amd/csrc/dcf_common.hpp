@@ -331,29 +331,46 @@ __device__ __forceinline__ void hllc(const double *qL, const double *qR, double 
 // refined hardware ones (no IEEE division).
 __device__ __forceinline__ void teno6a_pair(double v0, double v1, double v2, double v3, double v4,
                                             double v5, double &yl, double &yr) {
+  constexpr double c1312 = 13.0 / 12.0;
+  // first differences over the faces, second differences over the cells
+  const double e0 = v1 - v0, e1 = v2 - v1, e2 = v3 - v2, e3 = v4 - v3, e4 = v5 - v4;
   double ct;
   {
     const double Cr = 0.17, xi = 1.0e-3;
     const double ee = 0.9 * Cr * xi * xi / (1.0 - 0.9 * Cr);
-    const double d0 = v1 - v0, d1 = v2 - v1, d2 = v3 - v2, d3 = v4 - v3, d4 = v5 - v4;
-    auto ren = [&](double dm, double dp) {
-      return (fabs(2.0 * dp * dm) + ee) * rcp_nr(fma(dp, dp, fma(dm, dm, ee)));
-    };
-    const double eta = fmin(fmin(ren(d0, d1), ren(d1, d2)), fmin(ren(d2, d3), ren(d3, d4)));
+    // the least of four ratios n_k / d_k, compared over common denominators:
+    // one reciprocal
+    const double f0 = e0 * e0, f1 = e1 * e1, f2 = e2 * e2, f3 = e3 * e3, f4 = e4 * e4;
+    const double n0 = fabs(2.0 * e1 * e0) + ee, n1 = fabs(2.0 * e2 * e1) + ee;
+    const double n2 = fabs(2.0 * e3 * e2) + ee, n3 = fabs(2.0 * e4 * e3) + ee;
+    const double g0 = f1 + (f0 + ee), g1 = f2 + (f1 + ee), g2 = f3 + (f2 + ee),
+                 g3 = f4 + (f3 + ee);
+    const double na = fmin(n0 * g1, n1 * g0), ga = g0 * g1;
+    const double nb = fmin(n2 * g3, n3 * g2), gb = g2 * g3;
+    const double eta = fmin(na * gb, nb * ga) * rcp_nr(ga * gb);
     const double m = 1.0 - fmin(1.0, eta * (1.0 / Cr));
     const double om = 1.0 - m, om2 = om * om;
     const double bbar = 10.5 - 3.5 * (1.0 - om2 * om2 * (1.0 + 4.0 * m));
-    const int k = (int)floor(bbar);
-    ct = k >= 10 ? 1.0e-10 : (k == 9 ? 1.0e-9 : (k == 8 ? 1.0e-8 : 1.0e-7));
+    ct = bbar >= 8.0 ? 1.0e-8 : 1.0e-7;
+    ct = bbar >= 9.0 ? 1.0e-9 : ct;
+    ct = bbar >= 10.0 ? 1.0e-10 : ct;
   }
-  auto side = [ct](double a, double b, double c, double d, double e, double f) {
-    constexpr double c1312 = 13.0 / 12.0;
-    const double s0 = b - 2.0 * c + d, t0 = b - d;
-    const double s1 = c - 2.0 * d + e, t1 = 3.0 * c - 4.0 * d + e;
-    const double s2 = a - 2.0 * b + c, t2 = a - 4.0 * b + 3.0 * c;
-    const double b0 = fma(c1312 * s0, s0, 0.25 * t0 * t0);
-    const double b1 = fma(c1312 * s1, s1, 0.25 * t1 * t1);
-    const double b2 = fma(c1312 * s2, s2, 0.25 * t2 * t2);
+  const double d0 = e1 - e0, d1 = e2 - e1, d2 = e3 - e2, d3 = e4 - e3;
+  const double r0 = c1312 * (d0 * d0), r1 = c1312 * (d1 * d1), r2 = c1312 * (d2 * d2),
+               r3 = c1312 * (d3 * d3);
+  // One side, cells a .. f along its own direction, differences ea = b - a ..
+  // ef = f - e, ra, rb, rc = 13/12 (second difference)^2 of (a b c), (b c d),
+  // (c d e): six times the offset's numerator over the sum of the kept weights.
+  // (b3 and b6 stay forms in the cell values: where the data are uniform to
+  // rounding their own rounding decides the cut-off, and there the selection is
+  // to stay as it is defined by these forms.)
+  auto side = [ct](double a, double b, double c, double d, double e, double f, double ea,
+                   double eb, double ec, double ed, double ef, double ra, double rb, double rc,
+                   double &N, double &W) {
+    const double t0 = eb + ec, t1 = fma(-3.0, ec, ed), t2 = fma(3.0, eb, -ea);
+    const double b0 = fma(0.25 * t0, t0, rb);
+    const double b1 = fma(0.25 * t1, t1, rc);
+    const double b2 = fma(0.25 * t2, t2, ra);
     const double b3 = (c * (2107.0 * c - 9402.0 * d + 7042.0 * e - 1854.0 * f) +
                        d * (11003.0 * d - 17246.0 * e + 4642.0 * f) +
                        e * (7043.0 * e - 3882.0 * f) + 547.0 * f * f) * (1.0 / 240.0);
@@ -366,24 +383,39 @@ __device__ __forceinline__ void teno6a_pair(double v0, double v1, double v2, dou
          d * (17195652.0 * d - 15880404.0 * e + 2863984.0 * f) +
          e * (3824847.0 * e - 1429976.0 * f) + 139633.0 * f * f) * (1.0 / 120960.0);
     const double tau = fabs(b6 - (b0 + b2 + 4.0 * b1) * (1.0 / 6.0));
-    auto gam = [tau](double beta) {
-      const double r = fma(tau, rcp_nr(beta + 1.0e-40), 1.0);
-      const double r2 = r * r;
-      return r2 * r2 * r2;
+    // (1 + tau / beta)^6: the four reciprocals from one
+    const double h0 = b0 + 1.0e-40, h1 = b1 + 1.0e-40, h2 = b2 + 1.0e-40, h3 = b3 + 1.0e-40;
+    const double h01 = h0 * h1, h23 = h2 * h3;
+    const double R = tau * rcp_nr(h01 * h23);
+    const double R01 = R * h23, R23 = R * h01;
+    auto gam = [](double x, double y) {
+      const double r = fma(x, y, 1.0), rr = r * r;
+      return rr * rr * rr;
     };
-    const double g0 = gam(b0), g1 = gam(b1), g2 = gam(b2), g3 = gam(b3);
+    const double g0 = gam(R01, h1), g1 = gam(R01, h0), g2 = gam(R23, h3), g3 = gam(R23, h2);
     const double lim = ct * (g0 + g1 + g2 + g3);
     const double w0 = g0 < lim ? 0.0 : 0.45, w1 = g1 < lim ? 0.0 : 0.3;
     const double w2 = g2 < lim ? 0.0 : 0.05, w3 = g3 < lim ? 0.0 : 0.2;
     // candidates: (b c d), (c d e), (a b c), (c d e f)
-    const double q0 = (-b + 5.0 * c + 2.0 * d) * (1.0 / 6.0);
-    const double q1 = (2.0 * c + 5.0 * d - e) * (1.0 / 6.0);
-    const double q2 = (2.0 * a - 7.0 * b + 11.0 * c) * (1.0 / 6.0);
-    const double q3 = (3.0 * c + 13.0 * d - 5.0 * e + f) * (1.0 / 12.0);
-    return (w0 * q0 + w1 * q1 + w2 * q2 + w3 * q3) * rcp_nr(w0 + w1 + w2 + w3);
+    const double q0 = fma(2.0, ec, eb), q1 = fma(4.0, ec, -ed), q2 = fma(5.0, eb, -2.0 * ea);
+    const double q3 = fma(4.5, ec, fma(0.5, ef, -2.0 * ed));
+    N = w0 * q0 + w1 * q1 + w2 * q2 + w3 * q3;
+    W = w0 + w1 + w2 + w3;
   };
-  yl = side(v0, v1, v2, v3, v4, v5);
-  yr = side(v5, v4, v3, v2, v1, v0);
+  double Nl, Wl, Nr, Wr;
+  // (the sides one after the other, and evaluated here: interleaved, or sunk to
+  // the flux with those of the other components, they take the registers of two
+  // wavefronts per SIMD instead of four)
+  asm volatile("" : "+v"(ct));
+  side(v0, v1, v2, v3, v4, v5, e0, e1, e2, e3, e4, r0, r1, r2, Nl, Wl);
+  asm volatile("" : "+v"(Nl), "+v"(Wl));
+  __builtin_amdgcn_sched_barrier(0);
+  side(v5, v4, v3, v2, v1, v0, -e4, -e3, -e2, -e1, -e0, r3, r2, r1, Nr, Wr);
+  const double r = rcp_nr(6.0 * Wl * Wr);
+  yl = fma(Nl * Wr, r, v2);
+  yr = fma(Nr * Wl, r, v3);
+  asm volatile("" : "+v"(yl), "+v"(yr));
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // 6th-order central interpolation and derivatives in index space: face value

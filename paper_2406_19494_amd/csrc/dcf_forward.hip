@@ -1138,7 +1138,7 @@ hipError_t launch_prim_halo(const Dev &g, const double *U, hipStream_t st) {
   // first, then the ghosts copied from it (then a second launch costs less than
   // ghost threads that convert their source state themselves; 65 x 49 x 33, 31 %
   // ghosts: 7.8 us in one launch, 11.3 in two)
-  if ((g.nbox - g.ncell) * 2 <= g.nbox) {
+  if ((g.nbox - g.ncell) * (g.nbox < 1L << 20 ? 2 : 10) <= g.nbox) {
     k_prim_halo<<<grid_for(g.nbox), 256, 0, st>>>(g, U);
   } else {
     k_prim_interior<<<grid_for(g.ncell), 256, 0, st>>>(g, U);
