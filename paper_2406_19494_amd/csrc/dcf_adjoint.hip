@@ -285,7 +285,7 @@ struct Tile {
   int c0, c1;   // cells written by the tile along D: [c0, c1)
   int line[3];  // tangential position of this thread's line (pos[D] unused)
   int lane_line, lane_face;
-  long lg;      // line group of the tile
+  unsigned lg;  // line group of the tile
   bool line_ok;
   bool valid;   // the workgroup has a tile
 };
@@ -302,17 +302,17 @@ __device__ __forceinline__ Tile make_tile(const Dev &g, unsigned P, unsigned nb)
   const int nt1 = g.n[T1], nt2 = g.n[T2];
   const int cmin = OLO;                         // first cell receiving contributions
   const int ncell_line = g.n[D] + 1 + SPAN;     // cells [OLO, n + OHI]
-  const int tiles_d = (ncell_line + CPT - 1) / CPT;
-  const long lines = (long)nt1 * nt2;
+  const unsigned tiles_d = (unsigned)(ncell_line + CPT - 1) / CPT;
+  const unsigned lines = (unsigned)nt1 * nt2;  // (ncell < 2^31)
   // y/z tiles: the two line groups that share each 128-byte row segment (and
   // the tiles along D of both, which share halo rows) run on one XCD, with
   // such chunks dealt round robin so that every XCD gets wall and free-stream
   // regions alike; x tiles keep the hardware order
-  long tile = D == 0 ? P : xcd_chunk_remap(P, nb, 2u * tiles_d);
-  int td = (int)(tile % tiles_d);
-  long lg = tile / tiles_d;  // line group
+  const unsigned tile = D == 0 ? P : xcd_chunk_remap(P, nb, 2u * tiles_d);
+  const unsigned lg = tile / tiles_d;  // line group
+  const int td = (int)(tile - lg * tiles_d);
   Tile t;
-  t.valid = tile < (long)tiles_d * ((lines + TW - 1) / TW);
+  t.valid = lg < (lines + TW - 1) / TW;
   const int tid = threadIdx.x;
   if (D == 0) {
     t.lane_face = tid % TF;
@@ -321,10 +321,10 @@ __device__ __forceinline__ Tile make_tile(const Dev &g, unsigned P, unsigned nb)
     t.lane_line = tid % TW;
     t.lane_face = tid / TW;
   }
-  long ln = lg * TW + t.lane_line;  // line index over (t1 fastest, t2)
+  const unsigned ln = lg * TW + t.lane_line;  // line index over (t1 fastest, t2)
   t.line_ok = ln < lines;
-  int a = t.line_ok ? (int)(ln % nt1) : 0;
-  int bq = t.line_ok ? (int)(ln / nt1) : 0;
+  const int bq = t.line_ok && nt2 > 1 ? (int)(ln / (unsigned)nt1) : 0;
+  const int a = t.line_ok ? (int)ln - bq * nt1 : 0;
   t.line[D] = 0;
   t.line[T1] = a;
   t.line[T2] = bq;
@@ -397,7 +397,8 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
   static_assert(NCH * TW * NCW == L::ACC, "accumulator layout");
   Tile t = make_tile<OLO, OHI, D>(g, P, nb);
   if (!t.valid) return;  // uniform across the workgroup
-  for (int i = threadIdx.x; i < NCH * TW * NCW; i += 256) (&acc[0][0][0])[i] = 0.0;
+  // (the convective channels 0 .. CP are set by the first pass)
+  for (int i = threadIdx.x; i < (NCH - CT) * TW * NCW; i += 256) (&acc[CT][0][0])[i] = 0.0;
   // x tiles: each wavefront holds the 64 faces of one line and its lanes
   // are the only writers of that line's window, one lane per cell in the
   // convective gather, so after this barrier that gather uses lane shuffles
@@ -412,6 +413,17 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
   double Fb[5] = {0, 0, 0, 0, 0};
   long base = 0;
   const long s = g.sb[D];
+  // the next component's stencil, read again ahead of its use (all of them held
+  // since the first pass would not fit the registers)
+  double nv[NOFF] = {0, 0, 0, 0, 0, 0};
+  // for the dissipative flux: face velocities and their differences (face frame)
+  // from the same reads, T and mu of the four inner cells
+  double uf[3] = {0, 0, 0}, dn[3] = {0, 0, 0}, Tc[4] = {0, 0, 0, 0}, muc[4] = {0, 0, 0, 0};
+  auto fetch = [&](int m) {
+    const double *Qm = g.Q[qi[m]] + base;
+#pragma unroll
+    for (int o = 0; o < NOFF; ++o) nv[o] = Qm[(o - 3) * s];
+  };
   if (active) {
     int pos[3] = {t.line[0], t.line[1], t.line[2]};
     pos[D] = f;
@@ -431,19 +443,34 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
       weno5_pair(v0, v1, v2, v3, v4, v5, qL[m], qR[m]);
     }
     double Fr[5] = {Fb[0], Fb[1 + D], Fb[1 + T1], Fb[1 + T2], Fb[4]};
+    fetch(0);
     hllc_vjp(qL, qR, g.gamma, g.gm1i, Fr, qLb, qRb);
   }
   // convective, per component: reverse the two reconstructions, stage the
   // contributions to cells f-3 .. f+2 in LDS, then gather them per window
   // cell in a fixed order of faces (deterministic, no atomics)
+#pragma unroll
   for (int m = 0; m < 5; ++m) {
     const bool act = !((m == 2 && T1 >= NDIM) || (m == 3 && T2 >= NDIM));
     if (!act) continue;  // uniform across the block
     double c[NOFF] = {0, 0, 0, 0, 0, 0};
+    const double v0 = nv[0], v1 = nv[1], v2 = nv[2], v3 = nv[3], v4 = nv[4], v5 = nv[5];
+    const int next = m + 1 + (m == 1 && T1 >= NDIM ? 1 : 0) +
+                     ((m == 1 && T1 >= NDIM) || m == 2 ? (T2 >= NDIM ? 1 : 0) : 0);
     if (active) {
-      const double *Qm = g.Q[qi[m]];
-      double v0 = Qm[base - 3 * s], v1 = Qm[base - 2 * s], v2 = Qm[base - s];
-      double v3 = Qm[base], v4 = Qm[base + s], v5 = Qm[base + 2 * s];
+      if (next < 5) {
+        fetch(next);
+      } else if constexpr (VISC) {
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          Tc[o] = g.Q[QT][base + (o - 2) * s];
+          muc[o] = g.Q[QMU][base + (o - 2) * s];
+        }
+      }
+      if (VISC && m >= 1 && m <= 3) {
+        uf[m - 1] = interp4(v1, v2, v3, v4);
+        dn[m - 1] = dface4(v1, v2, v3, v4);
+      }
       weno5_vjp(v0, v1, v2, v3, v4, v5, qLb[m], qRb[m], c);
     }
     if (D == 0) {
@@ -458,8 +485,8 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
         if (L >= o) s0 += v0;
         if (o > L) s1 += v1;
       }
-      acc[ch[m]][t.lane_line][L] += s0;
-      if (L < SPAN) acc[ch[m]][t.lane_line][TF + L] += s1;
+      acc[ch[m]][t.lane_line][L] = s0;
+      if (L < SPAN) acc[ch[m]][t.lane_line][TF + L] = s1;
       continue;
     }
 #pragma unroll
@@ -473,7 +500,7 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
         const int fl = w - o;  // face (lane) whose offset o lands on window cell w
         if (fl >= 0 && fl < TF) sum += buf[o][ll][fl];
       }
-      acc[ch[m]][ll][w] += sum;
+      acc[ch[m]][ll][w] = sum;
     }
     __syncthreads();
   }
@@ -483,24 +510,10 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
     double divtb = 0.0, dtnb[3] = {0, 0, 0};
     double mfD = 0.0;
     if (active) {
-      double vel[3][4], Tc[4], muc[4];
-#pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        long cb = base + (o - 2) * s;
-        vel[0][o] = g.Q[QU][cb];
-        vel[1][o] = NDIM >= 2 ? g.Q[QV][cb] : 0.0;
-        vel[2][o] = NDIM >= 3 ? g.Q[QW][cb] : 0.0;
-        Tc[o] = g.Q[QT][cb];
-        muc[o] = g.Q[QMU][cb];
-      }
       mfD = g.mf[D][f];
       double muf = interp4(muc[0], muc[1], muc[2], muc[3]);
-      double uf[3], dn[3];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        uf[c] = interp4(vel[c][0], vel[c][1], vel[c][2], vel[c][3]);
-        dn[c] = dface4(vel[c][0], vel[c][1], vel[c][2], vel[c][3]) * mfD;
-      }
+      for (int c = 0; c < 3; ++c) dn[c] *= mfD;
       double dT = dface4(Tc[0], Tc[1], Tc[2], Tc[3]) * mfD;
       double divt = 0.0, dtn[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -521,36 +534,31 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
           gtn[o] = dcell4(Ud[cb - 2 * stt], Ud[cb - stt], Ud[cb + stt], Ud[cb + 2 * stt]) * mct;
         }
         divt += interp4(gtt[0], gtt[1], gtt[2], gtt[3]);
-        dtn[tt] = interp4(gtn[0], gtn[1], gtn[2], gtn[3]);
+        dtn[1 + r] = interp4(gtn[0], gtn[1], gtn[2], gtn[3]);
       }
-      double brk[3] = {0.0, 0.0, 0.0};
-      brk[D] = (4.0 / 3.0) * dn[D] - (2.0 / 3.0) * divt;
-      if (T1 < NDIM) brk[T1] = dtn[T1] + dn[T1];
-      if (T2 < NDIM) brk[T2] = dtn[T2] + dn[T2];
-      double tau[3] = {muf * brk[0], muf * brk[1], muf * brk[2]};
+      // (component 0 normal, 1 along T1, 2 along T2)
+      constexpr bool on[3] = {true, T1 < NDIM, T2 < NDIM};
+      double brk[3];
+      brk[0] = (4.0 / 3.0) * dn[0] - (2.0 / 3.0) * divt;
+      brk[1] = on[1] ? dtn[1] + dn[1] : 0.0;
+      brk[2] = on[2] ? dtn[2] + dn[2] : 0.0;
       const double cpPr = g.cpPr;
-      double lam = muf * cpPr;
       // reverse
-      double enb = -Fb[4];
+      const double enb = -Fb[4];
+      const double Fm[3] = {Fb[1 + D], Fb[1 + T1], Fb[1 + T2]};
       double taub[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        taub[c] = -Fb[1 + c] + enb * uf[c];
-        ufb[c] = enb * tau[c];
+        taub[c] = -Fm[c] + enb * uf[c];
+        ufb[c] = enb * (muf * brk[c]);
       }
-      double lamb = enb * dT;
-      dTb = enb * lam;
-      mufb = lamb * cpPr + taub[0] * brk[0] + taub[1] * brk[1] + taub[2] * brk[2];
-      dnb[D] = taub[D] * muf * (4.0 / 3.0);
-      divtb = -taub[D] * muf * (2.0 / 3.0);
-      if (T1 < NDIM) {
-        dtnb[T1] = taub[T1] * muf;
-        dnb[T1] = taub[T1] * muf;
-      }
-      if (T2 < NDIM) {
-        dtnb[T2] = taub[T2] * muf;
-        dnb[T2] = taub[T2] * muf;
-      }
+      dTb = enb * (muf * cpPr);
+      mufb = enb * dT * cpPr + taub[0] * brk[0] + taub[1] * brk[1] + taub[2] * brk[2];
+      dnb[0] = taub[0] * muf * (4.0 / 3.0);
+      divtb = -taub[0] * muf * (2.0 / 3.0);
+#pragma unroll
+      for (int c = 1; c < 3; ++c)
+        if (on[c]) dnb[c] = dtnb[c] = taub[c] * muf;
     }
     // cells f-2 .. f+1 are window cells lane_face + 1 .. lane_face + 4; one
     // offset at a time so that no two faces update a cell together
@@ -563,16 +571,18 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
         const int ll = t.lane_line;
         const double dm = D4[o] * mfD, im = I4[o];
 #pragma unroll
-        for (int c = 0; c < NDIM; ++c) acc[1 + c][ll][w] += ufb[c] * im + dnb[c] * dm;
+        for (int c = 0; c < 3; ++c)
+          if (c == 0 || (c == 1 && T1 < NDIM) || (c == 2 && T2 < NDIM))
+            acc[ch[1 + c]][ll][w] += ufb[c] * im + dnb[c] * dm;
         acc[CT][ll][w] += dTb * dm;
         acc[CMU][ll][w] += mufb * im;
         if constexpr (T1 < NDIM) {
           acc[CG][ll][w] += divtb * im;
-          acc[CG + 1][ll][w] += dtnb[T1] * im;
+          acc[CG + 1][ll][w] += dtnb[1] * im;
         }
         if constexpr (T2 < NDIM) {
           acc[CG + 2][ll][w] += divtb * im;
-          acc[CG + 3][ll][w] += dtnb[T2] * im;
+          acc[CG + 3][ll][w] += dtnb[2] * im;
         }
       }
       // neighbouring faces update the same cells at consecutive offsets
@@ -587,12 +597,12 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
     const int ll = D == 0 ? i / NCW : i % TW, w = D == 0 ? i % NCW : i / TW;
     const int cell = t.f0 + OLO + w;
     if (cell < t.c0 || cell >= t.c1) continue;
-    long ln = t.lg * TW + ll;
-    if (ln >= (long)g.n[T1] * g.n[T2]) continue;
+    const unsigned ln = t.lg * TW + ll;
+    if (ln >= (unsigned)g.n[T1] * g.n[T2]) continue;
     int p[3];
     p[D] = cell;
-    p[T1] = (int)(ln % g.n[T1]);
-    p[T2] = (int)(ln / g.n[T1]);
+    p[T2] = g.n[T2] > 1 ? (int)(ln / (unsigned)g.n[T1]) : 0;
+    p[T1] = (int)ln - p[T2] * g.n[T1];
     const long b = bidx(g, p[0], p[1], p[2]);
     const bool ghost = cell < 0 || cell >= g.n[D];
     if constexpr (SIDE) {
