@@ -11,9 +11,9 @@
 //   Qb = sum over faces of (dF/dQ)^T Fb        (convective + dissipative),
 //   Qb += D_t^T Gb   (tangential derivatives were cell-centred, then
 //                     interpolated: their adjoint Gb is gathered along t),
-//   Tb += mu'(T) mub, then the halo fill is transposed axis by axis in the
-//   reverse order z, y, x (ghost adjoints fold into their sources and, for
-//   the porous wall, into dJ/dK), and Vb = b Wb + (dQ/dU)^T Qb.
+//   Tb += mu'(T) mub, then the halo fill is transposed (ghosts along two axes
+//   into those along one, these into their sources and, for the walls'
+//   parameters, into dJ/dK), and Vb = b Wb + (dQ/dU)^T Qb.
 // Every scatter of the reverse pass is done as a deterministic gather: face
 // adjoints are accumulated in LDS tiles offset by offset (one writer per
 // cell per phase), and the tile only writes the cells all of whose faces it
@@ -850,54 +850,6 @@ __device__ __forceinline__ void halo_images(int kind, int side, int i, int n, in
   if (kind == BC_DIRICHLET) cnt = 0;
 }
 
-// Ghost cells along exactly one axis: their complete adjoint, before the
-// interior cells collect it.  The flux tiles' contribution (Qb, or the side
-// array of the axis' direction), the tangential gather, mu'(T) folded into T,
-// and the ghosts along a second axis (the edges of the box) that copy this
-// cell: the halo fill runs along x, then y, then z, so its transpose folds z
-// ghosts first, and an edge's adjoint is a tangential gather alone (velocity
-// components: no face flux reads an edge, and no derivative that is a ghost
-// along two axes has an adjoint, so corners have none).
-// Launch and memory latency bound: a thread per ghost, no second pass over
-// the edges (this kernel and the collection in k_interior_vjp replace a
-// transpose launch per axis, 6 to 7 us each).
-template <int NDIM, int D, bool ALL3>
-__device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int want_dk,
-                                          const int *p);
-
-template <int NDIM, bool ALL3>
-__global__ void __launch_bounds__(64)
-k_ghost_vjp(Dev g, AdjBuffers A, int want_dk) {
-  long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long n0 = g.n[0], n1 = g.n[1], n2 = g.n[2];
-  // ghost number c (side, layer) of an axis of n cells -> its position
-  auto at = [](int c, int n) { return c < 3 ? c - 3 : n + c - 3; };
-  if (t < 6 * n1 * n2) {  // x ghosts: a line's six together
-    const long line = t / 6;
-    const int p[3] = {at((int)(t % 6), g.n[0]), (int)(line % n1), (int)(line / n1)};
-    ghost_vjp<NDIM, 0, ALL3>(g, A, want_dk, p);
-    return;
-  }
-  // y, then z ghosts: x fastest
-  t -= 6 * n1 * n2;
-  if constexpr (NDIM >= 2) {
-    if (t < 6 * n0 * n2) {
-      const long row = t / n0;
-      const int p[3] = {(int)(t % n0), at((int)(row % 6), g.n[1]), (int)(row / 6)};
-      ghost_vjp<NDIM, 1, ALL3>(g, A, want_dk, p);
-      return;
-    }
-    t -= 6 * n0 * n2;
-  }
-  if constexpr (NDIM == 3) {
-    if (t < 6 * n0 * n1) {
-      const long row = t / n0;
-      const int p[3] = {(int)(t % n0), (int)(row % n1), at((int)(row / n1), g.n[2])};
-      ghost_vjp<NDIM, 2, ALL3>(g, A, want_dk, p);
-    }
-  }
-}
-
 // The ghost at p, a ghost along axis D.
 template <int NDIM, int D, bool ALL3>
 __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int want_dk,
@@ -976,6 +928,51 @@ __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int
   for (int i = 0; i < HaloQ<NDIM>::nq; ++i) {
     const int q = HaloQ<NDIM>::qs[i];
     A.Qb[q][b] = qb[q];
+  }
+}
+
+// Ghost cells along exactly one axis: their complete adjoint, before the
+// interior cells collect it.  The flux tiles' contribution (Qb, or the side
+// array of the axis' direction), the tangential gather, mu'(T) folded into T,
+// and the ghosts along a second axis (the edges of the box) that copy this
+// cell: the halo fill runs along x, then y, then z, so its transpose folds z
+// ghosts first, and an edge's adjoint is a tangential gather alone (velocity
+// components: no face flux reads an edge, and no derivative that is a ghost
+// along two axes has an adjoint, so corners have none).
+// Launch and memory latency bound, a thread per ghost (1024 x 256: 5.7 us; this
+// kernel and the collection in k_interior_vjp, 13.3 to 15.1 us, took the place
+// of a 4.9 us gather and a transpose launch of 6.2 us per axis; 65 x 49 x 33:
+// 16 us and 9.4 to 17.4 for 7.2 and three of 7.0).
+template <int NDIM, bool ALL3>
+__global__ void __launch_bounds__(64)
+k_ghost_vjp(Dev g, AdjBuffers A, int want_dk) {
+  long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long n0 = g.n[0], n1 = g.n[1], n2 = g.n[2];
+  // ghost number c (side, layer) of an axis of n cells -> its position
+  auto at = [](int c, int n) { return c < 3 ? c - 3 : n + c - 3; };
+  if (t < 6 * n1 * n2) {  // x ghosts: a line's six together
+    const long line = t / 6;
+    const int p[3] = {at((int)(t % 6), g.n[0]), (int)(line % n1), (int)(line / n1)};
+    ghost_vjp<NDIM, 0, ALL3>(g, A, want_dk, p);
+    return;
+  }
+  // y, then z ghosts: x fastest
+  t -= 6 * n1 * n2;
+  if constexpr (NDIM >= 2) {
+    if (t < 6 * n0 * n2) {
+      const long row = t / n0;
+      const int p[3] = {(int)(t % n0), at((int)(row % 6), g.n[1]), (int)(row / 6)};
+      ghost_vjp<NDIM, 1, ALL3>(g, A, want_dk, p);
+      return;
+    }
+    t -= 6 * n0 * n2;
+  }
+  if constexpr (NDIM == 3) {
+    if (t < 6 * n0 * n1) {
+      const long row = t / n0;
+      const int p[3] = {(int)(t % n0), (int)(row % n1), at((int)(row / n1), g.n[2])};
+      ghost_vjp<NDIM, 2, ALL3>(g, A, want_dk, p);
+    }
   }
 }
 

@@ -14,7 +14,7 @@ struct AdjBuffers {
                     // added to Qb's on interior cells, Qb itself on y ghosts; every cell
                     // read is written each stage
   double *Qbz[NQ];  // the z tiles' (3D)
-  double *Gs[3];    // second direction's share of the adjoint of d u_t / d x_t (3D, as Qbz)
+  double *Gs[3];    // the later direction's share of the adjoint of d u_t / d x_t (3D, as Qbz)
   double *Ub1, *Ub2;  // stage adjoints
   const double *Wb;  // stage-output adjoint of the stage being reversed
   const double *dtp; // step size (device)
@@ -30,8 +30,12 @@ struct AdjBuffers {
 };
 
 // 3D grids whose flux adjoints run in one launch (side arrays for two
-// directions), else one launch per direction adding to Qb.  XXXRULE
-constexpr long ADJ_ALL3_CELLS = 1L << 19;
+// directions), else one launch per direction adding to Qb.  Up to this size a
+// direction's workgroups fit the chip at most twice over and each launch ends
+// with it half idle; beyond, the side arrays' traffic and memory cost more (a
+// reverse step at 65 x 49 x 33: 482 us in one launch, 550 in three; 64^3: 736
+// and 780; 96 x 64 x 64: 941 and 922; 128 x 64 x 64: 1249 and 1191).
+constexpr long ADJ_ALL3_CELLS = 1L << 18;
 inline bool adjoint_all3(const Dev &g) { return g.ndim == 3 && g.ncell <= ADJ_ALL3_CELLS; }
 
 // Lays the adjoint buffers out in the workspace (or measures them).
