@@ -141,7 +141,8 @@ def source_digest():
     """sha256 of the forward kernel sources (counters are tied to them)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("dcf_forward.hip", "dcf_common.hpp"):
+    for f in ("dcf_forward.hip", "dcf_stage.hip", "dcf_stage.hpp", "dcf_cells.hpp",
+              "dcf_common.hpp"):
         with open(os.path.join(ROOT, "paper_2406_19494_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -170,8 +171,24 @@ def measured_traffic(kernel, workload):
     return 1024.0 * (fk * float(vals["copy_factor_fetch"]) + wk * float(vals["copy_factor_write"]))
 
 
+def stage_kernel(case):
+    """Name of the kernel that runs a whole RK3 stage of `case` in one launch
+    (ghost cells, fluxes and update; short 1D lines run all steps of a call in
+    one), or None where a stage is split into the launches of step_kernel_ids:
+    3D grids with the TENO6-A scheme or with porous, disturbance or Dirichlet
+    faces."""
+    if case.ndim == 1:
+        return "k_line" if case.n[0] < 1024 and case.source == "none" else "k_stage1"
+    if case.ndim == 2:
+        return "k_stage2"
+    plain = all(b in ("periodic", "zerograd", "wall") for b in case.bc)
+    return "k_stage3" if case.scheme == "weno5" and plain else None
+
+
 def step_kernel_ids(case):
-    """dcf_time_kernel ids of the launches one RK3 stage of `case` runs:
+    """dcf_time_kernel ids of the launches one RK3 stage of `case` runs when it
+    is split (stage_kernel is None; otherwise these kernels are timed for the
+    record only):
     halo fill (0; 8 = ghosts only, stages 2-3 of a fused step), fluxes (7 =
     x+y of a 3D grid, 1..3 per direction; on 2D and 3D grids they compute the
     velocity derivatives they need themselves, so no derivative launch),
@@ -473,16 +490,18 @@ def main():
     ms_step = ms / args.steps
     value = case.ncells * 3 / (ms_step * 1e-3)
 
-    # Kernels of a step.  A 2D/3D step without source term (or with the
-    # body force and a periodic last direction) runs the last direction's
-    # fluxes fused with the stage update (k_flux_update); a 3D step launches
-    # the x and y fluxes as one grid (k_flux_xy).  The update of stages 1 and
-    # 2 also writes the next stage's primitive interior, so later stages fill
-    # only the ghosts (k_prim_ghost, 8; the first step of a call runs the
-    # whole halo fill, 0).  The unfused kernels are timed too, for the record.
+    # Kernels of a step.  Where a stage is one launch (stage_kernel) the step
+    # is that kernel three times, plus the CFL reduction.  Otherwise the last
+    # direction's fluxes are fused with the stage update (k_flux_update), the x
+    # and y fluxes of a 3D grid are one grid (k_flux_xy), and the update of
+    # stages 1 and 2 also writes the next stage's primitive interior, so later
+    # stages fill only the ghosts (k_prim_ghost, 8; the first step of a call
+    # runs the whole halo fill, 0).  The split kernels are timed back to back
+    # for the record in either case.
     names = {0: "k_prim_halo", 1: "k_flux_x", 2: "k_flux_yz<y>", 3: "k_flux_yz<z>", 4: "k_update",
              6: "k_flux_update", 7: "k_flux_xy", 8: "k_prim_ghost"}
     step_kinds = step_kernel_ids(case)
+    one_launch = stage_kernel(case)
     kinds = sorted(set(step_kinds) | set(range(1, case.ndim + 1)) | {4})
     kt = {w: s.time_kernel(U, w, reps=20) for w in kinds}  # back-to-back launches
 
@@ -490,8 +509,9 @@ def main():
     # event pairs around each of its launches on the stream of the stepping
     # call (dcf_probe_*), one replay of the timed region per kernel (the
     # timed value above runs without events).
+    # (one-launch stages answer to every id: probed once)
     probed = {}
-    for w in step_kinds:
+    for w in ([1 if case.ndim == 1 else 6] if one_launch else step_kinds):
         if w in (1, 6, 7, 8):
             s.probe_begin(w, 4 * args.steps + 8)
             s.steps_cfl(U, dt, args.steps, cfl=case.cfl)
@@ -517,6 +537,20 @@ def main():
         return None
 
     visc = case.visc_law != "none"
+
+    def stage_roof(t_ms):
+        # a whole stage in one launch against the unit figures of a cell-stage
+        t = t_ms * 1e-3
+        flops = case.ncells * flops_per_cell_stage(case)
+        nbytes = case.ncells * BYTES_PER_CELL_STAGE[case.ndim]
+        t_alu, t_hbm = flops / PEAK_FP64, nbytes / PEAK_HBM
+        out = {"algorithmic_flops": flops, "algorithmic_bytes": nbytes, "alu_frac": t_alu / t,
+               "hbm_frac": t_hbm / t}
+        if t_hbm > t_alu:
+            return {"bound": "hbm", "achieved": nbytes / t / 1e9, "peak": PEAK_HBM / 1e9,
+                    "unit": "GB/s", "frac": t_hbm / t} | out
+        return {"bound": "alu", "achieved": flops / t / 1e12, "peak": PEAK_FP64 / 1e12,
+                "unit": "TFLOP/s", "frac": t_alu / t} | out
 
     def kernel_roof(w, t_ms):
         # a launch against the roof that binds it: the larger of the FP64
@@ -551,6 +585,11 @@ def main():
 
     # dominant kernel: the step kernel with the most in-loop time per step
     # (launches per step x mean duration)
+    in_loop_name = {w: one_launch or names[w] for w in probed}
+
+    def in_loop_roof(w, t_ms):
+        return stage_roof(t_ms) if one_launch else kernel_roof(w, t_ms)
+
     if probed:
         dom = max(probed, key=lambda w: probed[w][0] * probed[w][1])
         probe_n, t_dom = probed[dom]
@@ -559,32 +598,33 @@ def main():
         probe_n, t_dom = 0, kt[dom]
     timing = ("HIP events around each launch inside the stepping loop, replay of the timed region"
               if probe_n else "HIP events over back-to-back launches")
-    roof = kernel_roof(dom, t_dom)
+    dom_name = in_loop_name.get(dom, names[dom])
+    roof = in_loop_roof(dom, t_dom) if probed else kernel_roof(dom, t_dom)
     roof = {k: roof[k] for k in ("bound", "achieved", "peak", "unit", "frac")} | {
-        "traffic": measured_traffic(names[dom], args.workload), "kernel": names[dom],
+        "traffic": measured_traffic(dom_name, args.workload), "kernel": dom_name,
         "avg_ms": t_dom, "launches_timed": probe_n, "timing": timing,
-        "avg_ms_back_to_back": kt[dom]} | {k: v for k, v in roof.items()
+        "avg_ms_back_to_back": None if probed and one_launch else kt[dom]} | {k: v for k, v in roof.items()
                                           if k not in ("bound", "achieved", "peak", "unit", "frac")}
     # the same launch against both roofs from the hardware counters: FP64
     # VALU operations issued and HBM bytes moved, per launch, over its time
-    vf = measured_valu(names[dom], args.workload)
+    vf = measured_valu(dom_name, args.workload)
     roof["valu_fp64_tflops"] = None if vf is None else vf / (t_dom * 1e-3) / 1e12
     roof["valu_frac"] = None if vf is None else vf / (t_dom * 1e-3) / PEAK_FP64
     tr = roof["traffic"]
     roof["hbm_frac_measured"] = None if tr is None else tr / (t_dom * 1e-3) / PEAK_HBM
     # every step kernel in the loop, and every kernel back to back, against
     # its own roof
-    roof["in_loop"] = {names[w]: {"launches_per_step": n_l / args.steps, "avg_ms": t_l,
-                                  "ms_per_step": n_l / args.steps * t_l,
-                                  "frac": kernel_roof(w, t_l)["frac"],
-                                  "bound": kernel_roof(w, t_l)["bound"]}
+    roof["in_loop"] = {in_loop_name[w]: {"launches_per_step": n_l / args.steps, "avg_ms": t_l,
+                                         "ms_per_step": n_l / args.steps * t_l,
+                                         "frac": in_loop_roof(w, t_l)["frac"],
+                                         "bound": in_loop_roof(w, t_l)["bound"]}
                        for w, (n_l, t_l) in probed.items()}
     per_kernel = {}
     for w in kinds:
         r = kernel_roof(w, kt[w])
         per_kernel[names[w]] = {"bound": r["bound"], "frac": r["frac"], "avg_ms": kt[w],
                                 ("achieved_tflops" if r["bound"] == "alu" else "achieved_gbs"):
-                                    r["achieved"], "in_step": w in step_kinds}
+                                    r["achieved"], "in_step": not one_launch and w in step_kinds}
         for k in ("alu_frac", "hbm_frac"):
             if k in r:
                 per_kernel[names[w]][k] = r[k]
@@ -611,7 +651,7 @@ def main():
     # committed summary matches the kernel sources)
     moved, complete = 0.0, True
     for w, (n_l, _) in probed.items():
-        tw = measured_traffic(names[w], args.workload)
+        tw = measured_traffic(in_loop_name[w], args.workload)
         if tw is None:
             complete = False
             break
@@ -641,7 +681,7 @@ def main():
         "roofline": roof,
         "stage_roofline": stage,
         "kernel_ms": {names[k]: v for k, v in kt.items()},
-        "step_kernels": [names[k] for k in step_kinds],
+        "step_kernels": [one_launch] if one_launch else [names[k] for k in step_kinds],
         "source_sha": source_digest(),
         "wall_s": wall,
     }

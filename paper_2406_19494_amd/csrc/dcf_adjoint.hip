@@ -743,13 +743,16 @@ __device__ __forceinline__ double dviscosity(const Dev &g, double T, double mu) 
 }
 
 // Gather of the tangential-derivative adjoints at box cell p: y = x + k along
-// t contributes coef(k) mc(y) Gb(y); the metric factors of the (at most
-// four) neighbours along each axis are shared by the NDIM velocity components.
-// INTERIOR: p is an interior cell (else a box cell of the ghost layers).  ALL3:
-// the diagonals' second shares are in Gs.
-template <int NDIM, bool INTERIOR, bool ALL3>
+// t contributes coef(k) mc(y) Gb(y) where y is interior along t; the metric
+// factors of the (at most four) neighbours along each axis are shared by the
+// NDIM velocity components.  G: the axes along which p is a ghost, as bits.
+// Along those only the two inward neighbours can be interior; a cell that is a
+// ghost along two axes has no derivative adjoint, so along the other axes of an
+// edge there is nothing to gather.  ALL3: the diagonals' second shares are in Gs.
+template <int NDIM, unsigned G, bool ALL3>
 __device__ __forceinline__ void tangential_gather(const Dev &g, const AdjBuffers &A, const int *p,
                                                   long b, double *add) {
+  constexpr bool edge = (G & (G - 1u)) != 0u;
   constexpr int ks[4] = {-1, 1, -2, 2};
   constexpr double cf[4] = {8.0 / 12.0, -8.0 / 12.0, -1.0 / 12.0, 1.0 / 12.0};
   // Every load is issued first, so all of them are in flight together, then
@@ -762,14 +765,19 @@ __device__ __forceinline__ void tangential_gather(const Dev &g, const AdjBuffers
   bool in[NDIM][4];
 #pragma unroll
   for (int t = 0; t < NDIM; ++t) {
+    const bool ghost = (G >> t) & 1u;
+    if (edge && !ghost) continue;
     const long st = g.sb[t];
-    const int pt = INTERIOR ? p[t] : min(max(p[t], 0), g.n[t] - 1);
+    const int pt = ghost ? min(max(p[t], 0), g.n[t] - 1) : p[t];
+    const int s = ghost && p[t] >= 0 ? -1 : 1;  // inwards
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int yt = p[t] + ks[r];
+    for (int r = 0; r < (ghost ? 2 : 4); ++r) {
+      const int k = ghost ? s * (r + 1) : ks[r];
+      const int yt = p[t] + k;
       in[t][r] = yt >= 0 && yt < g.n[t];
       mct[t][r] = g.mc[t][in[t][r] ? yt : pt];
-      const long bb = (INTERIOR || in[t][r]) ? b + ks[r] * st : b;
+      if (ghost) mct[t][r] *= (double)s;
+      const long bb = (G == 0u || in[t][r]) ? b + k * st : b;
 #pragma unroll
       for (int phi = 0; phi < NDIM; ++phi) gv[t][r][phi] = A.Gb[3 * t + phi][bb];
       if constexpr (ALL3) gv[t][r][t] += A.Gs[t][bb];
@@ -778,16 +786,19 @@ __device__ __forceinline__ void tangential_gather(const Dev &g, const AdjBuffers
 #pragma unroll
   for (int phi = 0; phi < NDIM; ++phi) add[phi] = 0.0;
 #pragma unroll
-  for (int t = 0; t < NDIM; ++t)
+  for (int t = 0; t < NDIM; ++t) {
+    const bool ghost = (G >> t) & 1u;
+    if (edge && !ghost) continue;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double w = cf[r] * mct[t][r];
+    for (int r = 0; r < (ghost ? 2 : 4); ++r) {
+      const double w = (ghost ? cf[2 * r + 1] : cf[r]) * mct[t][r];
 #pragma unroll
       for (int phi = 0; phi < NDIM; ++phi) {
         const double sum = add[phi] + w * gv[t][r][phi];
         add[phi] = in[t][r] ? sum : add[phi];
       }
     }
+  }
 }
 
 // Adjoint components carried through the halo fill: rho, the active
@@ -850,6 +861,35 @@ __device__ __forceinline__ void halo_images(int kind, int side, int i, int n, in
   if (kind == BC_DIRICHLET) cnt = 0;
 }
 
+// Adds the edges along axes D and E that fold into the ghost at p to its
+// velocity adjoints.
+template <int NDIM, int D, int E, bool ALL3>
+__device__ __forceinline__ void edge_ghosts(const Dev &g, const AdjBuffers &A, const int *p,
+                                            double *qb) {
+  if constexpr (E > D && E < NDIM) {
+    unsigned mask = 0u;
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      int m0, cnt;
+      halo_images(g.bck[2 * E + side], side, p[E], g.n[E], m0, cnt);
+      mask |= (cnt == 3 ? 7u : (cnt ? 1u << m0 : 0u)) << (3 * side);
+    }
+    while (mask) {
+      const int bit = __ffs(mask) - 1;
+      mask &= mask - 1u;
+      const int side = bit >= 3 ? 1 : 0, m = bit - 3 * side;
+      const bool wall = side ? is_wall(g.bck[2 * E + 1]) : is_wall(g.bck[2 * E]);
+      int pe[3] = {p[0], p[1], p[2]};
+      pe[E] = side == 0 ? -1 - m : g.n[E] + m;
+      double add[NDIM];
+      tangential_gather<NDIM, (1u << D) | (1u << E), ALL3>(g, A, pe, bidx(g, pe[0], pe[1], pe[2]),
+                                                          add);
+#pragma unroll
+      for (int phi = 0; phi < NDIM; ++phi) qb[QU + phi] += wall ? -add[phi] : add[phi];
+    }
+  }
+}
+
 // The ghost at p, a ghost along axis D.
 template <int NDIM, int D, bool ALL3>
 __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int want_dk,
@@ -872,39 +912,14 @@ __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int
   if (visc) qb[QT] += dviscosity(g, Tq, muq) * qb[QMU];
   if (gather) {
     double add[NDIM];
-    tangential_gather<NDIM, false, ALL3>(g, A, p, b, add);
+    tangential_gather<NDIM, 1u << D, ALL3>(g, A, p, b, add);
 #pragma unroll
     for (int phi = 0; phi < NDIM; ++phi) qb[QU + phi] += add[phi];
   }
-  // the edges folded into this ghost: layers of the axes e after D, as bits
-  // (2 (e - 1) + side) 3 + layer; each lane takes its next one per pass
-  if (gather && D + 1 < NDIM) {
-    unsigned mask = 0u, walls = 0u;
-#pragma unroll
-    for (int e = 1; e < NDIM; ++e) {
-      if (e <= D) continue;
-#pragma unroll
-      for (int side = 0; side < 2; ++side) {
-        int m0, cnt;
-        halo_images(g.bck[2 * e + side], side, p[e], g.n[e], m0, cnt);
-        mask |= (cnt == 3 ? 7u : (cnt ? 1u << m0 : 0u)) << (3 * (2 * (e - 1) + side));
-        if (is_wall(g.bck[2 * e + side])) walls |= 1u << (2 * (e - 1) + side);
-      }
-    }
-    while (mask) {
-      const int bit = __ffs(mask) - 1;
-      mask &= mask - 1u;
-      const int fs = bit / 3, m = bit - 3 * fs, side = fs & 1;
-      const bool ez = fs >= 2;
-      const int x = side == 0 ? -1 - m : (ez ? g.n[2] : g.n[1]) + m;
-      const int pe[3] = {p[0], ez ? p[1] : x, ez ? x : p[2]};
-      double add[NDIM];
-      tangential_gather<NDIM, false, ALL3>(g, A, pe, bidx(g, pe[0], pe[1], pe[2]), add);
-      const double sign = (walls >> fs) & 1u ? -1.0 : 1.0;
-#pragma unroll
-      for (int phi = 0; phi < NDIM; ++phi) qb[QU + phi] += sign * add[phi];
-    }
-  }
+  // the edges folded into this ghost: the layers of both sides of an axis e
+  // after D, as bits 3 side + layer; each lane takes its next one per pass
+  if (gather) edge_ghosts<NDIM, D, 1, ALL3>(g, A, p, qb);
+  if (gather) edge_ghosts<NDIM, D, 2, ALL3>(g, A, p, qb);
   // the (A, kappa) of a z disturbance wall act on its edge columns too, those
   // whose x lies inside: the layer-0 source's thread sums the column
   if (NDIM == 3 && D == 1 && want_dk) {
@@ -918,7 +933,7 @@ __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int
         for (int m = 0; m < 3; ++m) {
           const int pe[3] = {p[0], p[1], side == 0 ? -1 - m : g.n[2] + m};
           double add[NDIM];
-          tangential_gather<NDIM, false, ALL3>(g, A, pe, bidx(g, pe[0], pe[1], pe[2]), add);
+          tangential_gather<NDIM, 6u, ALL3>(g, A, pe, bidx(g, pe[0], pe[1], pe[2]), add);
           vsum += add[NDIM - 1];
         }
       A.dpart[side * A.dcols + (long)(p[1] + 3) * g.n[0] + p[0]] = vsum;
@@ -1162,7 +1177,7 @@ k_interior_vjp(Dev g, AdjBuffers A, const double *V,
   }
   if (NDIM >= 2 && A.Gb[0] != nullptr) {
     double add[NDIM];
-    tangential_gather<NDIM, true, ALL3>(g, A, pc, bx, add);
+    tangential_gather<NDIM, 0u, ALL3>(g, A, pc, bx, add);
 #pragma unroll
     for (int phi = 0; phi < NDIM; ++phi) ub[phi] += add[phi];
   }
