@@ -338,11 +338,13 @@ dcf_status dcf_gradient(dcf_ctx *ctx, const double *U0_dev, int nsteps, const do
  * which: 0 primitive box + halos, 1/2/3 face fluxes along x/y/z, 4 the
  * divergence + RK stage update, 5 the cell-centred velocity derivatives,
  * 6 the last direction's fluxes fused with the divergence and stage update
- * (2D/3D without source term; the kernel dcf_rk3_step runs in place of 3 or
- * 2 and 4), 7 the x and y face fluxes of a 3D grid in one launch (the form
- * the step runs in place of 1 and 2), 8 the ghost cells of the primitive box
- * alone (stages 2 and 3 of such a step: the previous stage's update wrote
- * the interior).  5 and 9 are not used: the flux kernels compute the
+ * (2D/3D without source term), 7 the x and y face fluxes of a 3D grid in one
+ * launch, 8 the ghost cells of the primitive box alone (stages 2 and 3 of a
+ * split step: the previous stage's update wrote the interior).  These are the
+ * kernels of a split stage, which dcf_rk3_step runs on 3D grids with the
+ * TENO6-A scheme or with porous, disturbance or Dirichlet faces; other grids
+ * run each stage in one launch, which these kernels do not time (the probe
+ * below does).  5 and 9 are not used: the flux kernels compute the
  * cell-centred velocity derivatives while staging their tiles (no separate
  * derivative launch).  The inputs it needs (primitive box, face fluxes) are
  * computed from U once before timing.  DCF_EINVAL for an unknown `which` or
@@ -354,11 +356,12 @@ dcf_status dcf_time_kernel(dcf_ctx *ctx, const double *U_dev, int which, int rep
  * dcf_time_kernel: 1 x fluxes of a 2D step, 6 fused last-direction flux +
  * update, 7 x + y fluxes of a 3D step, 8 ghost fill of stages after the
  * first (with the carried CFL reduction where a step follows another in one
- * call)) that the fused stepping calls (dcf_rk3_step,
- * dcf_rk3_step_cfl, dcf_rk3_steps_cfl) make is bracketed by a pair of HIP
- * events recorded on that call's stream, up to max_launches launches (later
- * ones are not recorded).  The events are created here and owned by the
- * context.  dcf_probe_end waits for the last recorded event, returns the
+ * call)) that the stepping calls (dcf_rk3_step, dcf_rk3_step_cfl,
+ * dcf_rk3_steps_cfl) make is bracketed by a pair of HIP events recorded on
+ * that call's stream, up to max_launches launches (later ones are not
+ * recorded).  Where a stage is one launch, that launch is bracketed whichever
+ * id is armed (8: not the first stage of a call).  The events are created here
+ * and owned by the context.  dcf_probe_end waits for the last recorded event, returns the
  * number of recorded launches and their mean duration in milliseconds, and
  * releases the events (a later dcf_probe_begin may arm again).  DCF_EINVAL for
  * an id that cannot be probed, max_launches outside [1, 2^20], arming twice or

@@ -356,17 +356,17 @@ __host__ inline unsigned tile_count(const Dev &g, int D) {
 // Both share the face adjoint from Wb and one LDS window of cells
 // (f0-3 .. f0+TF+1 per line); the tile writes each completed cell once.
 // ---------------------------------------------------------------------------
-// LDS of one tile: the accumulators (NCH channels x TW lines x NCW window
-// cells) and, along y and z, the staging rows of the convective gather.
+// LDS of one tile: each wavefront's accumulators, NCH channels of the cells its
+// 64 faces touch.  A wavefront holds 64 faces of one line (x) or 8 faces of 8
+// lines (y, z: line fastest), so the cell at offset o of its lane's face is
+// entry lane + ST o: consecutive entries for consecutive lanes.
 template <int NDIM, int D, bool VISC> struct DirLds {
   static constexpr int TF = TileShape<D>::TF, TW = TileShape<D>::TW;
   static constexpr int NOFF = 6, NCW = TF + 5;
   static constexpr int CP = 1 + NDIM, CT = 2 + NDIM, CMU = 3 + NDIM, CG = 4 + NDIM;
   static constexpr int NCH = VISC ? CG + 2 * (NDIM - 1) : CP + 1;
-  static constexpr int BF = D == 0 ? TF : TF + 4;
-  static constexpr int ACC = NCH * TW * NCW;
-  static constexpr int BUF = D == 0 ? 0 : NOFF * TW * BF;
-  static constexpr int SIZE = ACC + BUF;  // doubles
+  static constexpr int ST = D == 0 ? 1 : TW, RW = 64 + (NOFF - 1) * ST;
+  static constexpr int SIZE = 4 * NCH * RW;  // doubles
 };
 
 // One tile of direction D.  ALL: the tiles of every direction run in one launch,
@@ -380,30 +380,22 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
   using L = DirLds<NDIM, D, VISC>;
   constexpr bool SIDE = ALL && D > 0;
   constexpr int OLO = -3, OHI = 2, NOFF = L::NOFF, SPAN = OHI - OLO;
-  constexpr int TF = L::TF, TW = L::TW;
+  constexpr int TW = L::TW;
   constexpr int NCW = L::NCW;  // window cells per line
   constexpr int T1 = tan1(D), T2 = tan2(D);
   // accumulator channels, active axes only: rho, the NDIM global velocity
   // components, p, then T, mu and Gb(T1,T1), Gb(T1,D) (Gb(T2,T2), Gb(T2,D))
-  // for each active tangential axis when viscous.  In 2D this is 8 channels,
-  // which keeps a y tile within a fifth of the CU's LDS (5 blocks per CU).
+  // for each active tangential axis when viscous
   constexpr int CP = L::CP, CT = L::CT, CMU = L::CMU, CG = L::CG;
-  constexpr int NCH = L::NCH;
-  // y/z tiles: a row stride of 36 doubles puts the 8 lines x 4 faces of a
-  // half-wave on distinct LDS banks
-  constexpr int BF = L::BF;
-  auto acc = reinterpret_cast<double (*)[TW][NCW]>(lds);
-  auto buf = reinterpret_cast<double (*)[TW][BF]>(lds + L::ACC);
-  static_assert(NCH * TW * NCW == L::ACC, "accumulator layout");
+  constexpr int NCH = L::NCH, ST = L::ST, RW = L::RW;
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  // [channel][entry] of this wavefront, which alone touches it before the
+  // write-out: LDS operations of a wavefront are in order, no barriers
+  double *acc = lds + wave * NCH * RW;
   Tile t = make_tile<OLO, OHI, D>(g, P, nb);
   if (!t.valid) return;  // uniform across the workgroup
   // (the convective channels 0 .. CP are set by the first pass)
-  for (int i = threadIdx.x; i < (NCH - CT) * TW * NCW; i += 256) (&acc[CT][0][0])[i] = 0.0;
-  // x tiles: each wavefront holds the 64 faces of one line and its lanes
-  // are the only writers of that line's window, one lane per cell in the
-  // convective gather, so after this barrier that gather uses lane shuffles
-  // and no barrier
-  if (D == 0) __syncthreads();
+  for (int i = lane; i < (NCH - CT) * RW; i += 64) acc[CT * RW + i] = 0.0;
 
   const int f = t.f0 + t.lane_face;
   const bool active = t.line_ok && f >= 0 && f <= g.n[D];
@@ -473,36 +465,18 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
       }
       weno5_vjp(v0, v1, v2, v3, v4, v5, qLb[m], qRb[m], c);
     }
-    if (D == 0) {
-      // window cell w = L (and w = 64 + L for the last SPAN cells) takes
-      // offset o from lane w - o, in the order of the LDS gather below
-      const int L = t.lane_face;
-      double s0 = 0.0, s1 = 0.0;
+    // entry L (and 64 + L for the last SPAN cells) takes offset o from lane
+    // L - ST o, in a fixed order of faces
+    double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-      for (int o = 0; o < NOFF; ++o) {
-        const double v0 = __shfl(c[o], L - o);
-        const double v1 = __shfl(c[o], TF + L - o);
-        if (L >= o) s0 += v0;
-        if (o > L) s1 += v1;
-      }
-      acc[ch[m]][t.lane_line][L] = s0;
-      if (L < SPAN) acc[ch[m]][t.lane_line][TF + L] = s1;
-      continue;
+    for (int o = 0; o < NOFF; ++o) {
+      const double x0 = __shfl(c[o], lane - ST * o);
+      const double x1 = __shfl(c[o], 64 + lane - ST * o);
+      if (lane >= ST * o) s0 += x0;
+      if (ST * o > lane) s1 += x1;
     }
-#pragma unroll
-    for (int o = 0; o < NOFF; ++o) buf[o][t.lane_line][t.lane_face] = c[o];
-    __syncthreads();
-    for (int i = threadIdx.x; i < TW * NCW; i += 256) {
-      const int ll = i / NCW, w = i % NCW;
-      double sum = 0.0;
-#pragma unroll
-      for (int o = 0; o < NOFF; ++o) {
-        const int fl = w - o;  // face (lane) whose offset o lands on window cell w
-        if (fl >= 0 && fl < TF) sum += buf[o][ll][fl];
-      }
-      acc[ch[m]][ll][w] = sum;
-    }
-    __syncthreads();
+    acc[ch[m] * RW + lane] = s0;
+    if (lane < SPAN * ST) acc[ch[m] * RW + 64 + lane] = s1;
   }
   if constexpr (VISC) {
     // face-level adjoints of the dissipative flux
@@ -560,36 +534,35 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
       for (int c = 1; c < 3; ++c)
         if (on[c]) dnb[c] = dtnb[c] = taub[c] * muf;
     }
-    // cells f-2 .. f+1 are window cells lane_face + 1 .. lane_face + 4; one
-    // offset at a time so that no two faces update a cell together
+    // cells f-2 .. f+1 are the entries at offsets 1 .. 4, one offset at a time:
+    // neighbouring faces update the same cells at consecutive offsets
     const double I4[4] = {-1.0 / 16.0, 9.0 / 16.0, 9.0 / 16.0, -1.0 / 16.0};
     const double D4[4] = {1.0 / 24.0, -27.0 / 24.0, 27.0 / 24.0, -1.0 / 24.0};
 #pragma unroll
     for (int o = 0; o < 4; ++o) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
       if (active) {
-        const int w = t.lane_face + 1 + o;
-        const int ll = t.lane_line;
+        double *w = acc + lane + ST * (1 + o);
         const double dm = D4[o] * mfD, im = I4[o];
 #pragma unroll
         for (int c = 0; c < 3; ++c)
           if (c == 0 || (c == 1 && T1 < NDIM) || (c == 2 && T2 < NDIM))
-            acc[ch[1 + c]][ll][w] += ufb[c] * im + dnb[c] * dm;
-        acc[CT][ll][w] += dTb * dm;
-        acc[CMU][ll][w] += mufb * im;
+            w[ch[1 + c] * RW] += ufb[c] * im + dnb[c] * dm;
+        w[CT * RW] += dTb * dm;
+        w[CMU * RW] += mufb * im;
         if constexpr (T1 < NDIM) {
-          acc[CG][ll][w] += divtb * im;
-          acc[CG + 1][ll][w] += dtnb[1] * im;
+          w[CG * RW] += divtb * im;
+          w[(CG + 1) * RW] += dtnb[1] * im;
         }
         if constexpr (T2 < NDIM) {
-          acc[CG + 2][ll][w] += divtb * im;
-          acc[CG + 3][ll][w] += dtnb[2] * im;
+          w[(CG + 2) * RW] += divtb * im;
+          w[(CG + 3) * RW] += dtnb[2] * im;
         }
       }
-      // neighbouring faces update the same cells at consecutive offsets
-      __syncthreads();
     }
   }
-  if (D == 0 && !VISC) __syncthreads();  // every line's window complete before the write-out
+  __syncthreads();  // every line's window complete before the write-out
   // write the completed cells: window cell w <-> cell t.f0 + OLO + w
   for (int i = threadIdx.x; i < TW * NCW; i += 256) {
     // x-lines: consecutive threads take consecutive cells of a line;
@@ -605,39 +578,54 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
     p[T1] = (int)ln - p[T2] * g.n[T1];
     const long b = bidx(g, p[0], p[1], p[2]);
     const bool ghost = cell < 0 || cell >= g.n[D];
+    // the window cell's sum: x tiles, its line's entry; y and z tiles, the
+    // wavefront whose faces start at or before it and the one before that
+    double sum[NCH];
+    if constexpr (D == 0) {
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) sum[k] = lds[(ll * NCH + k) * RW + w];
+    } else {
+      const int wv = w / 8, x = w % 8;
+      const bool own = wv < 4, before = wv > 0 && x < SPAN;
+      const double *a0 = lds + (own ? wv : 3) * NCH * RW + x * TW + ll;
+      const double *a1 = lds + (before ? wv - 1 : 0) * NCH * RW + ((before ? x : 0) + 8) * TW + ll;
+#pragma unroll
+      for (int k = 0; k < NCH; ++k)
+        sum[k] = (before ? a1[k * RW] : 0.0) + (own ? a0[k * RW] : 0.0);
+    }
     if constexpr (SIDE) {
       double *const *Qs = D == 1 ? A.Qby : A.Qbz;
-      Qs[QR][b] = acc[0][ll][w];
+      Qs[QR][b] = sum[0];
 #pragma unroll
-      for (int c = 0; c < NDIM; ++c) Qs[QU + c][b] = acc[1 + c][ll][w];
-      Qs[QP][b] = acc[CP][ll][w];
+      for (int c = 0; c < NDIM; ++c) Qs[QU + c][b] = sum[1 + c];
+      Qs[QP][b] = sum[CP];
       if constexpr (VISC) {
-        Qs[QT][b] = acc[CT][ll][w];
-        Qs[QMU][b] = acc[CMU][ll][w];
+        Qs[QT][b] = sum[CT];
+        Qs[QMU][b] = sum[CMU];
       } else {
         Qs[QT][b] = 0.0;
       }
     } else if (D == 0 || ghost) {
       // first writer of this cell in the stage: set every component the
       // later kernels accumulate into
-      A.Qb[QR][b] = acc[0][ll][w];
+      A.Qb[QR][b] = sum[0];
 #pragma unroll
-      for (int c = 0; c < NDIM; ++c) A.Qb[QU + c][b] = acc[1 + c][ll][w];
-      A.Qb[QP][b] = acc[CP][ll][w];
+      for (int c = 0; c < NDIM; ++c) A.Qb[QU + c][b] = sum[1 + c];
+      A.Qb[QP][b] = sum[CP];
       if constexpr (VISC) {
-        A.Qb[QT][b] = acc[CT][ll][w];
-        A.Qb[QMU][b] = acc[CMU][ll][w];
+        A.Qb[QT][b] = sum[CT];
+        A.Qb[QMU][b] = sum[CMU];
       } else {
         A.Qb[QT][b] = 0.0;
       }
     } else {
-      A.Qb[QR][b] += acc[0][ll][w];
+      A.Qb[QR][b] += sum[0];
 #pragma unroll
-      for (int c = 0; c < NDIM; ++c) A.Qb[QU + c][b] += acc[1 + c][ll][w];
-      A.Qb[QP][b] += acc[CP][ll][w];
+      for (int c = 0; c < NDIM; ++c) A.Qb[QU + c][b] += sum[1 + c];
+      A.Qb[QP][b] += sum[CP];
       if constexpr (VISC) {
-        A.Qb[QT][b] += acc[CT][ll][w];
-        A.Qb[QMU][b] += acc[CMU][ll][w];
+        A.Qb[QT][b] += sum[CT];
+        A.Qb[QMU][b] += sum[CMU];
       }
     }
     if constexpr (VISC) {
@@ -649,13 +637,13 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
       // a diagonal is set in Gs)
       if constexpr (T1 < NDIM) {
         double &d1 = (ALL && sh1 ? A.Gs[T1] : A.Gb[3 * T1 + T1])[b];
-        d1 = (!ALL && sh1 && !ghost ? d1 : 0.0) + acc[CG][ll][w];
-        A.Gb[3 * T1 + D][b] = acc[CG + 1][ll][w];
+        d1 = (!ALL && sh1 && !ghost ? d1 : 0.0) + sum[CG];
+        A.Gb[3 * T1 + D][b] = sum[CG + 1];
       }
       if constexpr (T2 < NDIM) {
         double &d2 = (ALL && sh2 ? A.Gs[T2] : A.Gb[3 * T2 + T2])[b];
-        d2 = (!ALL && sh2 && !ghost ? d2 : 0.0) + acc[CG + 2][ll][w];
-        A.Gb[3 * T2 + D][b] = acc[CG + 3][ll][w];
+        d2 = (!ALL && sh2 && !ghost ? d2 : 0.0) + sum[CG + 2];
+        A.Gb[3 * T2 + D][b] = sum[CG + 3];
       }
     }
   }

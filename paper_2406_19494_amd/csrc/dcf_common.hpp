@@ -328,7 +328,12 @@ __device__ __forceinline__ void hllc(const double *qL, const double *qR, double 
 // neighbouring differences (a, b) of the four inner cells,
 // e = 0.9 * 0.17 * (1e-3)^2 / (1 - 0.9 * 0.17); the mirrored differences give
 // the same measures, so C_T is shared by both sides.  Reciprocals are the
-// refined hardware ones (no IEEE division).
+// refined hardware ones (no IEEE division), one for the least ratio, one for a
+// side's four measures and one for both values: 5 per component where each
+// quotient had its own, 14.
+// The flux launches are bound by the issue of this arithmetic (VALU busy 87 %):
+// x + y faces of 256 x 128 x 128 in 638 us, 748 with the 14 reciprocals and 115
+// VGPRs (4 wavefronts per SIMD; 95 and 5 now), z faces + update 422 and 473.
 __device__ __forceinline__ void teno6a_pair(double v0, double v1, double v2, double v3, double v4,
                                             double v5, double &yl, double &yr) {
   constexpr double c1312 = 13.0 / 12.0;

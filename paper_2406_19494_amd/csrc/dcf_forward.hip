@@ -109,13 +109,9 @@ __global__ void __launch_bounds__(256) k_prim_halo(Dev g, const double *U) {
   prim_halo_body(g, U, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-
-// Ghost cell number t (after k_prim_interior): follow the chain of sources
-// back to an interior cell (or a Dirichlet profile), copy its primitives from
-// the box and apply the per-axis ghost transforms in x, y, z order; mu is
-// recomputed only where a transform changed T.
-
-// Ghost cell number t, after k_prim_interior has filled the interior.
+// Ghost cell number t, after k_prim_interior has filled the interior: follows
+// the chain of sources back to an interior cell (or a Dirichlet profile), whose
+// primitives it copies from the box.
 __device__ __forceinline__ void prim_ghost_body(const Dev &g, unsigned t) {
   if (t >= (unsigned)(g.nbox - g.ncell)) return;
   int p[3];
@@ -360,8 +356,7 @@ __device__ __forceinline__ void flux_x_body(const Dev &g, int nwmax, unsigned bi
 
 // Occupancy target of the x / x+y flux launches: 5 waves per SIMD with
 // WENO5-JS (no spill; the tiles are bound by per-wave latency, so the extra
-// wave pays); the TENO6-A instantiations keep the compiler's own allocation
-// (5 waves would spill there).
+// wave pays); the TENO6-A instantiations reach it by themselves.
 constexpr int flux_waves(int sch) { return sch == SCHEME_WENO5 ? 5 : 1; }
 
 template <int NDIM, bool VISC, int SCH = SCHEME_WENO5>
@@ -1089,11 +1084,6 @@ __global__ void k_copy(double *dst, const double *src, long n) {
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
     dst[i] = src[i];
 }
-__global__ void k_axpy(double *y, double a, const double *x, long n) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-    y[i] += a * x[i];
-}
-
 static inline unsigned grid_for(long n, int bs = 256) {
   long b = (n + bs - 1) / bs;
   return (unsigned)(b < 1 ? 1 : b);
@@ -1118,11 +1108,6 @@ hipError_t launch_copy(double *dst, const double *src, long n, hipStream_t st) {
   k_copy<<<grid_capped(n, 4096), 256, 0, st>>>(dst, src, n);
   return hipGetLastError();
 }
-hipError_t launch_axpy(double *y, double a, const double *x, long n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  k_axpy<<<grid_capped(n, 4096), 256, 0, st>>>(y, a, x, n);
-  return hipGetLastError();
-}
 
 hipError_t launch_metrics(int kind, double lo, double hi, double beta, int n, double *dx,
                           double *idx, double *mc, double *mf, double *xm, hipStream_t st) {
@@ -1137,8 +1122,8 @@ hipError_t launch_prim_halo(const Dev &g, const double *U, hipStream_t st) {
   // one launch while at most half of the box is ghost cells; otherwise interior
   // first, then the ghosts copied from it (then a second launch costs less than
   // ghost threads that convert their source state themselves; 65 x 49 x 33, 31 %
-  // ghosts: 7.8 us in one launch, 11.3 in two)
-  if ((g.nbox - g.ncell) * (g.nbox < 1L << 20 ? 2 : 10) <= g.nbox) {
+  // ghosts: 7.8 us in one launch, 11.3 in two; 256 x 128 x 128, 11 %: 86 and 92)
+  if ((g.nbox - g.ncell) * 2 <= g.nbox) {
     k_prim_halo<<<grid_for(g.nbox), 256, 0, st>>>(g, U);
   } else {
     k_prim_interior<<<grid_for(g.ncell), 256, 0, st>>>(g, U);
@@ -1322,10 +1307,6 @@ unsigned update_blocks(const Dev &g) { return grid_for(g.ncell); }
 hipError_t launch_dt_final(const double *part, int nparts, double cfl, double dt_max, double *dt,
                            hipStream_t st) {
   k_dt_final<<<1, 256, 0, st>>>(part, nparts, cfl, dt_max, dt);
-  return hipGetLastError();
-}
-hipError_t launch_prim_interior(const Dev &g, const double *U, hipStream_t st) {
-  k_prim_interior<<<grid_for(g.ncell), 256, 0, st>>>(g, U);
   return hipGetLastError();
 }
 hipError_t launch_prim_ghost_dt(const Dev &g, const double *part, int nparts, double cfl,

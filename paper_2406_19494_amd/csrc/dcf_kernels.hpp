@@ -160,9 +160,6 @@ hipError_t launch_prim_ghost(const Dev &g, hipStream_t st);
 // part as left by earlier launches and writes dt for later ones).
 hipError_t launch_prim_ghost_dt(const Dev &g, const double *part, int nparts, double cfl,
                                double dt_max, double *dt, hipStream_t st);
-// The interior cells' primitives alone (the first launch of launch_prim_halo's
-// two-launch form).
-hipError_t launch_prim_interior(const Dev &g, const double *U, hipStream_t st);
 hipError_t launch_dt_final(const double *part, int nparts, double cfl, double dt_max, double *dt,
                            hipStream_t st);
 hipError_t launch_dt(const Dev &g, const double *U, double cfl, double dt_max, double *part,
@@ -173,6 +170,5 @@ hipError_t launch_cost(const Dev &g, int face, double pref, const double *U, dou
                        double *J, double *grad, hipStream_t st);
 hipError_t launch_fill(double *p, double v, long n, hipStream_t st);
 hipError_t launch_copy(double *dst, const double *src, long n, hipStream_t st);
-hipError_t launch_axpy(double *y, double a, const double *x, long n, hipStream_t st);
 
 }  // namespace dcf

@@ -11,7 +11,11 @@ namespace dcf {
 // 1D.  A line of fewer than 1024 cells is stepped by one workgroup, one cell and
 // one face per thread, with the state in registers: all stages of all steps of
 // a call in one launch (a stage of 200 cells takes 1.5 us, a launch by itself
-// 3.5).  Longer lines take a launch per stage, in tiles of 255 cells.
+// 3.5; 10 CFL steps of 200 cells in a call: 393 us with five launches a stage,
+// 57 so).  What bounds it is the chain of one face's flux and the barriers
+// between its stages.  Longer lines take a launch per stage, in tiles of 255
+// cells (256 faces): 4001 cells, 4 steps: 165 us with split launches, 68 so,
+// launches and their starts.
 // ---------------------------------------------------------------------------
 template <bool VISC> struct Line1 {
   static constexpr int NP = VISC ? 5 : 3;  // rho, u, p (, T, mu)
@@ -196,7 +200,12 @@ __global__ void __launch_bounds__(256) k_stage1(Dev g, StageArgs A) {
 }
 
 // ---------------------------------------------------------------------------
-// 2D: tiles of TX x TY cells.
+// 2D: tiles of TX x TY cells, a window cell and a face per thread.  Bound by the
+// latency of a tile's phases (window, derivatives, faces, update) at two
+// workgroups of 8 wavefronts per CU: VALU busy 37 %, 48 % of a wavefront's
+// cycles waiting for data, 23 MB of HBM traffic.  1024 x 256: 22 to 24 us per
+// stage, 32 with ghost, x flux and y flux + update launches; 256 x 64: 8.0 and
+// 18.
 // ---------------------------------------------------------------------------
 // SMALL: 12 x 8 cells and 4 wavefronts, else 16 x 16 cells and 8 wavefronts.
 template <bool VISC, int SCH, bool SMALL> struct Tile2 {
@@ -396,7 +405,9 @@ k_stage2(Dev g, StageArgs A, unsigned nbx) {
 // The two kinds run loops of their own with the same number of barriers, so
 // that the windows of the one and the face stencils of the other never share
 // registers (in one loop they do not fit 256 VGPRs: 250 spills per plane, 1250
-// us per stage of 192 x 128 x 128).
+// us per stage of 192 x 128 x 128).  So: 340 to 353 us, VALU busy 60 %, 0.95 GB of
+// HBM traffic, for 522 us and 2.3 GB in ghost, x + y flux, z flux + update and
+// force launches; 64^3: 50 us for 53.
 // ---------------------------------------------------------------------------
 template <bool VISC> struct Col3 {
   static constexpr int TX = 15, TY = 16;
