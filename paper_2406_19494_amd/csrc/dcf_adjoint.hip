@@ -24,15 +24,15 @@
 
 namespace dcf {
 
-// Tile shape of direction D (TF faces per line x TW lines = 256 threads):
-// x-faces run along the lanes (64 x 4); y and z tiles take 8 neighbouring
-// x-lines so that a cell row is read and written in 64-byte segments
-// (32 x 8, at the price of more faces recomputed at tile edges).
-template <int D> struct TileShape {
-  static constexpr int TF = D == 0 ? 64 : 32;
-  static constexpr int TW = 256 / TF;
+// Tile shape of direction D for workgroups of NWV wavefronts (TF faces per line x
+// TW lines): x-faces run along the lanes, a line per wavefront; y and z tiles take
+// 8 neighbouring x-lines so that a cell row is read and written in 64-byte
+// segments, 8 faces of them per wavefront.  A tile completes TF - 5 cells per
+// line; the faces of the other 5 are computed twice.
+template <int D, int NWV> struct TileShape {
+  static constexpr int TF = D == 0 ? 64 : 8 * NWV;
+  static constexpr int TW = D == 0 ? NWV : 8;
 };
-__host__ inline int tile_faces(int D) { return D == 0 ? 64 : 32; }
 
 // ---------------------------------------------------------------------------
 // Reverse of WENO5-JS at one face (the arithmetic of weno5_pair): the adjoints
@@ -293,9 +293,9 @@ struct Tile {
 // P: the workgroup's index among the nb workgroups of direction D (the
 // hardware index modulo 8 must equal P modulo 8: the XCD order below assumes
 // it); t.valid is false for workgroups beyond the direction's tile count
-template <int OLO, int OHI, int D>
+template <int OLO, int OHI, int D, int NWV>
 __device__ __forceinline__ Tile make_tile(const Dev &g, unsigned P, unsigned nb) {
-  constexpr int TF = TileShape<D>::TF, TW = TileShape<D>::TW;
+  constexpr int TF = TileShape<D, NWV>::TF, TW = TileShape<D, NWV>::TW;
   constexpr int SPAN = OHI - OLO;
   constexpr int CPT = TF - SPAN;  // cells completed per tile line
   const int T1 = tan1(D), T2 = tan2(D);
@@ -335,15 +335,29 @@ __device__ __forceinline__ Tile make_tile(const Dev &g, unsigned P, unsigned nb)
   return t;
 }
 
+// Tiles of direction D in workgroups of nwv wavefronts.
 template <int OLO, int OHI>
-__host__ inline unsigned tile_count(const Dev &g, int D) {
-  const int TF = tile_faces(D), TW = 256 / TF;
+__host__ inline unsigned tile_count(const Dev &g, int D, int nwv) {
+  const int TF = D == 0 ? 64 : 8 * nwv, TW = D == 0 ? nwv : 8;
   constexpr int SPAN = OHI - OLO;
   const int CPT = TF - SPAN;
   const int ncell_line = g.n[D] + 1 + SPAN;
   const long tiles_d = (ncell_line + CPT - 1) / CPT;
   const long lines = (long)g.n[tan1(D)] * g.n[tan2(D)];
   return (unsigned)(tiles_d * ((lines + TW - 1) / TW));
+}
+
+// Wavefronts per workgroup for directions d0 .. d1 - 1: 4, or 8 where y and z
+// tiles twice as long leave fewer wavefronts in all (65 x 49 x 33, whose y lines
+// take one tile of 8 instead of three of 4: a training step 487 us, 501 with 4;
+// at equal counts 4 starts and ends sooner, 1024 x 256: 304 and 307).
+__host__ inline int dir_waves(const Dev &g, int d0, int d1) {
+  unsigned long w4 = 0, w8 = 0;
+  for (int D = d0; D < d1; ++D) {
+    w4 += 4ul * tile_count<-3, 2>(g, D, 4);
+    w8 += 8ul * tile_count<-3, 2>(g, D, 8);
+  }
+  return w8 < w4 ? 8 : 4;
 }
 
 // ---------------------------------------------------------------------------
@@ -355,18 +369,24 @@ __host__ inline unsigned tile_count(const Dev &g, int D) {
 //    the adjoint Gb of the cell-centred tangential velocity derivatives.
 // Both share the face adjoint from Wb and one LDS window of cells
 // (f0-3 .. f0+TF+1 per line); the tile writes each completed cell once.
+// Bound by the latency of a face's chain (loads, reconstructions, Riemann
+// solver, their reverse component by component) at 4 wavefronts per SIMD, 121
+// VGPRs in 2D: 5 with 96 spill and are slower by a quarter.  1024 x 256, both
+// directions: 54.7 us, 62 with staged gathers between barriers, stencils read
+// when needed and 113 instead of 76 FP64 instructions per reversed side;
+// 65 x 49 x 33, three directions: 73 us, 119 in three launches.
 // ---------------------------------------------------------------------------
 // LDS of one tile: each wavefront's accumulators, NCH channels of the cells its
 // 64 faces touch.  A wavefront holds 64 faces of one line (x) or 8 faces of 8
 // lines (y, z: line fastest), so the cell at offset o of its lane's face is
 // entry lane + ST o: consecutive entries for consecutive lanes.
-template <int NDIM, int D, bool VISC> struct DirLds {
-  static constexpr int TF = TileShape<D>::TF, TW = TileShape<D>::TW;
+template <int NDIM, int D, bool VISC, int NWV> struct DirLds {
+  static constexpr int TF = TileShape<D, NWV>::TF, TW = TileShape<D, NWV>::TW;
   static constexpr int NOFF = 6, NCW = TF + 5;
   static constexpr int CP = 1 + NDIM, CT = 2 + NDIM, CMU = 3 + NDIM, CG = 4 + NDIM;
   static constexpr int NCH = VISC ? CG + 2 * (NDIM - 1) : CP + 1;
   static constexpr int ST = D == 0 ? 1 : TW, RW = 64 + (NOFF - 1) * ST;
-  static constexpr int SIZE = 4 * NCH * RW;  // doubles
+  static constexpr int SIZE = NWV * NCH * RW;  // doubles
 };
 
 // One tile of direction D.  ALL: the tiles of every direction run in one launch,
@@ -374,10 +394,10 @@ template <int NDIM, int D, bool VISC> struct DirLds {
 // arrays Qby or Qbz (set, never added) instead of adding them to the Qb that
 // the x tiles set; k_ghost_vjp (ghost cells) and k_interior_vjp (interior
 // cells) add them.
-template <int NDIM, int D, bool VISC, bool ALL>
+template <int NDIM, int D, bool VISC, bool ALL, int NWV>
 __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, unsigned P,
                                              unsigned nb, double *lds) {
-  using L = DirLds<NDIM, D, VISC>;
+  using L = DirLds<NDIM, D, VISC, NWV>;
   constexpr bool SIDE = ALL && D > 0;
   constexpr int OLO = -3, OHI = 2, NOFF = L::NOFF, SPAN = OHI - OLO;
   constexpr int TW = L::TW;
@@ -392,7 +412,7 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
   // [channel][entry] of this wavefront, which alone touches it before the
   // write-out: LDS operations of a wavefront are in order, no barriers
   double *acc = lds + wave * NCH * RW;
-  Tile t = make_tile<OLO, OHI, D>(g, P, nb);
+  Tile t = make_tile<OLO, OHI, D, NWV>(g, P, nb);
   if (!t.valid) return;  // uniform across the workgroup
   // (the convective channels 0 .. CP are set by the first pass)
   for (int i = lane; i < (NCH - CT) * RW; i += 64) acc[CT * RW + i] = 0.0;
@@ -564,7 +584,7 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
   }
   __syncthreads();  // every line's window complete before the write-out
   // write the completed cells: window cell w <-> cell t.f0 + OLO + w
-  for (int i = threadIdx.x; i < TW * NCW; i += 256) {
+  for (int i = threadIdx.x; i < TW * NCW; i += 64 * NWV) {
     // x-lines: consecutive threads take consecutive cells of a line;
     // otherwise consecutive lines (x-neighbours) of one cell position
     const int ll = D == 0 ? i / NCW : i % TW, w = D == 0 ? i % NCW : i / TW;
@@ -586,8 +606,8 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
       for (int k = 0; k < NCH; ++k) sum[k] = lds[(ll * NCH + k) * RW + w];
     } else {
       const int wv = w / 8, x = w % 8;
-      const bool own = wv < 4, before = wv > 0 && x < SPAN;
-      const double *a0 = lds + (own ? wv : 3) * NCH * RW + x * TW + ll;
+      const bool own = wv < NWV, before = wv > 0 && x < SPAN;
+      const double *a0 = lds + (own ? wv : NWV - 1) * NCH * RW + x * TW + ll;
       const double *a1 = lds + (before ? wv - 1 : 0) * NCH * RW + ((before ? x : 0) + 8) * TW + ll;
 #pragma unroll
       for (int k = 0; k < NCH; ++k)
@@ -650,11 +670,11 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
 }
 
 // One direction per launch (1D, 3D).
-template <int NDIM, int D, bool VISC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+template <int NDIM, int D, bool VISC, int NWV>
+__global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(4)))
 k_dir_vjp(Dev g, AdjBuffers A) {
-  __shared__ double lds[DirLds<NDIM, D, VISC>::SIZE];
-  dir_vjp_tile<NDIM, D, VISC, false>(g, A, blockIdx.x, gridDim.x, lds);
+  __shared__ double lds[DirLds<NDIM, D, VISC, NWV>::SIZE];
+  dir_vjp_tile<NDIM, D, VISC, false, NWV>(g, A, blockIdx.x, gridDim.x, lds);
 }
 
 // The tiles of every direction of a stage in one launch, so that the
@@ -698,19 +718,20 @@ __device__ __forceinline__ void dir_of_group(const DirGroups &G, int nd, unsigne
   }
 }
 
-template <int NDIM, bool VISC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+template <int NDIM, bool VISC, int NWV>
+__global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(4)))
 k_dir_vjp_all(Dev g, AdjBuffers A, DirGroups G) {
-  constexpr int SX = DirLds<NDIM, 0, VISC>::SIZE, SY = DirLds<NDIM, 1, VISC>::SIZE;
+  constexpr int SX = DirLds<NDIM, 0, VISC, NWV>::SIZE, SY = DirLds<NDIM, 1, VISC, NWV>::SIZE;
   __shared__ double lds[SX > SY ? SX : SY];  // (z tiles as y tiles)
   unsigned ci;
   int dir;
   dir_of_group(G, NDIM, blockIdx.x / 8u, dir, ci);
   const unsigned P = ci * 8u + blockIdx.x % 8u;
-  if (dir == 0) dir_vjp_tile<NDIM, 0, VISC, true>(g, A, P, 8u * G.c[0], lds);
-  else if (NDIM == 2 || dir == 1) dir_vjp_tile<NDIM, 1, VISC, true>(g, A, P, 8u * G.c[1], lds);
+  if (dir == 0) dir_vjp_tile<NDIM, 0, VISC, true, NWV>(g, A, P, 8u * G.c[0], lds);
+  else if (NDIM == 2 || dir == 1)
+    dir_vjp_tile<NDIM, 1, VISC, true, NWV>(g, A, P, 8u * G.c[1], lds);
   else if constexpr (NDIM == 3)
-    dir_vjp_tile<NDIM, 2, VISC, true>(g, A, P, 8u * G.c[2], lds);
+    dir_vjp_tile<NDIM, 2, VISC, true, NWV>(g, A, P, 8u * G.c[2], lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1223,12 +1244,20 @@ k_interior_vjp(Dev g, AdjBuffers A, const double *V,
 // Host sequencing.
 // ---------------------------------------------------------------------------
 using AdjKernel = void (*)(Dev, AdjBuffers);
+using AdjAllKernel = void (*)(Dev, AdjBuffers, DirGroups);
 
-static AdjKernel dir_kernel(int nd, int D, bool visc) {
-  if (nd == 1) return visc ? k_dir_vjp<1, 0, true> : k_dir_vjp<1, 0, false>;
-  if (D == 0) return visc ? k_dir_vjp<3, 0, true> : k_dir_vjp<3, 0, false>;
-  if (D == 1) return visc ? k_dir_vjp<3, 1, true> : k_dir_vjp<3, 1, false>;
-  return visc ? k_dir_vjp<3, 2, true> : k_dir_vjp<3, 2, false>;
+template <bool VISC, int NWV> static AdjKernel dir_kernel_t(int nd, int D) {
+  if (nd == 1) return k_dir_vjp<1, 0, VISC, 4>;  // (x tiles: 4 lines)
+  if (D == 0) return k_dir_vjp<3, 0, VISC, 4>;
+  return D == 1 ? k_dir_vjp<3, 1, VISC, NWV> : k_dir_vjp<3, 2, VISC, NWV>;
+}
+static AdjKernel dir_kernel(int nd, int D, bool visc, int nwv) {
+  if (nwv == 8) return visc ? dir_kernel_t<true, 8>(nd, D) : dir_kernel_t<false, 8>(nd, D);
+  return visc ? dir_kernel_t<true, 4>(nd, D) : dir_kernel_t<false, 4>(nd, D);
+}
+template <int NWV> static AdjAllKernel all_kernel(int nd, bool visc) {
+  if (nd == 3) return visc ? k_dir_vjp_all<3, true, NWV> : k_dir_vjp_all<3, false, NWV>;
+  return visc ? k_dir_vjp_all<2, true, NWV> : k_dir_vjp_all<2, false, NWV>;
 }
 
 static inline unsigned blocks(long n) { return (unsigned)((n + 255) / 256 > 0 ? (n + 255) / 256 : 1); }
@@ -1286,18 +1315,19 @@ static hipError_t stage_vjp(const Dev &g, const AdjBuffers &A0, const double *V,
   if (g.ndim == 2 || all3) {
     DirGroups G = {};
     unsigned nblk = 0u;
+    const int nwv = dir_waves(g, 0, g.ndim);
     for (int D = 0; D < g.ndim; ++D) {
-      G.c[D] = (tile_count<-3, 2>(g, D) + 7u) / 8u;
+      G.c[D] = (tile_count<-3, 2>(g, D, nwv) + 7u) / 8u;
       nblk += 8u * G.c[D];
     }
-    auto k = all3 ? (visc ? k_dir_vjp_all<3, true> : k_dir_vjp_all<3, false>)
-                  : (visc ? k_dir_vjp_all<2, true> : k_dir_vjp_all<2, false>);
-    k<<<nblk, 256, 0, st>>>(g, A, G);
+    auto k = nwv == 8 ? all_kernel<8>(g.ndim, visc) : all_kernel<4>(g.ndim, visc);
+    k<<<nblk, 64 * nwv, 0, st>>>(g, A, G);
     DCF_TRY(hipGetLastError());
   } else {
     for (int D = 0; D < g.ndim; ++D) {
-      hipLaunchKernelGGL(dir_kernel(g.ndim, D, visc), dim3(tile_count<-3, 2>(g, D)), dim3(256),
-                         0, st, g, A);
+      const int nwv = D == 0 ? 4 : dir_waves(g, D, D + 1);
+      hipLaunchKernelGGL(dir_kernel(g.ndim, D, visc, nwv), dim3(tile_count<-3, 2>(g, D, nwv)),
+                         dim3(64 * nwv), 0, st, g, A);
       DCF_TRY(hipGetLastError());
     }
   }

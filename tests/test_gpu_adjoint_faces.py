@@ -41,6 +41,9 @@ FACES = {
     "disturb_z_3d": _case((5, 6, 5), (P2, W2, D2), "sutherland"),
     "disturb_x_3d": _case((6, 5, 4), (D2, P2, W2)),
     "disturb_z_inviscid_3d": _case((4, 5, 6), (Z2, P2, D2), "none"),
+    # tiles of 8 wavefronts (59 cells and their ghosts), the last that fill one
+    "long_y_2d": _case((4, 49, 1), (P2, W2)),
+    "long_y_full_2d": _case((3, 53, 1), (Z2, W2), "none"),
     "porous_y_3d": _case((6, 6, 4), (Z2, ("porous", "zerograd"), W2), porous=(2, 1, 5)),
 }
 
@@ -74,7 +77,9 @@ def test_faces_match_dense_oracle_adjoint(which):
         assert np.abs(gk - lk_or).max() <= VJP_TOL * np.abs(lk_or).max(), (gk, lk_or)
 
 
-@pytest.mark.parametrize("n", [(64, 64, 64), (64, 65, 64)], ids=["one_launch", "per_direction"])
+@pytest.mark.parametrize("n", [(64, 64, 64), (64, 65, 64), (19, 50, 49), (110, 49, 51)],
+                         ids=["one_launch", "per_direction", "one_launch_long_tiles",
+                              "per_direction_long_tiles"])
 @pytest.mark.parametrize("which", ["force", "disturb"])
 def test_both_3d_forms_dot_product(n, which):
     print(f"[3d forms] {n} {which}", flush=True)
