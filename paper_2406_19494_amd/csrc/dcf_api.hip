@@ -656,7 +656,11 @@ dcf_status dcf_rhs(dcf_ctx *c, const double *U, double *R, void *stream) {
   if (s) return s;
   if (!U || !R) return fail(DCF_EINVAL, "null array");
   hipStream_t st = (hipStream_t)stream;
-  if (stage_fused(c->g)) {
+  // the one-launch stage reads neighbours of U while it writes R: where the two
+  // overlap, the fluxes are computed in launches of their own first
+  const size_t bytes = sizeof(double) * (size_t)c->g.nv * c->g.ncell;
+  const uintptr_t u = (uintptr_t)U, r = (uintptr_t)R;
+  if (stage_fused(c->g) && (u + bytes <= r || r + bytes <= u)) {
     StageArgs A = {};
     A.Un = A.Uin = U;
     A.Rout = R;

@@ -44,6 +44,8 @@ FACES = {
     # tiles of 8 wavefronts (59 cells and their ghosts), the last that fill one
     "long_y_2d": _case((4, 49, 1), (P2, W2)),
     "long_y_full_2d": _case((3, 53, 1), (Z2, W2), "none"),
+    # more cells along the wall's normal than columns along the wall
+    "disturb_narrow_2d": _case((5, 21, 1), (Z2, ("disturb", "zerograd"))),
     "porous_y_3d": _case((6, 6, 4), (Z2, ("porous", "zerograd"), W2), porous=(2, 1, 5)),
 }
 

@@ -1,11 +1,14 @@
 """The one-launch stage kernels at the sizes where their tiles end: right-hand
 sides and chained CFL steps against the oracle, and gradients whose stage boxes
 are kept against gradients that rebuild them."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 from oracle.pyoracle import Oracle
+from paper_2406_19494_amd import binding as B
 from paper_2406_19494_amd import workloads as W
 from paper_2406_19494_amd.solver import Solver
 from tests.helpers import flux_scale, rel_err_per_var
@@ -81,6 +84,19 @@ def test_stage_kernels_at_tile_edges(which):
     err = rel_err_per_var(U.cpu().numpy(), ref, np.full(case.nv, vmax))
     assert np.all(err <= STEP_TOL * (rhs_tol / RHS_TOL)), err
     assert abs(dt.item() - dt_ref) <= STEP_TOL * (rhs_tol / RHS_TOL) * dt_ref
+
+
+@pytest.mark.parametrize("which", ["1d_1024", "2d_13x17_teno", "2d_25x9_force",
+                                   "3d_31x15x9_force", "3d_47x33x40"])
+def test_rhs_in_place(which):
+    case = _case(*EDGES[which])
+    o, s = Oracle(case), Solver(case)
+    U0 = o.cons(W.random_smooth(case, seed=5, amp=0.1))
+    U = torch.as_tensor(U0, device="cuda")
+    p = C.c_void_p(U.data_ptr())
+    B.call("dcf_rhs", s.ctx, p, p, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    err = rel_err_per_var(U.cpu().numpy(), o.rhs(U0), flux_scale(case, U0))
+    assert np.all(err <= (RHS_TOL if case.scheme == "weno5" else 1e-10)), err
 
 
 @pytest.mark.parametrize("which", ["1d_255", "1d_1024", "2d_25x9", "3d_16x17x4", "3d_15x16x5"])
