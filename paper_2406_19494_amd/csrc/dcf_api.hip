@@ -753,6 +753,13 @@ static dcf_status batch_fill(dcf_ctx *const *ctxs, double *const *U, double *con
       return fail(DCF_EUNSUPPORTED, "solve %d: source terms are not batched", i);
     if (g.scheme != SCHEME_WENO5)
       return fail(DCF_EUNSUPPORTED, "solve %d: batched steps are of the WENO5-JS scheme", i);
+  }
+  unsigned long work = 0;
+  unsigned first = 0;
+  for (int i = 0; i < n; ++i) work += stage_work(ctxs[i]->g);
+  for (int i = 0; i < n; ++i) {
+    dcf_ctx *c = ctxs[i];
+    const Dev &g = c->g;
     BatchEntry e;
     e.g = g;
     e.gb = g;
@@ -763,7 +770,9 @@ static dcf_status batch_fill(dcf_ctx *const *ctxs, double *const *U, double *con
     e.U2 = c->U2;
     e.dt = dt[i];
     e.part = c->part;
-    batch_entry_sizes(e, n);
+    batch_entry_sizes(e, work);
+    e.st_first = first;
+    first += e.st_tiles;
     memcpy(&h[i], &e, sizeof e);
   }
   return DCF_OK;

@@ -1398,10 +1398,10 @@ __global__ void __launch_bounds__(256) kb_dt_final(const BatchEntry *tab, double
   dt_final_body(e.part, (int)e.nb_dt, cfl, 1.0e300, e.dt);
 }
 
-void batch_entry_sizes(BatchEntry &e, int n) {
+void batch_entry_sizes(BatchEntry &e, unsigned long work) {
   const Dev &g = e.g;
   e.nb_dt = grid_capped(g.ncell, RED_BLOCKS);
-  stage_entry_sizes(e, n);
+  stage_entry_sizes(e, work);
   e.nb_prim = e.nb_ghost = e.nb_x = 0;
   for (int D = 0; D < 3; ++D) e.yz_nbx[D] = e.yz_nby[D] = e.yz_ntot[D] = 0;
   e.fu_nbx = e.fu_nby = e.fu_ntot = 0;

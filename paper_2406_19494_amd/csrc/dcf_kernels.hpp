@@ -56,7 +56,10 @@ bool line_resident(const Dev &g);
 hipError_t launch_line(const Dev &g, const LineArgs &A, hipStream_t st);
 
 struct BatchEntry;
-void stage_entry_sizes(BatchEntry &e, int n);
+// A 3D solve's plane-tiles of one-launch stages (0: other solves), and the sizes
+// of a batch member's stage launch among members of `work` plane-tiles in all.
+unsigned long stage_work(const Dev &g);
+void stage_entry_sizes(BatchEntry &e, unsigned long work);
 // The three stages of every solve of a batch, one launch each (cfl > 0: the
 // first one also reduces each solve's CFL partials).
 hipError_t launch_batch_stages(const BatchEntry *tab_dev, const BatchEntry *tab_host, int n,
@@ -81,10 +84,12 @@ struct BatchEntry {
   // one-launch stage: its workgroups (0: the split kernels instead), tiles along
   // x, and in 3D the division of the planes
   unsigned st_tiles, st_nbx, st_len, st_nch;
+  unsigned st_first;  // workgroups of the members before it in the table
 };
 
-// Fills the per-kernel workgroup counts of an entry of a batch of n (host side).
-void batch_entry_sizes(BatchEntry &e, int n);
+// Fills the per-kernel workgroup counts of an entry of a batch whose 3D members
+// have `work` plane-tiles in all (host side).
+void batch_entry_sizes(BatchEntry &e, unsigned long work);
 // One TVD-RK3 step of every solve in the table (tab_dev: device copy of
 // tab_host), optionally preceded by the CFL step (cfl > 0).  All entries
 // share ndim and the viscous flag and carry no source term.

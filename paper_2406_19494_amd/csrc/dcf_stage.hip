@@ -1269,17 +1269,33 @@ __device__ __forceinline__ StageArgs batch_args(const BatchEntry &e, int stage, 
   return A;
 }
 
+// The member of this workgroup: the last that starts at or before it.  (Launches
+// are packed: a workgroup without a tile would still take its place, in 3D a
+// whole CU's LDS, and the others would be dealt unevenly.  Eight boxes of 12^3
+// to 18^3: 65 us a step, 105 with every member's workgroups filled up to the
+// largest.)
+__device__ __forceinline__ const BatchEntry &batch_member(const BatchEntry *tab, int n) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (tab[mid].st_first <= blockIdx.x) lo = mid;
+    else hi = mid - 1;
+  }
+  return tab[lo];
+}
+
 // The batch takes 16 x 16 tiles for every member (8 boundary layers of 256 x 64
 // to 384 x 96: 79.8 us per step, 81.7 with 12 x 8): its members fill the chip
 // together.
 template <bool VISC>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-kb_stage2(const BatchEntry *tab, int stage, double cfl) {
+kb_stage2(const BatchEntry *tab, int n, int stage, double cfl) {
   __shared__ double lds[Tile2<VISC, SCHEME_WENO5, false>::SIZE];
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.st_tiles) return;
+  const BatchEntry &e = batch_member(tab, n);
+  const unsigned wg = blockIdx.x - e.st_first;
+  if (wg >= e.st_tiles) return;
   const StageArgs A = batch_args(e, stage, cfl);
-  stage2_tile<VISC, SCHEME_WENO5, false>(e.g, A, blockIdx.x, e.st_nbx, lds);
+  stage2_tile<VISC, SCHEME_WENO5, false>(e.g, A, wg, e.st_nbx, lds);
 }
 
 // 1D members: lines short enough are stepped whole by one workgroup each, the
@@ -1303,36 +1319,49 @@ __global__ void __launch_bounds__(1024) kb_line(const BatchEntry *tab, double cf
   line_steps<VISC, SCHEME_WENO5, 1024>(e.g, A, lds);
 }
 template <bool VISC>
-__global__ void __launch_bounds__(256) kb_stage1(const BatchEntry *tab, int stage, double cfl) {
+__global__ void __launch_bounds__(256) kb_stage1(const BatchEntry *tab, int n, int stage,
+                                                 double cfl) {
   __shared__ double lds[Line1<VISC>::NP * 261 + 3 * 256];
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.st_tiles) return;
+  const BatchEntry &e = batch_member(tab, n);
+  const unsigned wg = blockIdx.x - e.st_first;
+  if (wg >= e.st_tiles) return;
   const StageArgs A = batch_args(e, stage, cfl);
-  stage1_tile<VISC, SCHEME_WENO5>(e.g, A, blockIdx.x, lds);
+  stage1_tile<VISC, SCHEME_WENO5>(e.g, A, wg, lds);
 }
 
 // 3D members whose stages run as one launch; each viscosity law has its kernel,
 // a workgroup of another member's law returns.
 template <int LAW>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
-kb_stage3(const BatchEntry *tab, int stage, double cfl) {
+kb_stage3(const BatchEntry *tab, int n, int stage, double cfl) {
   __shared__ double lds[Col3<LAW != VISC_NONE>::SIZE];
-  const BatchEntry &e = tab[blockIdx.y];
-  if (blockIdx.x >= e.st_tiles || e.g.visc != LAW) return;
+  const BatchEntry &e = batch_member(tab, n);
+  const unsigned wg = blockIdx.x - e.st_first;
+  if (wg >= e.st_tiles || e.g.visc != LAW) return;
   const StageArgs A = batch_args(e, stage, cfl);
   const Split3 s = {e.st_nbx, e.st_len, e.st_nch, e.st_tiles};
   unsigned long r0, r1;
-  split_range(e.g, s, blockIdx.x, r0, r1);
-  stage3_range<LAW, SCHEME_WENO5>(e.g, A, blockIdx.x, r0, r1, s.nbx, lds);
+  split_range(e.g, s, wg, r0, r1);
+  stage3_range<LAW, SCHEME_WENO5>(e.g, A, wg, r0, r1, s.nbx, lds);
 }
 
-void stage_entry_sizes(BatchEntry &e, int n) {
+unsigned long stage_work(const Dev &g) {
+  if (!stage3_takes(g)) return 0;
+  return (unsigned long)tiles_along(g.n[0], Col3<true>::TX) * tiles_along(g.n[1], Col3<true>::TY) *
+         (unsigned long)g.n[2];
+}
+
+// (3D: the 256 CUs are shared in proportion to the members' plane-tiles, so that
+// members of different sizes end together: five Taylor-Green boxes of 22 x 29 x 31
+// to 32 x 43 x 45: 150 us a step, 220 with equal shares.)
+void stage_entry_sizes(BatchEntry &e, unsigned long work) {
   e.st_tiles = e.st_nbx = e.st_len = e.st_nch = 0;
   if (!stage_fused(e.g)) return;
   if (e.g.ndim == 1) {
     e.st_tiles = line_resident(e.g) ? 0u : stage_tiles(e.g);
   } else if (e.g.ndim == 3) {
-    const Split3 s = stage3_split(e.g, std::max(1u, 256u / (unsigned)n));
+    const unsigned share = (unsigned)(256ul * stage_work(e.g) / work);
+    const Split3 s = stage3_split(e.g, std::max(1u, share));
     e.st_tiles = s.groups;
     e.st_nbx = s.nbx;
     e.st_len = s.len;
@@ -1345,13 +1374,10 @@ void stage_entry_sizes(BatchEntry &e, int n) {
 
 hipError_t launch_batch_stages(const BatchEntry *tab, const BatchEntry *h, int n, double cfl,
                                hipStream_t st) {
-  unsigned nt = 0;
-  bool law[3] = {false, false, false};
-  for (int i = 0; i < n; ++i) {
-    nt = std::max(nt, h[i].st_tiles);
-    if (h[i].st_tiles) law[h[i].g.visc] = true;
-  }
-  const dim3 grid(nt, (unsigned)n);
+  bool any = false, law[3] = {false, false, false};
+  for (int i = 0; i < n; ++i)
+    if (h[i].st_tiles) any = law[h[i].g.visc] = true;
+  const unsigned all = h[n - 1].st_first + h[n - 1].st_tiles;
   const bool v = h[0].g.visc != VISC_NONE;
   if (h[0].g.ndim == 1) {
     bool lines = false;
@@ -1360,22 +1386,23 @@ hipError_t launch_batch_stages(const BatchEntry *tab, const BatchEntry *h, int n
       if (v) kb_line<true><<<(unsigned)n, 1024, 0, st>>>(tab, cfl);
       else kb_line<false><<<(unsigned)n, 1024, 0, st>>>(tab, cfl);
     }
-    for (int stage = 0; stage < 3 && nt; ++stage) {
-      if (v) kb_stage1<true><<<grid, 256, 0, st>>>(tab, stage, cfl);
-      else kb_stage1<false><<<grid, 256, 0, st>>>(tab, stage, cfl);
+    for (int stage = 0; stage < 3 && any; ++stage) {
+      if (v) kb_stage1<true><<<all, 256, 0, st>>>(tab, n, stage, cfl);
+      else kb_stage1<false><<<all, 256, 0, st>>>(tab, n, stage, cfl);
     }
     return hipGetLastError();
   }
-  if (!nt) return hipSuccess;
+  if (!any) return hipSuccess;
   for (int stage = 0; stage < 3; ++stage) {
     if (h[0].g.ndim == 2) {
-      if (v) kb_stage2<true><<<grid, 512, 0, st>>>(tab, stage, cfl);
-      else kb_stage2<false><<<grid, 512, 0, st>>>(tab, stage, cfl);
+      if (v) kb_stage2<true><<<all, 512, 0, st>>>(tab, n, stage, cfl);
+      else kb_stage2<false><<<all, 512, 0, st>>>(tab, n, stage, cfl);
       continue;
     }
-    if (law[VISC_NONE]) kb_stage3<VISC_NONE><<<grid, 512, 0, st>>>(tab, stage, cfl);
-    if (law[VISC_POWER]) kb_stage3<VISC_POWER><<<grid, 512, 0, st>>>(tab, stage, cfl);
-    if (law[VISC_SUTHERLAND]) kb_stage3<VISC_SUTHERLAND><<<grid, 512, 0, st>>>(tab, stage, cfl);
+    if (law[VISC_NONE]) kb_stage3<VISC_NONE><<<all, 512, 0, st>>>(tab, n, stage, cfl);
+    if (law[VISC_POWER]) kb_stage3<VISC_POWER><<<all, 512, 0, st>>>(tab, n, stage, cfl);
+    if (law[VISC_SUTHERLAND])
+      kb_stage3<VISC_SUTHERLAND><<<all, 512, 0, st>>>(tab, n, stage, cfl);
   }
   return hipGetLastError();
 }
