@@ -523,12 +523,15 @@ struct PendingDt {
 // With pend (box_ready only) the first ghost fill also reduces the previous
 // step's partial maxima into dt, before any stage reads it.  With nstages = 2
 // only the stage states U1 and U2 are made (U is not written): the step's
-// inner states exactly as the full step makes them.
+// inner states exactly as the full step makes them.  With Un (one-launch
+// stages but the resident line) the step starts from that state and U is only
+// written.
 static dcf_status rk3_stages(dcf_ctx *c, double *U, const double *dt, hipStream_t st,
                              double *U1 = nullptr, double *U2 = nullptr,
                              double *dtpart = nullptr, int base = 0, bool box_ready = false,
                              bool write_next = false, const PendingDt *pend = nullptr,
-                             int nstages = 3, const BoxOut *boxes = nullptr) {
+                             int nstages = 3, const BoxOut *boxes = nullptr,
+                             const double *Un = nullptr) {
   Dev &g = c->g;
   if (line_resident(g) && !dtpart) {
     LineArgs A = {};
@@ -544,13 +547,14 @@ static dcf_status rk3_stages(dcf_ctx *c, double *U, const double *dt, hipStream_
   if (!U1) U1 = c->U1;
   if (!U2) U2 = c->U2;
   if (stage_fused(g)) {
-    const double *in[3] = {U, U1, U2};
+    if (!Un) Un = U;
+    const double *in[3] = {Un, U1, U2};
     double *out[3] = {U1, U2, U};
     const double a[3] = {0.0, 0.75, 1.0 / 3.0}, b[3] = {1.0, 0.25, 2.0 / 3.0};
     Probe &pr = c->probe;
     for (int k = 0; k < nstages; ++k) {
       StageArgs A = {};
-      A.Un = U;
+      A.Un = Un;
       A.Uin = in[k];
       A.Uout = out[k];
       A.dt = dt;
@@ -974,25 +978,29 @@ static dcf_status segment_step(dcf_ctx *c, int k, hipStream_t st) {
   Dev &g = c->g;
   const long M = (long)g.nv * g.ncell;
   double *Ua = c->seg + (long)k * M, *Ub = Ua + M;
-  DCF_HIP(launch_copy(Ub, Ua, M, st));
   double *S1 = c->sst + (long)(2 * k) * M, *S2 = S1 + M;
-  if (stage_fused(g) && c->boxc && g.source == SRC_NONE && g.ndim != 2) {
+  if (stage_fused(g)) {
+    // from Ua to Ub: only the resident line steps in place, from a copy
+    const bool line = line_resident(g);
+    if (line) DCF_HIP(launch_copy(Ub, Ua, M, st));
+    const bool cached = c->boxc && g.source == SRC_NONE;
+    BoxOut boxes[3];
+    if (cached)
+      for (int s = 0; s < 3; ++s) {
+        const Dev gs = stage_box(c, k, s);
+        for (int q = 0; q < NQ; ++q) boxes[s].Q[q] = gs.Q[q];
+      }
+    const dcf_status e = rk3_stages(c, Ub, gr.dt, st, S1, S2, nullptr, 0, false, false, nullptr, 3,
+                                    cached && g.ndim == 2 ? boxes : nullptr,
+                                    line ? nullptr : Ua);
+    if (e || !cached || g.ndim == 2) return e;
     // the 1D and 3D stage kernels keep no box: each stage's is filled from its
     // input, as the reverse step would fill it
-    const dcf_status e = rk3_stages(c, Ub, gr.dt, st, S1, S2);
-    if (e) return e;
     const double *in[3] = {Ua, S1, S2};
     for (int s = 0; s < 3; ++s) DCF_HIP(launch_prim_halo(stage_box(c, k, s), in[s], st));
     return DCF_OK;
   }
-  if (stage_fused(g) && c->boxc && g.source == SRC_NONE) {
-    BoxOut boxes[3];
-    for (int s = 0; s < 3; ++s) {
-      const Dev gs = stage_box(c, k, s);
-      for (int q = 0; q < NQ; ++q) boxes[s].Q[q] = gs.Q[q];
-    }
-    return rk3_stages(c, Ub, gr.dt, st, S1, S2, nullptr, 0, false, false, nullptr, 3, boxes);
-  }
+  DCF_HIP(launch_copy(Ub, Ua, M, st));
   if (c->boxc && g.source == SRC_NONE) {  // the same three stages, keeping each stage's boxes
     const double *in[3] = {Ub, S1, S2};
     double *out[3] = {S1, S2, Ub};
