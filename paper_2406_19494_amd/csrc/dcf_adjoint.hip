@@ -129,7 +129,8 @@ __device__ __forceinline__ void weno5_vjp(double v0, double v1, double v2, doubl
 }
 
 // Reverse of the HLLC flux (same branch choices as the forward: Davis wave
-// speeds with the left candidate kept on ties, 0 <= S selects the left side).
+// speeds with the left candidate kept on ties and a NaN one left out, the upwind
+// side of a supersonic face, else 0 <= S* selects the left side).
 __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, double gm1i,
                          const double *Fb, double *qLb, double *qRb) {
   double rL = qL[0], uL = qL[1], vL = qL[2], wL = qL[3], pL = qL[4];
@@ -142,16 +143,16 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   double cL = sound_speed(gamma, rL, pL, yL);
   double cR = sound_speed(gamma, rR, pR, yR);
   double aL = uL - cL, bL = uR - cR;
-  const bool selL = bL < aL;
-  double SL = selL ? bL : aL;
+  double SL = fmin(aL, bL);
+  const bool selL = SL != aL;
   double aR = uL + cL, bR = uR + cR;
-  const bool selR = bR > aR;
-  double SR = selR ? bR : aR;
+  double SR = fmax(aR, bR);
+  const bool selR = SR != aR;
   double mL = rL * (SL - uL), mR = rR * (SR - uR);
   double Nn = pR - pL + uL * mL - uR * mR, Dd = mL - mR;
   const double iDd = rcp_nr(Dd);
   double Ss = Nn * iDd;
-  const bool left = (0.0 <= Ss);
+  const bool left = 0.0 <= fmin(fmax(Ss, SL), SR);
   double r = left ? rL : rR, u = left ? uL : uR, v = left ? vL : vR, w = left ? wL : wR;
   double p = left ? pL : pR, E = left ? EL : ER, SK = left ? SL : SR, m = left ? mL : mR;
   double inv = rcp_nr(SK - Ss);
@@ -224,11 +225,13 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   qRb[1] += tLR + tRR;
   const double cLb = tRL - tLL, cRb = tRR - tLR;
   // c = sqrt(gamma p / rho): dc/dp = gamma / (2 rho c) = gamma y / 2 and
-  // dc/drho = -c / (2 rho) = -c^2 y / 2
+  // dc/drho = -c / (2 rho) = -c^2 y / 2 (a side whose c is NaN set no speed)
+  yL = fmax(yL, 0.0);
+  yR = fmax(yR, 0.0);
   qLb[4] += cLb * (0.5 * gamma) * yL;
-  qLb[0] -= cLb * (0.5 * cL * cL) * yL;
+  qLb[0] -= cLb * (0.5 * fmax(cL * cL, 0.0)) * yL;
   qRb[4] += cRb * (0.5 * gamma) * yR;
-  qRb[0] -= cRb * (0.5 * cR * cR) * yR;
+  qRb[0] -= cRb * (0.5 * fmax(cR * cR, 0.0)) * yR;
 }
 
 // Flux adjoint at face f of direction D from the stage-output adjoint Wb:

@@ -290,11 +290,13 @@ __device__ __forceinline__ void hllc(const double *qL, const double *qR, double 
   double SR = fmax(uL + cL, uR + cR);
   double mL = rL * (SL - uL), mR = rR * (SR - uR);
   double Ss = (pR - pL + uL * mL - uR * mR) * rcp_nr(mL - mR);
-  // 0 <= SL implies 0 <= S*, and SR < 0 implies S* < 0: on a supersonic face
-  // the selected side's wave term vanishes, F = F(U_K) (selections only: a
-  // branch would end the block in which this arithmetic and the
-  // reconstructions hide each other's latencies)
-  const bool left = (0.0 <= Ss);
+  // S* lies between SL and SR where both pressures are positive.  Where one is
+  // not, its sound speed is NaN, fmin and fmax leave that side out, and S* can
+  // lie on either side of 0: clamped, it selects the upwind side of a
+  // supersonic face all the same.  There the selected side's wave term vanishes,
+  // F = F(U_K) (selections only: a branch would end the block in which this
+  // arithmetic and the reconstructions hide each other's latencies).
+  const bool left = 0.0 <= fmin(fmax(Ss, SL), SR);
   const double SLm = fmin(SL, 0.0), SRp = fmax(SR, 0.0);
   double r = left ? rL : rR, u = left ? uL : uR, v = left ? vL : vR, w = left ? wL : wR;
   double p = left ? pL : pR, S = left ? SL : SR, m = left ? mL : mR;
