@@ -948,7 +948,7 @@ __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int
           tangential_gather<NDIM, 6u, ALL3>(g, A, pe, bidx(g, pe[0], pe[1], pe[2]), add);
           vsum += add[NDIM - 1];
         }
-      A.dpart[side * A.dcols + (long)(p[1] + 3) * g.n[0] + p[0]] = vsum;
+      A.dpart[(4 + side) * A.dcols + (long)(p[1] + 3) * g.n[0] + p[0]] = vsum;
     }
   }
 #pragma unroll
@@ -1048,7 +1048,7 @@ __device__ __forceinline__ void collect_ghosts(const Dev &g, const AdjBuffers &A
     const double *Qn = A.Qb[QU + d] + G0;
     const double vsum = Qn[0] + Qn[gs] + Qn[2 * gs];
     if (kind == BC_DISTURB) {
-      if (dJdK) A.dpart[side * A.dcols + (long)(bq + (t2 < d ? 3 : 0)) * g.n[t1] + a] = vsum;
+      if (dJdK) A.dpart[face * A.dcols + (long)(bq + (t2 < d ? 3 : 0)) * g.n[t1] + a] = vsum;
     } else if (face == g.pface && a >= g.pb && a < g.pe) {
       // v_g[d] = 2 sigma v_n - v_s[d], v_n = -K (p_w - p_inf)/p_inf
       const int kk = bq * (g.pe - g.pb) + (a - g.pb);
@@ -1278,7 +1278,7 @@ static hipError_t disturb_sums(const Dev &g, const AdjBuffers &A, int d, double 
   for (int side = 0; side < 2; ++side) {
     const int face = 2 * d + side;
     if (g.bck[face] != BC_DISTURB) continue;
-    k_disturb_sum<<<1, 256, 0, st>>>(g, A.dpart + side * A.dcols, disturb_cols(g, d), face,
+    k_disturb_sum<<<1, 256, 0, st>>>(g, A.dpart + face * A.dcols, disturb_cols(g, d), face,
                                      dJdK + g.doff[face]);
     DCF_TRY(hipGetLastError());
   }

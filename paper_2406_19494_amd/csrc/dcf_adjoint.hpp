@@ -22,7 +22,7 @@ struct AdjBuffers {
   double *src;      // body force of a stage: f, f-bar = sum Rb_rhou + Rb_E u
   double *spart;    // partial sums of f-bar, then of f
   double *dpart;    // normal-velocity ghost adjoints of the disturbance walls' columns, an
-                    // array per side
+                    // array per face (one launch fills those of every axis)
   long dcols;       // columns per array
   double *zero_begin;  // Qb and Gb are carved back to back: one clear (with the
                        // workspace) zeroes both
@@ -64,7 +64,7 @@ template <class Carver> void carve_adjoint(Carver &cv, const Dev &g, AdjBuffers 
     cols = n1 * n2 > cols ? n1 * n2 : cols;
   }
   a.dcols = cols;
-  a.dpart = cv.template take<double>(2 * cols);
+  a.dpart = cv.template take<double>(2 * g.ndim * cols);
   a.src = cv.template take<double>(4);
   a.spart = cv.template take<double>(2 * RED_BLOCKS);
 }

@@ -102,3 +102,62 @@ def test_both_3d_forms_dot_product(n, which):
     lhs = np.sum(lam * jv)
     rhs = np.sum(lu * v) + (np.sum(gK.cpu().numpy()[: s.nk] * vk) if s.nk else 0.0)
     assert abs(lhs - rhs) <= VJP_TOL * max(abs(lhs), np.sum(np.abs(lam * jv))), (lhs, rhs)
+
+
+# disturbance walls along two or three axes at once, each face with parameters of
+# its own: the faces of one side of every axis are reduced in the same launch
+SEVERAL = {
+    "xy_low_2d": ((7, 6, 1), (("disturb", "zerograd"), ("disturb", "wall"))),
+    "xy_2d": ((5, 9, 1), (D2, D2)),
+    "yz_low_3d": ((5, 6, 4), (P2, ("disturb", "wall"), ("disturb", "zerograd"))),
+    "yz_3d": ((4, 5, 6), (Z2, D2, D2)),
+    "xz_3d": ((6, 4, 5), (D2, W2, D2)),
+    "xyz_inviscid_3d": ((5, 4, 6), (D2, D2, D2), "none"),
+}
+
+
+def _several(n, bc, law="power"):
+    case = _case(n, bc, law)
+    case.dist_amp = (0.02, -0.03, 0.04, 0.05, -0.06, 0.07)
+    case.dist_kappa = (1.5, 0.7, 1.1, 2.3, 0.9, 1.9)
+    return case
+
+
+@pytest.mark.parametrize("which", list(SEVERAL))
+def test_disturbance_walls_on_several_axes(which):
+    print(f"[faces] {which}", flush=True)
+    case = _several(*SEVERAL[which])
+    o, s = Oracle(case), Solver(case, mode=1)
+    U = o.cons(W.random_smooth(case, seed=5, amp=0.1))
+    lam = np.random.default_rng(11).normal(size=U.shape)
+    dt = 1e-3
+    lu_or, lk_or = o.vjp_step(U, lam, dt)
+    gK = torch.zeros(s.nk, dtype=torch.float64, device="cuda")
+    lu = s.vjp_step(torch.as_tensor(U, device="cuda"),
+                    torch.full((1,), dt, dtype=torch.float64, device="cuda"),
+                    torch.as_tensor(lam, device="cuda"), dJdK=gK).cpu().numpy()
+    err = np.abs(lu - lu_or).max(axis=(1, 2, 3)) / np.abs(lu_or).max(axis=(1, 2, 3))
+    assert np.all(err <= VJP_TOL), err
+    gk = gK.cpu().numpy()
+    assert np.abs(gk - lk_or).max() <= VJP_TOL * np.abs(lk_or).max(), (gk, lk_or)
+
+
+def test_disturbance_walls_on_several_axes_per_direction_launches():
+    case = _several((64, 65, 64), (P2, D2, D2), "sutherland")
+    print(f"[3d forms] {case.n} disturb yz", flush=True)
+    o, s = Oracle(case), Solver(case, mode=1)
+    U = o.cons(W.random_smooth(case, seed=5, amp=0.1))
+    rng = np.random.default_rng(12)
+    lam = rng.normal(size=U.shape)
+    gK = torch.zeros(s.nk, dtype=torch.float64, device="cuda")
+    dt = 1e-3
+    s.vjp_step(torch.as_tensor(U, device="cuda"),
+               torch.full((1,), dt, dtype=torch.float64, device="cuda"),
+               torch.as_tensor(lam, device="cuda"), dJdK=gK)
+    gk = gK.cpu().numpy()
+    for i in range(s.nk):  # each parameter's derivative by itself
+        vk = np.zeros(s.nk)
+        vk[i] = 1.0
+        _, jv = o.jvp_step(U, np.zeros_like(U), dt, vk)
+        lhs = np.sum(lam * jv)
+        assert abs(lhs - gk[i]) <= VJP_TOL * np.sum(np.abs(lam * jv)), (i, lhs, gk[i])
