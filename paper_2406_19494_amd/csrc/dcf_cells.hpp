@@ -97,7 +97,7 @@ struct FromBox {
       q[QT] = g.Q[QT][sb];
       mu = g.Q[QMU][sb];
     } else {
-      q[QT] = q[QP] / (q[QR] * g.R);
+      q[QT] = q[QP] * rcp_nr(q[QR]) * g.iR;  // as prim_of_state, to the bit
       mu = -1.0;
     }
   }
