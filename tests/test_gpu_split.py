@@ -43,3 +43,53 @@ def test_chained_steps_equal_single_steps(which):
         s.step_cfl(V, dv, cfl=0.3)
     assert s.flags() == 0
     assert torch.equal(U, V) and torch.equal(dt, dv)
+
+
+# one batch of one-launch members under two viscosity laws and of members with
+# split launches; the order decides where the packed stage launch finds members
+# without workgroups of their own
+def _member(kind, k):
+    return {"power": lambda: _case((7 + k, 9, 5), (P2, W2, Z2)),
+            "suth": lambda: _case((16, 5 + k, 8), (W2, P2, P2), "sutherland"),
+            "disturb": lambda: _case((6 + k, 8, 7), (P2, W2, D2)),
+            "dirichlet": lambda: _dirichlet((9, 6 + k, 5))}[kind]()
+
+
+def _dirichlet(n):
+    case = _case(n, (("dirichlet", "zerograd"), W2, P2), "sutherland")
+    P = np.zeros((5, n[2], n[1]))
+    P[0], P[1], P[4] = 1.0, 0.1, 1.3
+    case.dirichlet[0] = P
+    return case
+
+
+ORDERS = {
+    "split_first": ("disturb", "power", "suth", "power"),
+    "split_middle": ("suth", "power", "dirichlet", "disturb", "suth"),
+    "split_last": ("power", "suth", "disturb", "dirichlet"),
+    "split_around": ("dirichlet", "power", "disturb"),
+    "split_alone": ("disturb", "dirichlet"),
+    "two_laws": ("suth", "power", "suth"),
+}
+
+
+@pytest.mark.parametrize("cfl", [0.3, None], ids=["cfl", "fixed"])
+@pytest.mark.parametrize("order", list(ORDERS))
+def test_mixed_batch_equals_single_steps(order, cfl):
+    print(f"[split] batch {order} {cfl}", flush=True)
+    cases = [_member(kind, k) for k, kind in enumerate(ORDERS[order])]
+    one, many = [Solver(c) for c in cases], [Solver(c) for c in cases]
+    Us = [s.init_state(W.random_smooth(c, seed=8, amp=0.1)) for s, c in zip(one, cases)]
+    dts = [s.compute_dt(U, cfl=0.3) for s, U in zip(one, Us)]
+    Vs, dvs = [U.clone() for U in Us], [d.clone() for d in dts]
+    bs = BatchStepper()
+    for _ in range(3):
+        for s, U, d in zip(one, Us, dts):
+            if cfl:
+                s.compute_dt(U, cfl=cfl, out=d)
+            s.step(U, d)
+        bs.step(many, Vs, dvs, cfl=cfl)
+    torch.cuda.synchronize()
+    for k, (U, V, d, e, s) in enumerate(zip(Us, Vs, dts, dvs, many)):
+        assert torch.equal(U, V) and torch.equal(d, e), (order, k)
+        assert s.flags() == 0
