@@ -110,3 +110,22 @@ def test_kept_stage_boxes_give_the_rebuilt_boxes_gradient(which):
     assert torch.any(out[0][2] != 0.0)
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# Chained calls at the limits of their launches: more partial maxima than a stage's
+# workgroups reduce themselves (more than 2048 tiles), and more steps of a short
+# line than one launch takes (2048).
+@pytest.mark.parametrize("n,nsteps", [((720, 736, 1), 3), ((40, 1, 1), 2051)],
+                         ids=["2070_tiles", "2051_steps"])
+def test_long_chains_equal_single_steps(n, nsteps):
+    print(f"[stage] chain {n} {nsteps}", flush=True)
+    case = _case(n, (P2, W2)[:2 if n[1] > 1 else 1])
+    s = Solver(case)
+    U = s.init_state(W.random_smooth(case, seed=5, amp=0.1))
+    dt = s.compute_dt(U, cfl=0.4)
+    V, dv = U.clone(), dt.clone()
+    s.steps_cfl(U, dt, nsteps, cfl=0.4)
+    for _ in range(nsteps):
+        s.step_cfl(V, dv, cfl=0.4)
+    assert s.flags() == 0
+    assert torch.equal(U, V) and torch.equal(dt, dv)
