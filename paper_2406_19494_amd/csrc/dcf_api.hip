@@ -664,7 +664,7 @@ dcf_status dcf_rhs(dcf_ctx *c, const double *U, double *R, void *stream) {
   // overlap, the fluxes are computed in launches of their own first
   const size_t bytes = sizeof(double) * (size_t)c->g.nv * c->g.ncell;
   const uintptr_t u = (uintptr_t)U, r = (uintptr_t)R;
-  if (stage_fused(c->g) && (u + bytes <= r || r + bytes <= u)) {
+  if (rhs_fused(c->g) && (u + bytes <= r || r + bytes <= u)) {
     StageArgs A = {};
     A.Un = A.Uin = U;
     A.Rout = R;
@@ -850,7 +850,7 @@ dcf_status dcf_rk3_steps_cfl(dcf_ctx *c, double *U, double *dt, int nsteps, doub
   if (!(dt_max > 0.0)) dt_max = 1.0e300;
   hipStream_t st = (hipStream_t)stream;
   if (line_resident(c->g)) return line_steps_cfl(c, U, dt, nsteps, cfl, dt_max, dt, st);
-  const bool fused = stage_fused(c->g) || fused_stages(c);
+  const bool one_launch = stage_fused(c->g), fused = one_launch || fused_stages(c);
   const unsigned nparts = dt_parts(c);
   const PendingDt pend{(int)nparts, cfl, dt_max, dt};
   bool pending = false;
@@ -864,7 +864,7 @@ dcf_status dcf_rk3_steps_cfl(dcf_ctx *c, double *U, double *dt, int nsteps, doub
       return s;
     // a stage launch's workgroups reduce the partial maxima themselves, each
     // of them: only while they are few
-    pending = chained && (!stage_fused(c->g) || nparts <= 2048);
+    pending = chained && (!one_launch || nparts <= 2048);
     if (!pending) DCF_HIP(launch_dt_final(c->dtpart, (int)nparts, cfl, dt_max, dt, st));
   }
   return DCF_OK;

@@ -26,9 +26,10 @@ struct StageArgs {
   double *dt_out;
 };
 
-// Whether a grid's stages run as one launch each, the workgroups of that launch
-// (the length of dtpart), and the launch.
+// Whether a grid's stages run as one launch each (and a right-hand side by
+// itself), the workgroups of that launch (the length of dtpart), and the launch.
 bool stage_fused(const Dev &g);
+bool rhs_fused(const Dev &g);
 unsigned stage_tiles(const Dev &g);
 hipError_t launch_stage(const Dev &g, const StageArgs &A, hipStream_t st);
 // The body force of a stage from its state A.Uin alone, where that is built (3D

@@ -376,12 +376,14 @@ __device__ __forceinline__ void stage2_tile(const Dev &g, const StageArgs &A, un
   }
 }
 
-// Both schemes at 4 waves per SIMD: a face's flux takes ~125 VGPRs and the
-// stage waits on its dependent chains; at 5 waves (96 VGPRs) it is slower by
-// a quarter (1024 x 256: 29.3 against 23.2 us).
+// 4 waves per SIMD: a face's flux takes ~125 VGPRs and the stage waits on its
+// dependent chains; at 5 waves (96 VGPRs) it is slower by a quarter (1024 x 256:
+// 29.3 against 23.2 us).  TENO6-A takes 144: in 16 x 16 tiles 128 with 14 spilled
+// let a CU hold two workgroups instead of one (512^2: 134 against 149 us a step),
+// the small tiles keep the compiler's choice (256^2: 45 against 47).
 template <bool VISC, int SCH, bool SMALL>
 __global__ void __launch_bounds__(SMALL ? 256 : 512)
-__attribute__((amdgpu_waves_per_eu(SCH == SCHEME_WENO5 ? 4 : 1)))
+__attribute__((amdgpu_waves_per_eu(SCH == SCHEME_WENO5 || !SMALL ? 4 : 1)))
 k_stage2(Dev g, StageArgs A, unsigned nbx) {
   __shared__ double lds[Tile2<VISC, SCH, SMALL>::SIZE];
   const unsigned tile = xcd_remap(blockIdx.x, gridDim.x);
@@ -1147,7 +1149,25 @@ static Split3 stage3_split(const Dev &g, unsigned slots = 256) {
   return s;
 }
 
-bool stage_fused(const Dev &g) { return g.ndim <= 2 || stage3_takes(g); }
+// Large 2D grids with TENO6-A take the split launches: bound by FP64 issue, they
+// run at 5 to 6 wavefronts per SIMD there and the stage's tiles at 4, while the
+// launches they take more matter less and less (512^2: 134 us a step in one
+// launch a stage, 147 split; 540^2: 159 and 156; 700^2: 255 and 225; 2048^2: 1952
+// and 1628; a right-hand side alone, one launch for three, 700^2: 80 and 82,
+// 1024^2: 159 and 154), and earlier with the body force, which the one launch
+// needs a halo fill and a reduction for (256^2: 116 and 114, 400^2: 186 and 153).
+static bool stage2_wins(const Dev &g, long most, long most_force) {
+  return g.scheme != SCHEME_TENO6A || g.ncell <= (g.source == SRC_NONE ? most : most_force);
+}
+
+bool stage_fused(const Dev &g) {
+  if (g.ndim == 3) return stage3_takes(g);
+  return g.ndim == 1 || stage2_wins(g, 300000, 100000);
+}
+bool rhs_fused(const Dev &g) {
+  if (g.ndim == 3) return stage3_takes(g);
+  return g.ndim == 1 || stage2_wins(g, 800000, 150000);
+}
 unsigned stage_tiles(const Dev &g) {
   if (g.ndim == 1) return tiles_along(g.n[0], 255);
   if (g.ndim == 3) return stage3_split(g).groups;
@@ -1192,7 +1212,7 @@ hipError_t launch_stage_force(const Dev &g, StageArgs &A, double *part, hipStrea
 }
 
 hipError_t launch_stage(const Dev &g, const StageArgs &A, hipStream_t st) {
-  if (!stage_fused(g)) return hipErrorInvalidValue;
+  if (g.ndim == 3 && !stage3_takes(g)) return hipErrorInvalidValue;
   if (g.ndim == 1) {
     const unsigned n = tiles_along(g.n[0], 255);
     const bool v = g.visc != VISC_NONE;

@@ -129,3 +129,32 @@ def test_long_chains_equal_single_steps(n, nsteps):
         s.step_cfl(V, dv, cfl=0.4)
     assert s.flags() == 0
     assert torch.equal(U, V) and torch.equal(dt, dv)
+
+
+# Large 2D grids with TENO6-A take the split launches.  (Against the oracle the
+# scheme's cut-off would fall either way on rounding somewhere in so many faces.)
+# A field that repeats along x takes the same cut-offs in both routes: its
+# right-hand side and step are its period's, which one launch computes, to
+# rounding.
+@pytest.mark.parametrize("period,repeats,law,source", [
+    ((30, 520, 1), 20, "power", "none"), ((24, 520, 1), 25, "none", "none"),
+    ((30, 520, 1), 20, "power", "massflux"), ((31, 896, 1), 29, "power", "none")],
+    ids=["viscous", "inviscid", "force", "rhs"])
+def test_large_teno_grids_repeat_their_period(period, repeats, law, source):
+    print(f"[stage] teno {period} x {repeats}", flush=True)
+    small = _case(period, (P2, W2), law, "teno6a", source)
+    large = _case((period[0] * repeats, *period[1:]), (P2, W2), law, "teno6a", source)
+    a, b = Solver(small), Solver(large)
+    U = a.init_state(W.random_smooth(small, seed=5, amp=0.1))
+    V = U.repeat(1, 1, 1, repeats)
+    scale = flux_scale(small, U.cpu().numpy())
+    err = rel_err_per_var(b.rhs(V).cpu().numpy(), a.rhs(U).repeat(1, 1, 1, repeats).cpu().numpy(),
+                          scale)
+    assert np.all(err <= RHS_TOL), err
+    dt = a.compute_dt(U, cfl=0.5)
+    a.step(U, dt)
+    b.step(V, dt)
+    ref = U.repeat(1, 1, 1, repeats).cpu().numpy()
+    err = rel_err_per_var(V.cpu().numpy(), ref, np.full(small.nv, np.abs(ref).max()))
+    assert np.all(err <= STEP_TOL / 3), err
+    assert a.flags() == 0 and b.flags() == 0
