@@ -176,7 +176,8 @@ def stage_kernel(case):
     (ghost cells, fluxes and update; short 1D lines run all steps of a call in
     one), or None where a stage is split into the launches of step_kernel_ids:
     3D grids with the TENO6-A scheme or with porous, disturbance or Dirichlet
-    faces."""
+    faces.  (Of the grids here: the library also splits 3D grids thin along y
+    and large 2D ones with TENO6-A.)"""
     if case.ndim == 1:
         return "k_line" if case.n[0] < 1024 and case.source == "none" else "k_stage1"
     if case.ndim == 2:

@@ -342,9 +342,11 @@ dcf_status dcf_gradient(dcf_ctx *ctx, const double *U0_dev, int nsteps, const do
  * launch, 8 the ghost cells of the primitive box alone (stages 2 and 3 of a
  * split step: the previous stage's update wrote the interior).  These are the
  * kernels of a split stage, which dcf_rk3_step runs on 3D grids with the
- * TENO6-A scheme or with porous, disturbance or Dirichlet faces; other grids
- * run each stage in one launch, which these kernels do not time (the probe
- * below does).  5 and 9 are not used: the flux kernels compute the
+ * TENO6-A scheme or with porous, disturbance or Dirichlet faces, on 3D grids
+ * that fill the one-launch kernel's tiles badly (thin along y) or carry the body
+ * force on few cells, and on 2D grids of more than 300000 cells with TENO6-A;
+ * other grids run each stage in one launch, which these kernels do not time
+ * (the probe below does).  5 and 9 are not used: the flux kernels compute the
  * cell-centred velocity derivatives while staging their tiles (no separate
  * derivative launch).  The inputs it needs (primitive box, face fluxes) are
  * computed from U once before timing.  DCF_EINVAL for an unknown `which` or

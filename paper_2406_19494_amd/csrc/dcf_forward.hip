@@ -1419,10 +1419,10 @@ void batch_entry_sizes(BatchEntry &e, unsigned long work) {
   e.fu_ntot = e.fu_nbx * e.fu_nby * g.n[1];
 }
 
-// The 3D members whose stages do not run as one launch (their faces need more
-// of the halo chain): the split kernels' sequence.
+// The 3D members whose stages do not run as one launch: the split kernels'
+// sequence over n members.
 template <bool VISC>
-static hipError_t batch_split_stages(const BatchEntry *tab, const BatchEntry *h, int n,
+static hipError_t batch_split_run(const BatchEntry *tab, const BatchEntry *h, int n,
                                      hipStream_t st) {
   unsigned mp = 0, mh = 0, mx = 0, my = 0, mf = 0;
   int nw = 0;
@@ -1444,6 +1444,47 @@ static hipError_t batch_split_stages(const BatchEntry *tab, const BatchEntry *h,
     kb_flux_update<3, VISC><<<dim3(mf, ny), 256, 0, st>>>(tab, stage);
   }
   return hipGetLastError();
+}
+
+// One member's step in launches of its own, as dcf_rk3_step makes them.
+static hipError_t split_step(const BatchEntry &e, hipStream_t st) {
+  hipError_t err = hipSuccess;
+  for (int stage = 0; stage < 3 && err == hipSuccess; ++stage) {
+    const Dev &g = (stage & 1) ? e.gb : e.g, &gn = (stage & 1) ? e.g : e.gb;
+    const double a = stage == 0 ? 0.0 : (stage == 1 ? 0.75 : 1.0 / 3.0);
+    const double b = stage == 0 ? 1.0 : (stage == 1 ? 0.25 : 2.0 / 3.0);
+    const double *in = stage == 0 ? e.U : (stage == 1 ? e.U1 : e.U2);
+    double *out = stage == 0 ? e.U1 : (stage == 1 ? e.U2 : e.U);
+    BoxOut next;
+    for (int q = 0; q < NQ && stage < 2; ++q) next.Q[q] = gn.Q[q];
+    err = stage == 0 ? launch_prim_halo(g, in, st) : launch_prim_ghost(g, st);
+    if (err == hipSuccess)
+      err = launch_fluxes_update(g, e.U, in, out, e.dt, a, b, nullptr, st, next, nullptr, nullptr,
+                                 nullptr);
+  }
+  return err;
+}
+
+// Members of more than 2^17 cells take launches of their own: they fill the chip
+// alone, and in shared launches the members' arrays push each other out of the
+// caches between one kernel and the next (four of 128 x 17 x 128: 684 us a step,
+// 812 shared; of 256 x 3 x 256: 683 and 807; smaller ones fill the chip together:
+// 33 x 17 x 129: 294 shared, four single steps 356).
+template <bool VISC>
+static hipError_t batch_split_stages(const BatchEntry *tab, const BatchEntry *h, int n,
+                                     hipStream_t st) {
+  auto alone = [&](int i) { return h[i].fu_ntot && h[i].g.ncell > 1L << 17; };
+  hipError_t e = hipSuccess;
+  for (int i = 0, m; i < n && e == hipSuccess; i = m) {
+    m = i + 1;
+    if (alone(i)) {
+      e = split_step(h[i], st);
+    } else {
+      while (m < n && !alone(m)) ++m;
+      e = batch_split_run<VISC>(tab + i, h + i, m - i, st);
+    }
+  }
+  return e;
 }
 
 hipError_t launch_batch_step(const BatchEntry *tab, const BatchEntry *h, int n, double cfl,

@@ -1123,11 +1123,18 @@ static bool stage3_takes(const Dev &g) {
 // chunks per tile 50 us, ranges of 5 planes 54 us; 192 x 128 x 128: ranges of 52
 // planes 353 us, 7 chunks per tile 420 us.)
 // (slots: the workgroups in flight, a share of 256 for a member of a batch.)
-static Split3 stage3_split(const Dev &g, unsigned slots = 256) {
+// (plane_times: the cost of the division found, in planes.)
+static Split3 stage3_split(const Dev &g, unsigned slots = 256, double *plane_times = nullptr) {
   const unsigned nz = g.n[2];
   const unsigned tiles = tiles_along(g.n[0], Col3<true>::TX) * tiles_along(g.n[1], Col3<true>::TY);
   const unsigned long total = (unsigned long)tiles * nz;
   Split3 s = {tiles_along(g.n[0], Col3<true>::TX), 0u, 1u, 0u};
+  if (total <= slots) {  // a plane each
+    s.nch = nz;
+    s.groups = (unsigned)total;
+    if (plane_times) *plane_times = 2.8;
+    return s;
+  }
   double cost = 1e300;
   // (more rounds than a few only add starts)
   const unsigned cmax = 8u * slots / tiles + 8u;
@@ -1143,10 +1150,38 @@ static Split3 stage3_split(const Dev &g, unsigned slots = 256) {
   const unsigned len = (unsigned)((total + slots - 1) / slots);
   const unsigned runs = len % nz == 0 ? len / nz : (len - 1) / nz + 2;
   if (len + 1.8 * runs < cost) {
+    cost = len + 1.8 * runs;
     s.len = len;
     s.groups = (unsigned)((total + len - 1) / len);
   }
+  if (plane_times) *plane_times = cost;
   return s;
+}
+
+// The column kernel against the split launches, in plane times of 5.8 us.  A
+// plane of a tile costs that whatever part of its 15 x 16 columns the grid has,
+// and a grid of few planes per CU pays for whole ones; the split launches cost
+// 20 us a stage (13 more for a right-hand side alone, which fuses less) and 88 ps
+// for every cell of their tiles (16 wide along x, 15 deep along z), twice that
+// beyond 2^19, where their arrays leave the caches.  The body force by itself
+// costs the column form 5 us more (k_force3 against the face fluxes at hand).
+// Where at least two thirds of the tiles' columns are the grid's own the column
+// form is kept: ahead or even by itself (64^3: 46 us a stage, 47 split), and up
+// to 1.3 times ahead in batches, whose members take the kernels that they take
+// alone.  Steps in us, columns and split: 256 x 4 x 256: 324 and 186;
+// 128 x 17 x 128: 202 and 161; 46 x 17 x 200: 158 and 116; 64^3 with the body
+// force: 174 and 162; 128 x 16 x 128: 124 and 158; 256 x 20 x 256: 639 and 646.
+static bool stage3_wins(const Dev &g, double split_start) {
+  const bool force = g.source != SRC_NONE;
+  const long nx = g.n[0], ny = g.n[1], nz = g.n[2];
+  const long tiles = (nx + 14) / 15 * ((ny + 15) / 16);
+  if (!force && 3 * nx * ny >= 2 * 240 * tiles) return true;
+  const double cells = (double)((nx + 15) / 16 * 16 * ny) * (double)((nz + 14) / 15 * 15);
+  const double split = split_start - (force ? 0.95 : 0.0) + cells / 65536.0 +
+                       std::max(0.0, cells - 524288.0) / 65536.0;
+  double columns;
+  (void)stage3_split(g, 256, &columns);
+  return columns <= split;
 }
 
 // Large 2D grids with TENO6-A take the split launches: bound by FP64 issue, they
@@ -1161,11 +1196,11 @@ static bool stage2_wins(const Dev &g, long most, long most_force) {
 }
 
 bool stage_fused(const Dev &g) {
-  if (g.ndim == 3) return stage3_takes(g);
+  if (g.ndim == 3) return stage3_takes(g) && stage3_wins(g, 3.5);
   return g.ndim == 1 || stage2_wins(g, 300000, 100000);
 }
 bool rhs_fused(const Dev &g) {
-  if (g.ndim == 3) return stage3_takes(g);
+  if (g.ndim == 3) return stage3_takes(g) && stage3_wins(g, 5.75);
   return g.ndim == 1 || stage2_wins(g, 800000, 150000);
 }
 unsigned stage_tiles(const Dev &g) {
@@ -1366,7 +1401,7 @@ kb_stage3(const BatchEntry *tab, int n, int stage, double cfl) {
 }
 
 unsigned long stage_work(const Dev &g) {
-  if (!stage3_takes(g)) return 0;
+  if (g.ndim != 3 || !stage_fused(g)) return 0;
   return (unsigned long)tiles_along(g.n[0], Col3<true>::TX) * tiles_along(g.n[1], Col3<true>::TY) *
          (unsigned long)g.n[2];
 }

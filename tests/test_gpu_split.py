@@ -52,7 +52,11 @@ def _member(kind, k):
     return {"power": lambda: _case((7 + k, 9, 5), (P2, W2, Z2)),
             "suth": lambda: _case((16, 5 + k, 8), (W2, P2, P2), "sutherland"),
             "disturb": lambda: _case((6 + k, 8, 7), (P2, W2, D2)),
-            "dirichlet": lambda: _dirichlet((9, 6 + k, 5))}[kind]()
+            "dirichlet": lambda: _dirichlet((9, 6 + k, 5)),
+            # beyond 2^17 cells: in launches of its own
+            "large": lambda: _case((52, 51 + k, 50), (P2, D2, W2)),
+            # few cells per tile: split although its faces are plain
+            "thin": lambda: _case((128, 3, 128 + k), (W2, P2, Z2))}[kind]()
 
 
 def _dirichlet(n):
@@ -70,6 +74,7 @@ ORDERS = {
     "split_around": ("dirichlet", "power", "disturb"),
     "split_alone": ("disturb", "dirichlet"),
     "two_laws": ("suth", "power", "suth"),
+    "large": ("large", "power", "disturb", "large", "dirichlet", "thin", "suth"),
 }
 
 

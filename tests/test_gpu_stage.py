@@ -131,6 +131,41 @@ def test_long_chains_equal_single_steps(n, nsteps):
     assert torch.equal(U, V) and torch.equal(dt, dv)
 
 
+# Grids whose stages (and right-hand sides) take the split launches though the
+# one-launch kernels could: thin or ragged tiles, the body force on a small box;
+# and neighbours of theirs that do not.
+ROUTES = {
+    "3d_thin": ((128, 3, 128), (P2, W2, Z2)),
+    "3d_thin_inviscid": ((130, 4, 127), (P2, P2, W2), "none"),
+    "3d_ragged": ((33, 17, 129), (Z2, W2, P2), "sutherland"),
+    "3d_full_tiles": ((30, 32, 129), (P2, W2, P2)),
+    "3d_force": ((16, 16, 16), (P2, W2, P2), "power", "weno5", "massflux"),
+    "3d_force_walls": ((16, 15, 17), (W2, W2, W2), "power", "weno5", "massflux"),
+    "3d_force_column": ((24, 24, 24), (P2, W2, P2), "power", "weno5", "massflux"),
+}
+
+
+@pytest.mark.parametrize("which", list(ROUTES))
+def test_both_routes_of_a_stage(which):
+    case = _case(*ROUTES[which])
+    print(f"[stage] route {which}", flush=True)
+    o, s = Oracle(case), Solver(case)
+    U0 = o.cons(W.random_smooth(case, seed=5, amp=0.1))
+    U = torch.as_tensor(U0, device="cuda")
+    err = rel_err_per_var(s.rhs(U).cpu().numpy(), o.rhs(U0), flux_scale(case, U0))
+    assert np.all(err <= RHS_TOL), err
+    dt = s.compute_dt(U, cfl=0.5)
+    V, dv = U.clone(), dt.clone()
+    s.steps_cfl(U, dt, 2, cfl=0.5)
+    s.step_cfl(V, dv, cfl=0.5)
+    ref, _, _ = o.run(U0, 1, dt_fixed=o.dt(U0, 0.5))
+    err = rel_err_per_var(V.cpu().numpy(), ref, np.full(case.nv, np.abs(ref).max()))
+    assert np.all(err <= STEP_TOL / 3), err  # three stages, not nine
+    s.step_cfl(V, dv, cfl=0.5)
+    assert s.flags() == 0
+    assert torch.equal(U, V) and torch.equal(dt, dv)
+
+
 # Large 2D grids with TENO6-A take the split launches.  (Against the oracle the
 # scheme's cut-off would fall either way on rounding somewhere in so many faces.)
 # A field that repeats along x takes the same cut-offs in both routes: its
