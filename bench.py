@@ -589,7 +589,9 @@ def main():
     in_loop_name = {w: one_launch or names[w] for w in probed}
 
     def in_loop_roof(w, t_ms):
-        return stage_roof(t_ms) if one_launch else kernel_roof(w, t_ms)
+        # (a short 1D line's launch runs all stages of many steps)
+        n_stages = 3.0 * args.steps / probed[w][0] if one_launch == "k_line" else 1.0
+        return stage_roof(t_ms / n_stages) if one_launch else kernel_roof(w, t_ms)
 
     if probed:
         dom = max(probed, key=lambda w: probed[w][0] * probed[w][1])

@@ -362,10 +362,12 @@ dcf_status dcf_time_kernel(dcf_ctx *ctx, const double *U_dev, int which, int rep
  * dcf_rk3_steps_cfl) make is bracketed by a pair of HIP events recorded on
  * that call's stream, up to max_launches launches (later ones are not
  * recorded).  Where a stage is one launch, that launch is bracketed whichever
- * id is armed (8: not the first stage of a call).  The events are created here
- * and owned by the context.  dcf_probe_end waits for the last recorded event, returns the
- * number of recorded launches and their mean duration in milliseconds, and
- * releases the events (a later dcf_probe_begin may arm again).  DCF_EINVAL for
+ * id is armed (8: not the first stage of a call); a 1D line of fewer than 1024
+ * cells without a source runs up to 2048 steps of a call in one launch, bracketed
+ * as one (8: not at all).  The events are created here and owned by the
+ * context.  dcf_probe_end waits for the last recorded event, returns the number
+ * of recorded launches and their mean duration in milliseconds, and releases
+ * the events (a later dcf_probe_begin may arm again).  DCF_EINVAL for
  * an id that cannot be probed, max_launches outside [1, 2^20], arming twice or
  * ending an unarmed probe. */
 dcf_status dcf_probe_begin(dcf_ctx *ctx, int which, int max_launches);

@@ -514,6 +514,16 @@ struct PendingDt {
   double *dt;  // the step (also what the stages read)
 };
 
+// One launch of a resident line; it does the work of every probed family but 8
+// (it holds the first stage of the call).
+static dcf_status line_launch(dcf_ctx *c, const LineArgs &A, hipStream_t st) {
+  Probe &pr = c->probe;
+  if (pr.which != 8) pr.before(pr.which, st);
+  DCF_HIP(launch_line(c->g, A, st));
+  if (pr.which != 8) pr.after(pr.which, st);
+  return DCF_OK;
+}
+
 // Fused steps chain their primitive boxes: stage k of a step works on box
 // (base + k) & 1 (0: g.Q, 1: qalt).  With box_ready the interior of the
 // first stage's box already holds the primitives of U (written by the
@@ -541,8 +551,7 @@ static dcf_status rk3_stages(dcf_ctx *c, double *U, const double *dt, hipStream_
     A.U2 = U2;
     A.nsteps = 1;
     A.nstages = nstages;
-    DCF_HIP(launch_line(g, A, st));
-    return DCF_OK;
+    return line_launch(c, A, st);
   }
   if (!U1) U1 = c->U1;
   if (!U2) U2 = c->U2;
@@ -638,7 +647,7 @@ static dcf_status line_steps_cfl(dcf_ctx *c, double *U, const double *dt, int ns
   A.dt_next = dt_next;
   while (nsteps > 0) {
     A.nsteps = std::min(nsteps, 2048);
-    DCF_HIP(launch_line(c->g, A, st));
+    if (dcf_status s = line_launch(c, A, st)) return s;
     nsteps -= A.nsteps;
     A.dt = dt_next;
   }

@@ -149,3 +149,23 @@ def test_probe_argument_errors():
     assert L.dcf_probe_begin(s.ctx, 7, 10) == -1  # armed twice
     assert L.dcf_probe_end(s.ctx, C.byref(n), C.byref(ms)) == 0
     assert n.value == 0 and ms.value == 0.0
+
+
+def test_probe_counts_launches_of_short_lines():
+    # a line that one workgroup steps: a launch per single step, one for the
+    # steps of a call (up to 2048), none of family 8
+    print("[probe] sod 200", flush=True)
+    case, P = W.sod(200)
+    s = Solver(case)
+    U = s.init_state(P)
+    dt = s.compute_dt(U, cfl=0.4)
+    s.probe_begin(1, 100)
+    for _ in range(3):
+        s.step(U, dt)
+    s.step_cfl(U, dt, cfl=0.4)
+    s.steps_cfl(U, dt, 5, cfl=0.4)
+    n, ms = s.probe_end()
+    assert n == 5 and ms > 0.0
+    s.probe_begin(8, 100)
+    s.steps_cfl(U, dt, 5, cfl=0.4)
+    assert s.probe_end()[0] == 0
