@@ -151,15 +151,15 @@ __device__ void hllc_vjp(const double *qL, const double *qR, double gamma, doubl
   double mL = rL * (SL - uL), mR = rR * (SR - uR);
   double Nn = pR - pL + uL * mL - uR * mR, Dd = mL - mR;
   const double iDd = rcp_nr(Dd);
-  double Ss = Nn * iDd;
-  const bool left = 0.0 <= fmin(fmax(Ss, SL), SR);
+  double Ss = fma(Nn, iDd, 0.0);
+  const bool left = hllc_left(SL, Ss, SR);
   double r = left ? rL : rR, u = left ? uL : uR, v = left ? vL : vR, w = left ? wL : wR;
   double p = left ? pL : pR, E = left ? EL : ER, SK = left ? SL : SR, m = left ? mL : mR;
   double inv = rcp_nr(SK - Ss);
   // a supersonic face (0 <= SL: left, or SR < 0: right) has the flux of its
   // side alone: the wave term has weight S = 0 there, and the adjoint of the
   // clamped speed is dropped (selections only, as in the forward)
-  const bool sub = left ? SL < 0.0 : 0.0 <= SR;
+  const bool sub = hllc_subsonic(SL, SR);
   const double S = sub ? SK : 0.0;
   double Us0 = m * inv;
   double A4 = m * Ss + p;

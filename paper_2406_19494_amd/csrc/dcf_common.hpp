@@ -274,6 +274,17 @@ __device__ __forceinline__ void weno5_pair(double v0, double v1, double v2, doub
   yr = fma(nr * dl, r, v3);
 }
 
+// The side whose state a face takes (0 <= SL: left; SR < 0: right; else left
+// where 0 <= S*), and whether its wave term counts (SL < 0 <= SR): on the sign
+// bits, as none of the three speeds is -0 (192 x 128 x 128: 0.2 % over a selection
+// by S* alone, 0.7 % with S* clamped to [SL, SR]).
+__device__ __forceinline__ bool hllc_left(double SL, double Ss, double SR) {
+  return (__double2hiint(SL) & (__double2hiint(SR) | __double2hiint(Ss))) >= 0;
+}
+__device__ __forceinline__ bool hllc_subsonic(double SL, double SR) {
+  return (__double2hiint(SL) & ~__double2hiint(SR)) < 0;
+}
+
 // HLLC flux in the face frame.  q = (rho, u_n, u_t1, u_t2, p) on each side;
 // F = (mass, normal momentum, t1 momentum, t2 momentum, energy).  Ties at
 // 0 <= S select the left-side state.  Star state written with one
@@ -289,14 +300,14 @@ __device__ __forceinline__ void hllc(const double *qL, const double *qR, double 
   double SL = fmin(uL - cL, uR - cR);
   double SR = fmax(uL + cL, uR + cR);
   double mL = rL * (SL - uL), mR = rR * (SR - uR);
-  double Ss = (pR - pL + uL * mL - uR * mR) * rcp_nr(mL - mR);
-  // S* lies between SL and SR where both pressures are positive.  Where one is
-  // not, its sound speed is NaN, fmin and fmax leave that side out, and S* can
-  // lie on either side of 0: clamped, it selects the upwind side of a
-  // supersonic face all the same.  There the selected side's wave term vanishes,
-  // F = F(U_K) (selections only: a branch would end the block in which this
-  // arithmetic and the reconstructions hide each other's latencies).
-  const bool left = 0.0 <= fmin(fmax(Ss, SL), SR);
+  double Ss = fma(pR - pL + uL * mL - uR * mR, rcp_nr(mL - mR), 0.0);  // (+0, not -0)
+  // On a supersonic face the upwind side's wave term vanishes, F = F(U_K), also
+  // where S* points the other way: where a reconstructed pressure is not
+  // positive its sound speed is NaN, fmin and fmax leave that side out, and S*
+  // need not lie between SL and SR (selections only: a branch would end the
+  // block in which this arithmetic and the reconstructions hide each other's
+  // latencies).
+  const bool left = hllc_left(SL, Ss, SR);
   const double SLm = fmin(SL, 0.0), SRp = fmax(SR, 0.0);
   double r = left ? rL : rR, u = left ? uL : uR, v = left ? vL : vR, w = left ? wL : wR;
   double p = left ? pL : pR, S = left ? SL : SR, m = left ? mL : mR;
