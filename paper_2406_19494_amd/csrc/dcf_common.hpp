@@ -163,10 +163,10 @@ __device__ __forceinline__ double sound_speed(double gamma, double rho, double p
 // range: with x = m 2^e, m in [sqrt(1/2), sqrt(2)), and s = (m - 1)/(m + 1),
 // log m = 2 atanh s = 2 s sum_k s^{2k} / (2k + 1), |s| < 0.1716; and exp as 2^n
 // times the Taylor series of the remainder, |r| <= log(2)/2.  Both series are cut
-// below 1e-17 of their sum; what the leading terms of w log x lose to rounding
-// is carried in a second word.  Error of x^0.7 in ulp, largest and rms: 0.70
-// and 0.23 over x in [1/2, 2], 0.64 and 0.24 over [0.05, 20] (exp and log of
-// the math library: 0.65 and 0.23, 1.5 and 0.36), at 110 instead of 150
+// below 3e-17 of their sum; what the leading terms of w log x and of the last sum
+// lose to rounding is carried in a second word.  Error of x^0.7 in ulp, largest
+// and rms: 0.8 and 0.29 over x in [1/2, 2] and over [0.05, 20] (exp and log of
+// the math library 1.0 and 0.31, 2.9 and 0.50), at 113 instead of 150
 // instructions.
 __device__ __forceinline__ double pow_positive(double x, double w) {
   double m = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
@@ -177,8 +177,7 @@ __device__ __forceinline__ double pow_positive(double x, double w) {
   const double ln2 = 0.69314718055994531, ln2lo = 2.3190468138462996e-17;
   const double a = m - 1.0, b = m + 1.0, rb = rcp_nr(b);
   const double s = a * rb, z = s * s, s2 = s + s;
-  double t = 1.0 / 21.0;
-  t = fma(t, z, 1.0 / 19.0);
+  double t = 1.0 / 19.0;
   t = fma(t, z, 1.0 / 17.0);
   t = fma(t, z, 1.0 / 15.0);
   t = fma(t, z, 1.0 / 13.0);
@@ -193,7 +192,7 @@ __device__ __forceinline__ double pow_positive(double x, double w) {
   const double l = h + s2, llo = ((h - l) + s2) + small;
   const double y = w * l, ylo = fma(w, l, -y) + w * llo;
   const double n = __builtin_rint(y * 1.4426950408889634);
-  const double r = fma(n, -ln2, y) + fma(n, -ln2lo, ylo);
+  const double r0 = fma(n, -ln2, y), rlo = fma(n, -ln2lo, ylo), r = r0 + rlo;
   double p = 1.0 / 6227020800.0;
   p = fma(p, r, 1.0 / 479001600.0);
   p = fma(p, r, 1.0 / 39916800.0);
@@ -206,7 +205,9 @@ __device__ __forceinline__ double pow_positive(double x, double w) {
   p = fma(p, r, 1.0 / 24.0);
   p = fma(p, r, 1.0 / 6.0);
   p = fma(p, r, 0.5);
-  p = 1.0 + fma(r * r, p, r);
+  // 1 + r0 and what it loses to rounding, so that the last sum alone rounds
+  const double hi = 1.0 + r0, lo = (1.0 - hi) + r0;
+  p = hi + fma(r * r, p, lo + rlo);
   p = __builtin_amdgcn_ldexp(p, (int)n);
   return x > 0.0 ? p : __builtin_nan("");
 }
