@@ -78,7 +78,7 @@ struct dcf_ctx {
   int ws_mode = -1;
   int ws_nsteps = 0, ws_seg = 0;
   double *U1 = nullptr, *U2 = nullptr, *part = nullptr, *force = nullptr;
-  double *dtpart = nullptr;  // per-block signal rates of the last stage (fused CFL step)
+  double *dtpart = nullptr;  // per-block signal rates of the last stage (dt_maxima)
   BoxOut qalt;               // second primitive box (fused stages alternate the two)
   AdjBuffers adj;
   double *ckpt = nullptr;  // gradient checkpoints
@@ -291,7 +291,7 @@ static size_t carve(dcf_ctx *c, void *base, int mode, int nsteps, int seg_len) {
   c->U2 = cv.take<double>(nv * ncell);
   c->part = cv.take<double>(8 * RED_BLOCKS);
   c->force = cv.take<double>(4);
-  c->dtpart = cv.take<double>(std::max({update_blocks(g), flux_update_blocks(g), stage_tiles(g)}));
+  c->dtpart = cv.take<double>(std::max(update_blocks(g), flux_update_blocks(g)));
   g.flags = cv.take<unsigned>(64);
   for (int q = 0; q < NQ; ++q) c->qalt.Q[q] = g.ndim >= 2 ? cv.take<double>(nbox) : nullptr;
   if (mode >= 1) carve_adjoint(cv, g, c->adj);
@@ -500,14 +500,17 @@ static hipError_t stage_source(dcf_ctx *c, StageArgs &A, hipStream_t st) {
   return e;
 }
 
-// Partial maxima the last stage of a step leaves in dtpart.
+// Where the last stage of a step leaves its partial maxima, and how many.  (A
+// one-launch stage has more tiles than the split kernels blocks on some grids; it
+// leaves the x face fluxes' array unused, five doubles a cell.)
+static double *dt_maxima(const dcf_ctx *c) { return stage_fused(c->g) ? c->g.F[0] : c->dtpart; }
 static unsigned dt_parts(const dcf_ctx *c) {
   if (stage_fused(c->g)) return stage_tiles(c->g);
   return fused_stages(c) ? flux_update_blocks(c->g) : update_blocks(c->g);
 }
 
 // A CFL step reduction left pending by the previous step (nparts partial
-// maxima in dtpart): the next fused step runs it with its first ghost fill.
+// maxima in dt_maxima): the next fused step runs it with its first ghost fill.
 struct PendingDt {
   int nparts;
   double cfl, dt_max;
@@ -573,7 +576,7 @@ static dcf_status rk3_stages(dcf_ctx *c, double *U, const double *dt, hipStream_
       if (boxes) A.box = boxes[k];
       if (g.source == SRC_MASSFLUX) DCF_HIP(stage_source(c, A, st));
       if (k == 0 && pend) {
-        A.part = c->dtpart;
+        A.part = dt_maxima(c);
         A.nparts = pend->nparts;
         A.cfl = pend->cfl;
         A.dt_max = pend->dt_max;
@@ -843,9 +846,9 @@ dcf_status dcf_rk3_step_cfl(dcf_ctx *c, double *U, const double *dt, double cfl,
   if (!(dt_max > 0.0)) dt_max = 1.0e300;
   hipStream_t st = (hipStream_t)stream;
   if (line_resident(c->g)) return line_steps_cfl(c, U, dt, 1, cfl, dt_max, dt_next, st);
-  if ((s = rk3_stages(c, U, dt, st, nullptr, nullptr, c->dtpart))) return s;
+  if ((s = rk3_stages(c, U, dt, st, nullptr, nullptr, dt_maxima(c)))) return s;
   const unsigned nparts = dt_parts(c);
-  DCF_HIP(launch_dt_final(c->dtpart, (int)nparts, cfl, dt_max, dt_next, st));
+  DCF_HIP(launch_dt_final(dt_maxima(c), (int)nparts, cfl, dt_max, dt_next, st));
   return DCF_OK;
 }
 
@@ -861,6 +864,7 @@ dcf_status dcf_rk3_steps_cfl(dcf_ctx *c, double *U, double *dt, int nsteps, doub
   if (line_resident(c->g)) return line_steps_cfl(c, U, dt, nsteps, cfl, dt_max, dt, st);
   const bool one_launch = stage_fused(c->g), fused = one_launch || fused_stages(c);
   const unsigned nparts = dt_parts(c);
+  double *const parts = dt_maxima(c);
   const PendingDt pend{(int)nparts, cfl, dt_max, dt};
   bool pending = false;
   for (int n = 0; n < nsteps; ++n) {
@@ -868,13 +872,13 @@ dcf_status dcf_rk3_steps_cfl(dcf_ctx *c, double *U, double *dt, int nsteps, doub
     // first starts from the primitive box the previous one left, and its
     // first ghost fill finishes the previous step's CFL reduction
     const bool chained = fused && n + 1 < nsteps;
-    if ((s = rk3_stages(c, U, dt, st, nullptr, nullptr, c->dtpart, n & 1, fused && n > 0, chained,
+    if ((s = rk3_stages(c, U, dt, st, nullptr, nullptr, parts, n & 1, fused && n > 0, chained,
                         pending ? &pend : nullptr)))
       return s;
     // a stage launch's workgroups reduce the partial maxima themselves, each
     // of them: only while they are few
     pending = chained && (!one_launch || nparts <= 2048);
-    if (!pending) DCF_HIP(launch_dt_final(c->dtpart, (int)nparts, cfl, dt_max, dt, st));
+    if (!pending) DCF_HIP(launch_dt_final(parts, (int)nparts, cfl, dt_max, dt, st));
   }
   return DCF_OK;
 }

@@ -74,3 +74,18 @@ def test_noalloc_rejects_a_case_beyond_the_scratch():
     with pytest.raises(B.DcfError) as ei:
         _noalloc_step(bare, U, dt, flags)
     assert ei.value.code == -5  # DCF_EBUDGET
+
+
+def test_noalloc_takes_narrow_grids_up_to_the_scratch():
+    # 3 x 16521 cells fill the scratch to a few KB: their small tiles' partial
+    # maxima must not add to it
+    case = W.Case(name="narrow", ndim=2, n=(3, 16521, 1), hi=(0.3, 1652.1, 1.0), R=1.3, Pr=0.7,
+                  visc_law="power", mu_ref=0.01, T_ref=1.0, visc_param=0.7)
+    ref, bare = Solver(case), Solver(case, mode=-1)
+    U = ref.init_state(W.random_smooth(case, seed=3, amp=0.1))
+    V = U.clone()
+    dt = ref.compute_dt(U, cfl=0.4)
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ref.step(U, dt)
+    _noalloc_step(bare, V, dt, flags)
+    assert torch.equal(U, V) and int(flags.item()) == 0 and ref.flags() == 0
