@@ -123,8 +123,10 @@ dcf_status dcf_state_info(const dcf_ctx *ctx, int *nv, long *ncell, size_t *stat
  * the primitive box of every stage of a segment from the forward recompute,
  * so the reverse sweep recomputes nothing of the forward (3 seg_len more
  * boxes of memory; bitwise the same gradient).
- * nsteps/seg_len are ignored below mode 2.  The library keeps the pointer
- * until the next call, clears the parts that must start at zero (the call
+ * nsteps/seg_len are ignored below mode 2.  Ask for the size, do not store it:
+ * it depends on the kernels of the library at hand (modes 1 to 3 of 3D grids of
+ * up to 2^18 cells hold 17 more boxes than larger ones).  The library keeps the
+ * pointer until the next call, clears the parts that must start at zero (the call
  * returns once that is done) and owns the contents from then on: the caller
  * must not write into the workspace. */
 dcf_status dcf_workspace_size(const dcf_ctx *ctx, int mode, int nsteps, int seg_len,
@@ -283,7 +285,7 @@ dcf_status dcf_batch_rk3_step(dcf_ctx *const *ctxs, double *const *U, double *co
  * launches alone: they read the table from table_dev (dev, a copy of
  * table_host, which must stay unchanged while launches or graph replays that
  * use it are pending); table_host is read during the call for the launch
- * sizes.  It enqueues kernels only (no copy, no allocation), so it may be
+ * sizes (and the launches of members that run by themselves).  It enqueues kernels only (no copy, no allocation), so it may be
  * captured; the contexts, states and steps named in the table must outlive
  * every replay.  Bitwise the same results as dcf_batch_rk3_step. */
 dcf_status dcf_batch_table_fill(dcf_ctx *const *ctxs, double *const *U, double *const *dt, int n,

@@ -461,9 +461,9 @@ __device__ __forceinline__ void dir_vjp_tile(const Dev &g, const AdjBuffers &A, 
     fetch(0);
     hllc_vjp(qL, qR, g.gamma, g.gm1i, Fr, qLb, qRb);
   }
-  // convective, per component: reverse the two reconstructions, stage the
-  // contributions to cells f-3 .. f+2 in LDS, then gather them per window
-  // cell in a fixed order of faces (deterministic, no atomics)
+  // convective, per component: reverse the two reconstructions, then sum the
+  // contributions to cells f-3 .. f+2 per window cell by lane shuffles, in a
+  // fixed order of faces (deterministic, no atomics)
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     const bool act = !((m == 2 && T1 >= NDIM) || (m == 3 && T2 >= NDIM));
@@ -821,14 +821,6 @@ template <int NDIM> struct HaloQ {
                                 NDIM == 3 ? QW : (NDIM == 2 ? QP : QT), NDIM == 3 ? QP : QT, QT};
 };
 
-// Source cell of ghost layer m (0 nearest the face) on side `side` of an axis
-// of n cells: the cell the forward halo fill copies (and mirrors) into it.
-__device__ __forceinline__ int halo_source(int kind, int side, int m, int n) {
-  if (kind == BC_PERIODIC) return side == 0 ? n - 1 - m : m;
-  if (kind == BC_ZEROGRAD) return side == 0 ? 0 : n - 1;
-  return side == 0 ? m : n - 1 - m;
-}
-
 // A ghost adjoint mapped to its contribution to the source: copies pass
 // through; walls: p_g = p_s, u_g = -u_s (plus a prescribed normal part that
 // depends on the state only through the porous p_w, taken separately);
@@ -938,7 +930,7 @@ __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int
 #pragma unroll 1
     for (int side = 0; side < 2; ++side) {
       const int kind = g.bck[4 + side];
-      if (kind != BC_DISTURB || p[2] != halo_source(kind, side, 0, g.n[2])) continue;
+      if (kind != BC_DISTURB || p[2] != ghost_source(kind, side, 0, g.n[2])) continue;
       double vsum = 0.0;
       if (gather)
 #pragma unroll 1
@@ -969,7 +961,7 @@ __device__ __forceinline__ void ghost_vjp(const Dev &g, const AdjBuffers &A, int
 // Launch and memory latency bound, a thread per ghost (1024 x 256: 5.7 us; this
 // kernel and the collection in k_interior_vjp, 13.3 to 15.1 us, took the place
 // of a 4.9 us gather and a transpose launch of 6.2 us per axis; 65 x 49 x 33:
-// 16 us and 9.4 to 17.4 for 7.2 and three of 7.0).
+// 10.4 us and 9.4 to 17.4 for 7.2 and three of 7.0).
 template <int NDIM, bool ALL3>
 __global__ void __launch_bounds__(64)
 k_ghost_vjp(Dev g, AdjBuffers A, int want_dk) {

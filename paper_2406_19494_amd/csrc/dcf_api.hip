@@ -1020,23 +1020,16 @@ static dcf_status segment_step(dcf_ctx *c, int k, hipStream_t st) {
     const double a[3] = {0.0, 0.75, 1.0 / 3.0}, b[3] = {1.0, 0.25, 2.0 / 3.0};
     for (int s = 0; s < 3; ++s) {
       const Dev gs = stage_box(c, k, s);
-      if (fused_stages(c)) {
-        // as rk3_stages: each update writes the interior of the next
-        // stage's cached box
-        BoxOut next;
-        if (s < 2) {
-          const Dev gn = stage_box(c, k, s + 1);
-          for (int q = 0; q < NQ; ++q) next.Q[q] = gn.Q[q];
-        }
-        if (s == 0) DCF_HIP(launch_prim_halo(gs, in[s], st));
-        else DCF_HIP(launch_prim_ghost(gs, st));
-        DCF_HIP(launch_fluxes_update(gs, Ub, in[s], out[s], gr.dt, a[s], b[s], nullptr, st,
-                                     next));
-      } else {
-        DCF_HIP(launch_prim_halo(gs, in[s], st));
-        DCF_HIP(launch_fluxes(gs, st));
-        DCF_HIP(launch_update(gs, Ub, in[s], out[s], nullptr, gr.dt, a[s], b[s], nullptr, st));
+      // as rk3_stages: each update writes the interior of the next stage's
+      // cached box
+      BoxOut next;
+      if (s < 2) {
+        const Dev gn = stage_box(c, k, s + 1);
+        for (int q = 0; q < NQ; ++q) next.Q[q] = gn.Q[q];
       }
+      if (s == 0) DCF_HIP(launch_prim_halo(gs, in[s], st));
+      else DCF_HIP(launch_prim_ghost(gs, st));
+      DCF_HIP(launch_fluxes_update(gs, Ub, in[s], out[s], gr.dt, a[s], b[s], nullptr, st, next));
     }
     return DCF_OK;
   }

@@ -59,6 +59,8 @@ __device__ __forceinline__ void cons_to_prim(const Dev &g, const double *U, long
 // interior (or to a Dirichlet profile) and applies the per-axis ghost
 // transforms in x, y, z order.
 // ---------------------------------------------------------------------------
+// Source cell of ghost layer m (0 nearest the face) on side `side` of an axis of
+// n cells.
 __device__ __forceinline__ int ghost_source(int kind, int side, int m, int n) {
   if (kind == BC_PERIODIC) return side == 0 ? n - 1 - m : m;
   if (kind == BC_ZEROGRAD) return side == 0 ? 0 : n - 1;

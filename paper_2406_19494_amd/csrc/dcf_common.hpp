@@ -345,9 +345,10 @@ __device__ __forceinline__ void hllc(const double *qL, const double *qR, double 
 // refined hardware ones (no IEEE division), one for the least ratio, one for a
 // side's four measures and one for both values: 5 per component where each
 // quotient had its own, 14.
-// The flux launches are bound by the issue of this arithmetic (VALU busy 87 %):
-// x + y faces of 256 x 128 x 128 in 638 us, 748 with the 14 reciprocals and 115
-// VGPRs (4 wavefronts per SIMD; 95 and 5 now), z faces + update 422 and 473.
+// The flux launches are bound by the issue of this arithmetic (VALU busy 87 % in
+// the x + y launch, 80 % in z + update: 192 x 128 x 128, 489 and 320 us): x + y
+// faces of 256 x 128 x 128 in 638 us, 748 with the 14 reciprocals and 115 VGPRs
+// (4 wavefronts per SIMD; 95 and 5 now), z faces + update 422 and 473.
 __device__ __forceinline__ void teno6a_pair(double v0, double v1, double v2, double v3, double v4,
                                             double v5, double &yl, double &yr) {
   constexpr double c1312 = 13.0 / 12.0;

@@ -407,7 +407,7 @@ k_stage2(Dev g, StageArgs A, unsigned nbx) {
 // The two kinds run loops of their own with the same number of barriers, so
 // that the windows of the one and the face stencils of the other never share
 // registers (in one loop they do not fit 256 VGPRs: 250 spills per plane, 1250
-// us per stage of 192 x 128 x 128).  So: 340 to 353 us, VALU busy 60 %, 0.95 GB of
+// us per stage of 192 x 128 x 128).  So: 335 to 353 us, VALU busy 60 %, 1.0 GB of
 // HBM traffic, for 522 us and 2.3 GB in ghost, x + y flux, z flux + update and
 // force launches; 64^3: 50 us for 53.
 // ---------------------------------------------------------------------------
