@@ -285,9 +285,10 @@ dcf_status dcf_batch_rk3_step(dcf_ctx *const *ctxs, double *const *U, double *co
  * launches alone: they read the table from table_dev (dev, a copy of
  * table_host, which must stay unchanged while launches or graph replays that
  * use it are pending); table_host is read during the call for the launch
- * sizes (and the launches of members that run by themselves).  It enqueues kernels only (no copy, no allocation), so it may be
- * captured; the contexts, states and steps named in the table must outlive
- * every replay.  Bitwise the same results as dcf_batch_rk3_step. */
+ * sizes (and the launches of members that run by themselves).  It enqueues
+ * kernels only (no copy, no allocation), so it may be captured; the contexts,
+ * states and steps named in the table must outlive every replay.  Bitwise the
+ * same results as dcf_batch_rk3_step. */
 dcf_status dcf_batch_table_fill(dcf_ctx *const *ctxs, double *const *U, double *const *dt, int n,
                                 void *table_host, size_t table_bytes);
 dcf_status dcf_batch_rk3_step_table(const void *table_dev, const void *table_host, int n,
