@@ -1094,8 +1094,10 @@ __global__ void __launch_bounds__(256) k_force3(Dev g, const double *U, double *
 // ---------------------------------------------------------------------------
 // Small tiles up to 2^16 cells: there 16 x 16 tiles leave CUs without one, and
 // a tile's second round of faces (32 of 544) waits alone; above, their extra
-// halo conversions and idle lanes cost more (256 x 64: 7.9 against 9.8 us per
-// stage, 300 x 200: 10.5 against 10.8, 1024 x 256: 23.2 against 22.6).
+// halo conversions and idle lanes come to cost more.  Steps, small against 16 x 16
+// tiles, in us: 64^2 24.0 and 30.7, 200^2 25.4 and 28.9, 300 x 200 28.5 and 28.9,
+// 512 x 128 29.1 and 30.5; beyond the line the rounds of tiles decide: 300^2 32.0
+// and 35.1, 340^2 41.2 and 35.8, 360^2 45.3 and 49.7, 512 x 256 45.4 and 38.3.
 static bool stage2_small(const Dev &g) { return g.ncell <= 65536; }
 
 static unsigned tiles_along(int n, int t) { return (unsigned)((n + t - 1) / t); }
