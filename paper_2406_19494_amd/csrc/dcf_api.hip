@@ -476,7 +476,7 @@ static dcf_status eval_fluxes(dcf_ctx *c, const double *U, hipStream_t st) {
 // One RK3 step in place; the stage states go to U1, U2 (default: scratch).
 // The last direction's fluxes are fused into the stage update where there is
 // no source term, or the constant-mass-flux source with a periodic last
-// direction: the body force needs every boundary flux, and a periodic
+// direction: the body force needs every boundary flux, and a periodic last
 // direction's boundary terms vanish, so the force is reduced from the other
 // directions' fluxes before the fused kernel applies it.
 static bool fused_stages(const dcf_ctx *c) {
@@ -484,7 +484,8 @@ static bool fused_stages(const dcf_ctx *c) {
   if (g.ndim < 2) return false;
   if (g.source == SRC_NONE) return true;
   // the body force needs every boundary flux: only the last direction's can
-  // be left to the fused kernel, and only where they cancel (periodic)
+  // be left to the fused kernel, and only where they cancel (periodic; no later
+  // axis whose ghosts could make them differ)
   const int f = 2 * (g.ndim - 1);
   return g.source == SRC_MASSFLUX && g.bck[f] == BC_PERIODIC && g.bck[f + 1] == BC_PERIODIC;
 }

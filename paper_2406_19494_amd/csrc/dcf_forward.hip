@@ -499,18 +499,30 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double *sh /*[NV*BS]*
   for (int q = 0; q < NV; ++q) v[q] = sh[q * BS];
 }
 
+// Whether the two boundary faces of direction D see the same stencil values, so
+// that their fluxes are equal and their term of the body force is an exact zero:
+// on a periodic axis, unless a later axis has a face whose ghosts depend on the
+// position along the face (a strip's coefficients, a disturbance, a Dirichlet
+// profile).  Ghosts are filled axis by axis, so beyond the ends of D that face
+// takes the plain wall's values or the profile's end, not the periodic image, and
+// the viscous fluxes read them there; the faces of earlier axes are copied with it.
+__device__ __forceinline__ bool boundary_fluxes_equal(const Dev &g, int D) {
+  if (g.bck[2 * D] != BC_PERIODIC || g.bck[2 * D + 1] != BC_PERIODIC) return false;
+  for (int f = 2 * (D + 1); f < 2 * g.ndim; ++f)
+    if (g.bck[f] == BC_POROUS || g.bck[f] == BC_DISTURB || g.bck[f] == BC_DIRICHLET) return false;
+  return true;
+}
+
 // Body force, pass 1.  The volume-weighted sum of the unforced x-momentum
 // right-hand side, sum_c V_c R_c = -sum_D sum_c A_D (F_D(c+1/2) - F_D(c-1/2))
 // with A_D = V_c / dx_D constant along a grid line, telescopes along every
-// line to its two boundary faces: -sum_lines A_D (F_D(n) - F_D(0)).  (On a
-// periodic axis both boundary faces see the same stencil values, so their
-// fluxes are equal and cancel.)  Per-block partial sums of that boundary
-// term and of the volume, over one thread per boundary line.
+// line to its two boundary faces: -sum_lines A_D (F_D(n) - F_D(0)).  (On most
+// periodic axes these cancel: boundary_fluxes_equal.)  Per-block partial sums
+// of that boundary term and of the volume, over one thread per boundary line.
 // Directions D >= ndir are skipped (their faces not computed yet; the
 // caller guarantees that their boundary terms vanish, as for a periodic
-// direction, whose two boundary faces see the same stencil).  The grid and
-// the line-to-thread map do not depend on ndir, so the sums are bitwise
-// those over every direction.
+// last direction).  The grid and the line-to-thread map do not depend on
+// ndir, so the sums are bitwise those over every direction.
 __global__ void __launch_bounds__(256) k_force_partial(Dev g, double *part, int ndir) {
   __shared__ double sh[2 * 256];
   double v[2] = {0.0, 0.0};
@@ -531,9 +543,7 @@ __global__ void __launch_bounds__(256) k_force_partial(Dev g, double *part, int 
     double A = 1.0;
     if (T1 < nd) A *= g.dx[T1][a];
     if (T2 < nd) A *= g.dx[T2][b];
-    // a periodic direction's two boundary fluxes are equal: an exact zero,
-    // not read
-    if (!(g.bck[2 * D] == BC_PERIODIC && g.bck[2 * D + 1] == BC_PERIODIC)) {
+    if (!boundary_fluxes_equal(g, D)) {
       int p[3];
       p[T1] = a;
       p[T2] = b;
@@ -579,10 +589,8 @@ __device__ __forceinline__ double box_face_xmom_flux(const Dev &g, const int *p,
 
 // Body force, pass 1, from the primitive box alone (the adjoint's stages
 // have no face fluxes): the sums of k_force_partial over every direction,
-// with each boundary flux evaluated by box_face_xmom_flux.  A periodic
-// direction's two boundary faces see the same stencil values, so its terms
-// are exact zeros (not evaluated) and the sums equal k_force_partial's
-// bitwise.
+// with each boundary flux evaluated by box_face_xmom_flux (k_force_partial's
+// sums bitwise).
 template <int NDIM, bool VISC, int SCH>
 __global__ void __launch_bounds__(256) k_force_direct(Dev g, double *part) {
   __shared__ double sh[2 * 256];
@@ -606,8 +614,8 @@ __global__ void __launch_bounds__(256) k_force_direct(Dev g, double *part) {
     p[T1] = a;
     p[T2] = b;
     double F0 = 0.0, F1 = 0.0;
-    if (g.bck[2 * D] == BC_PERIODIC && g.bck[2 * D + 1] == BC_PERIODIC) {
-      // equal fluxes: an exact zero either way, not evaluated
+    if (boundary_fluxes_equal(g, D)) {
+      // an exact zero either way, not evaluated
     } else if (D == 0) {
       F0 = box_face_xmom_flux<NDIM, 0, VISC, SCH>(g, p, 0);
       F1 = box_face_xmom_flux<NDIM, 0, VISC, SCH>(g, p, g.n[0]);
